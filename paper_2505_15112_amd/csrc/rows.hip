@@ -4,13 +4,14 @@
 //
 // Two schedules, after the paper's observation that many short rows and a
 // few long rows want different mappings (its batched-scan crossover):
-//  * len <= one tile: one wavefront owns a whole row and walks it in chunks
-//    of 64 lanes x 4 elements with a running carry -- many rows per
+//  * rows of up to 1024: one wavefront owns a whole row and walks it in
+//    chunks of 64 lanes x 4 elements with a running carry -- many rows per
 //    workgroup, no inter-workgroup communication;
-//  * longer rows: each row is cut into tile-sized segments, tiles are handed
+//  * rows of up to 65536, unless a small batch leaves the chip idle: one
+//    workgroup per row, the whole row one register tile (k_rows_tile);
+//  * other rows: each row is cut into tile-sized segments, tiles are handed
 //    out row-major by ticket, and the decoupled look-back runs inside a row
-//    (it stops at the row's first segment), so 128 rows of 2^17 still give
-//    4096 workgroups to fill 256 CUs.
+//    (it stops at the row's first segment).
 // The top-p cutoff needs only one index per row: every tile sums its part of
 // the row and the row's last tile to finish locates the index (k_topp).
 // Weighted sampling of rows up to 2^22 and the cutoff of rows up to 2^20 run
@@ -41,12 +42,14 @@ __device__ __forceinline__ int32_t wave_min(int32_t v) {
 
 // ---------------------------------------------------------------- rows of one tile
 
-// Rows of 1025 to 4096 elements (a scan, not the top-p cutoff): one
-// workgroup per row, the whole row one tile (4 waves of 4 chunks of 64 lanes
-// x 4 when aligned), scanned in registers and stored; nothing crosses
-// workgroups.  A wavefront per row walks such a row in up to 16 dependent
-// steps; four waves take 4 each.  (The 128 x 4096 count tables of the row
-// sort: 7.7 against ~4 us per scan.)
+// Rows of 1025 to 65536 elements (a scan, not the top-p cutoff): one
+// workgroup per row, the whole row one tile of 4 to 16 waves (see rows_any),
+// scanned in registers and stored; nothing crosses workgroups, and no ticket
+// or look-back is paid.  Bound: HBM, one read and one write.  fp32, warm
+// passes over rotating inputs, against the look-back kernel on the row's
+// tiles: 2048 x 8192 62 -> 20 us, 1024 x 16384 64 -> 20, 512 x 32768 46 -> 20,
+// 256 x 65536 47 -> 21.5 (6.2 TB/s); the 128 x 4096 count tables of the row
+// sort 7.7 -> 4 (against a wavefront per row).
 constexpr int64_t kRowsTileMin = 1024;
 template <class TileT, bool EXCL, bool VEC>
 __global__ __launch_bounds__(TileT::kThreads) LS_OCCUPANCY4 void k_rows_tile(
@@ -786,22 +789,76 @@ static unsigned wave_grid(int64_t rows) {
     return (unsigned)(blocks < 65536 ? blocks : 65536);
 }
 
-template <class T, class G>
-static void rows_long(bool exclusive, bool vec, const T* x, T* y, int64_t rows, int64_t len,
-                      void* ws, size_t ws_bytes, hipStream_t stream) {
-    using TV = RowTile<T, G, true>;
-    using TU = RowTile<T, G, false>;
-    static_assert(TV::kElems == TU::kElems, "one tile size per geometry");
-    const uint32_t segs = (uint32_t)((len + TV::kElems - 1) / TV::kElems);
+// Row scan on tiles of TileT: one workgroup per row when the tile holds it,
+// else the look-back over the row's segments.
+template <class TileT, bool VEC>
+static void rows_tiles(bool exclusive, const typename TileT::T* x, typename TileT::T* y,
+                       int64_t rows, int64_t len, void* ws, size_t ws_bytes, hipStream_t stream) {
+    if (len <= TileT::kElems) {
+        auto k = exclusive ? k_rows_tile<TileT, true, VEC> : k_rows_tile<TileT, false, VEC>;
+        hipLaunchKernelGGL(k, dim3((unsigned)rows), dim3(TileT::kThreads), 0, stream, x, y, len);
+        return;
+    }
+    const uint32_t segs = (uint32_t)((len + TileT::kElems - 1) / TileT::kElems);
     const uint32_t nt = (uint32_t)(rows * segs);
     WsHeader* hdr = reinterpret_cast<WsHeader*>(ws);
     uint64_t* status = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(ws) + kWsHeader);
     const int64_t status_words = (int64_t)((ws_bytes - kWsHeader) / sizeof(uint64_t));
-    auto k = exclusive ? (vec ? k_rows_lookback<TV, true, true> : k_rows_lookback<TU, true, false>)
-                       : (vec ? k_rows_lookback<TV, false, true> : k_rows_lookback<TU, false, false>);
-    const unsigned threads = vec ? TV::kThreads : TU::kThreads;
-    hipLaunchKernelGGL(k, dim3(nt), dim3(threads), 0, stream, x, y, len, segs, nt, hdr, status,
-                       status_words);
+    auto k = exclusive ? k_rows_lookback<TileT, true, VEC> : k_rows_lookback<TileT, false, VEC>;
+    hipLaunchKernelGGL(k, dim3(nt), dim3(TileT::kThreads), 0, stream, x, y, len, segs, nt, hdr,
+                       status, status_words);
+}
+
+// Rows longer than kRowsTileMin.  A tile that holds the whole row needs no
+// look-back, so the smallest such tile is taken, except for batches too small
+// to fill the chip with rows, whose rows are cut up instead; rows that no
+// tile holds are cut into the largest tiles that still occupy the chip (n =
+// rows x len elements, fp32, us per call, inputs rotating, measured for every
+// geometry at each shape):
+//   1 x 12000:    look-back 4096  3.3, whole row 3.7;  1 x 20000: 3.7 / 4.3
+//   4 x 32768:    look-back 4096  4.2, whole row 4.0;  64 x 32768: 11.3 / 4.9
+//   8 x 65536:    look-back 8192  5.3, whole row 6.4;  32 x 65536:  8.6 / 6.9
+//   8 x 131072:   8192 6.5, 16384 6.4, 32768 7.4
+//   16 x 131072:  8192 8.5, 16384 7.7, 32768 8.2, 65536 10.8
+//   16 x 262144:  16384 10.7, 32768 9.9, 65536 12.1
+//   32 x 262144:  32768 15.2, 65536 14.8;  512 x 131072: 97 / 81
+// Misaligned rows (element-wise loads) stop at 32768 elements a tile:
+//   4 x 20003: look-back 4096 3.9, whole row 5.2;  64 x 20003: 9.3 / 6.2
+// The workspace holds (per row) one status word per 4096 elements up to
+// 65536, per 8192 up to 2^20, per 32768 above: smaller tiles are not taken.
+template <class T, bool VEC>
+static void rows_any(bool exclusive, const T* x, T* y, int64_t rows, int64_t len, void* ws,
+                     size_t ws_bytes, hipStream_t stream) {
+    // C chunks a lane and W waves when aligned, half the chunks and twice the
+    // waves when not (at most 16 of 8)
+#define LS_ROWS(W, C)                                                                    \
+    rows_tiles<Tile<T, T, kRVec, VEC ? (C) : ((W) < 16 ? (C) / 2 : 8),                    \
+                    VEC ? (W) : ((W) < 16 ? (W) * 2 : 16)>,                               \
+               VEC>(exclusive, x, y, rows, len, ws, ws_bytes, stream)
+    const int64_t n = rows * len;
+    const bool whole = len <= 8192 || (len <= 32768 && n > (VEC ? int64_t(1) << 15 : int64_t(1) << 20)) ||
+                       (len <= 65536 && n >= int64_t(1) << 20);
+    if (len <= kRowTile)
+        LS_ROWS(4, 4);
+    else if (len <= 8192)
+        LS_ROWS(8, 4);
+    else if (whole && len <= 16384)
+        LS_ROWS(8, 8);
+    else if (whole && len <= 32768)
+        LS_ROWS(16, 8);
+    else if (VEC && whole)
+        LS_ROWS(16, 16);
+    else if (len <= 65536 && n < int64_t(1) << 18)
+        LS_ROWS(4, 4);
+    else if (len <= int64_t(1) << 20 && n < int64_t(1) << 20)
+        LS_ROWS(8, 4);
+    else if (len <= int64_t(1) << 20 && n < int64_t(1) << 22)
+        LS_ROWS(8, 8);
+    else if (!VEC || n < int64_t(1) << 23)
+        LS_ROWS(16, 8);
+    else
+        LS_ROWS(16, 16);
+#undef LS_ROWS
 }
 
 template <class G, ToppMode MODE>
@@ -896,15 +953,14 @@ static hipError_t rows_typed(bool exclusive, const T* x, T* y, int64_t rows, int
         return hipGetLastError();
     }
     const bool vec = (len % 4 == 0) && aligned16(x) && (TOPP || aligned16(y));
-    if (!TOPP && !long_rows(len) && len > kRowsTileMin) {
-        using TV = RowTile<T, RGeomS, true>;
-        using TU = RowTile<T, RGeomS, false>;
-        static_assert(TV::kElems == kRowTile && TU::kElems == kRowTile, "one tile per row");
-        auto k = exclusive ? (vec ? k_rows_tile<TV, true, true> : k_rows_tile<TU, true, false>)
-                           : (vec ? k_rows_tile<TV, false, true> : k_rows_tile<TU, false, false>);
-        hipLaunchKernelGGL(k, dim3((unsigned)rows), dim3(vec ? TV::kThreads : TU::kThreads), 0,
-                           stream, x, y, len);
-        return hipGetLastError();
+    if constexpr (!TOPP) {
+        if (len > kRowsTileMin) {
+            if (vec)
+                rows_any<T, true>(exclusive, x, y, rows, len, ws, ws_bytes, stream);
+            else
+                rows_any<T, false>(exclusive, x, y, rows, len, ws, ws_bytes, stream);
+            return hipGetLastError();
+        }
     }
     if (!long_rows(len)) {
         const dim3 grid(wave_grid(rows)), block(256);
@@ -913,15 +969,9 @@ static hipError_t rows_typed(bool exclusive, const T* x, T* y, int64_t rows, int
         hipLaunchKernelGGL(k, grid, block, 0, stream, x, y, rows, len, p, cutoff);
         return hipGetLastError();
     }
-    const int64_t t = row_tile(len);
-    if constexpr (TOPP) {
+    if constexpr (TOPP)
         topp_any<ToppMode::Cutoff>(vec, x, nullptr, nullptr, cutoff, nullptr, rows, len, p, ws,
                                    stream);
-    } else {
-        if (t == 32768) rows_long<T, RGeomL>(exclusive, vec, x, y, rows, len, ws, ws_bytes, stream);
-        else if (t == 8192) rows_long<T, RGeomM>(exclusive, vec, x, y, rows, len, ws, ws_bytes, stream);
-        else rows_long<T, RGeomS>(exclusive, vec, x, y, rows, len, ws, ws_bytes, stream);
-    }
     return hipGetLastError();
 }
 

@@ -53,6 +53,30 @@ def test_rows_f32(ops, shape, excl):
                             f"rows f32 exact {shape}")
 
 
+# Each side of every line of the row scan's choice of tile: whole rows of 8192,
+# 16384, 32768 and 65536 (and one more than that), batches on both sides of the
+# sizes from which rows are no longer cut up, rows cut into each tile size;
+# aligned, and with rows that start off 16-byte boundaries.
+ROUTE_SHAPES = [(3, 8192), (3, 8193), (1, 12_000), (40, 16_384), (66, 16_385), (1, 20_004),
+                (2, 32_768), (33, 32_767), (40, 32_769), (3, 65_536), (9, 32_772), (17, 65_536),
+                (17, 65_533), (17, 65_540), (7, 131_072), (33, 131_068), (65, 131_076),
+                (70, 65_539), (2, (1 << 20) + 4), (9, (1 << 20) + 1)]
+
+
+@pytest.mark.parametrize("shape", ROUTE_SHAPES, ids=lambda s: f"{s[0]}x{s[1]}")
+@pytest.mark.parametrize("excl", [False, True])
+def test_rows_tile_choice(ops, shape, excl):
+    rows, length = shape
+    announce("rows tile choice", shape, excl)
+    x = W.scan_i32_full_range(rows * length, seed=length).reshape(rows, length)
+    y = to_host(ops.scan_rows_i32(to_dev(x), exclusive=excl))
+    assert_equal_first_diff(y, oracle.scan_rows_i32(x, exclusive=excl), f"rows i32 {shape}")
+    xe = W.exact_pm1(rows * length, seed=8).reshape(rows, length)
+    ye = to_host(ops.scan_rows_f32(to_dev(xe), exclusive=excl))
+    assert_equal_first_diff(ye.astype(np.float64), oracle.scan_rows_f32(xe, exclusive=excl)[0],
+                            f"rows f32 exact {shape}")
+
+
 def test_rows_inplace_and_empty(ops):
     import torch
     announce("rows in-place/empty")
