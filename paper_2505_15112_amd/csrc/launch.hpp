@@ -64,6 +64,11 @@ hipError_t launch_topk(const float* x, float* values, int32_t* indices, int64_t 
 hipError_t launch_topp_sample(const float* probs, const float* theta, float p, int32_t* token,
                               int32_t* cutoff, int64_t rows, int64_t len, void* scratch, void* ws,
                               hipStream_t stream);
+// The partial sort of the top-p sampler (nucleus.hip).
+struct NucSource;
+hipError_t launch_nucleus_sort(const float* probs, float p, uint32_t heads, int64_t rows,
+                               int64_t len, void* scratch, size_t scratch_bytes, NucSource* src,
+                               hipStream_t stream);
 hipError_t launch_weighted_sample(const float* w, const float* theta, int32_t* out, int64_t rows,
                                   int64_t len, void* ws, hipStream_t stream);
 hipError_t launch_topp_draw_sorted(const float* sorted, const int32_t* idx, const float* theta,

@@ -1,0 +1,990 @@
+// nucleus.hip -- sorting as much of every row as the top-p sampler reads
+// (Section 5 "Top-p or Nucleus Sampling").
+//
+// The cutoff and the draw look at a row's largest probabilities only, down to
+// where their running sum reaches p, and at values only: the one source index
+// they need is found afterwards.  So instead of sorting whole rows with their
+// indices (four radix passes, 16 bytes per element and pass), the elements
+// that can matter are gathered bin by bin and sorted in LDS:
+//  * k_nuc_hist, per tile of a row: a sample of the row gives a monotone map
+//    from keys to at most 4096 bins, fine where the row's keys are dense; the
+//    tile's elements are counted per bin;
+//  * k_nuc_pick, one workgroup per row: the bins in descending order, the
+//    first at which a lower bound of the running sum (each element counted as
+//    its bin's least key) passes p, hence how many elements the draw reads, and
+//    where each tile's share of them goes;
+//  * k_nuc_gather: those elements, keys and source indices, to the row's list;
+//  * k_nuc_sort, one workgroup per group (some thousand elements: the bins that
+//    start in one window of the sorted row): picks its keys out of the list and
+//    sorts them in LDS, in descending order.
+// Workgroups are numbered tile by tile (or group by group) of all rows, so that
+// with a multiple of 8 rows everything of one row runs on one XCD and finds the
+// row's list in its L2.  Rows of up to kNucGroupMax elements are one group, sorted whole by
+// k_nuc_sort_row alone.  The draw (rows.hip) then runs on the sorted keys with
+// the same additions as on a whole sorted row, so its results are the same.
+//
+// Bound: two reads of the rows from HBM (22 us for 128 x 131072) and the LDS
+// work of the sort.  Kernel times at 128 x 131072, p = 0.9 (about 38000
+// elements of each row gathered): histogram 19 us, pick 8, gather 22 (105 MB
+// moved), sort 33, and the draw 5 + 13; the call 272 us by the row sort, 101 us
+// this way.  4 x 200003: 93 -> 50 us, each of the six kernels a few us of
+// latency.  Measured on the way: the elements scattered to their bins by LDS
+// counters instead of gathered (one 8-byte store per lane and line): 62 us for
+// the scatter; a workgroup for every group a row could have, most of them
+// without work: 9 ns each, 26 us.
+#include <limits.h>
+
+#include <type_traits>
+
+#include "launch.hpp"
+#include "nucleus.hpp"
+
+namespace ls {
+
+constexpr int kNucThreads = 1024;
+constexpr int kNucWaves = kNucThreads / kWave;
+constexpr int kNucSample = 2048;  // elements of a row that shape its map
+constexpr int kNucPer = 12;              // keys per thread in a group's sort
+constexpr uint32_t kNucGroupMax = kNucPer * kNucThreads;  // 12288
+constexpr uint32_t kNucSlots = 14336;    // two sorts' LDS fits a CU
+static_assert(kNucSlots % (2 * kNucThreads) == 0, "whole words per thread");
+constexpr int64_t kNucMaxLen = int64_t(1) << 20;
+constexpr uint32_t kNucMinGroup = 4096;
+constexpr uint32_t kNucMaxGroups = (uint32_t)(kNucMaxLen / kNucMinGroup);
+constexpr uint32_t kNucMaxSegs = 40;  // 2^20 + 3 positions of 32768, 2^18 + 3 of 8192: 33
+// The last two bins are in no map (see k_nuc_hist): the elements above the
+// sampled range, and the flag of a row that holds a NaN.
+constexpr int kNucAbove = kNucBins - 2, kNucNan = kNucBins - 1;
+
+// A value that is the same in every lane, in a scalar register.
+__device__ __forceinline__ uint32_t uni(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+
+// Minimum over the wave with DPP (lanes outside the row / disabled read the
+// largest value), in a scalar register.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp_umin(uint32_t v) {
+    const uint32_t o =
+        (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, CTRL, ROW_MASK, 0xf, false);
+    return o < v ? o : v;
+}
+__device__ __forceinline__ uint32_t wave_reduce_min(uint32_t v) {
+    v = dpp_umin<0x111, 0xf>(v);
+    v = dpp_umin<0x112, 0xf>(v);
+    v = dpp_umin<0x114, 0xf>(v);
+    v = dpp_umin<0x118, 0xf>(v);
+    v = dpp_umin<0x142, 0xa>(v);
+    v = dpp_umin<0x143, 0xc>(v);
+    return lane_read(v, kWave - 1);
+}
+
+// Exclusive scan over the workgroup; s_w: one word per wave.  One barrier
+// inside; s_w may be rewritten after the next one.
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* s_w, uint32_t* total) {
+    const int w = threadIdx.x / kWave;
+    const uint32_t inc = wave_incl_scan(v);
+    if (lane_id() == kWave - 1) s_w[w] = inc;
+    __syncthreads();
+    const uint32_t t = lane_id() < kNucWaves ? s_w[lane_id()] : 0u;
+    const uint32_t sc = wave_incl_scan(t);
+    const int wu = __builtin_amdgcn_readfirstlane(w);
+    *total = lane_read(sc, kNucWaves - 1);
+    return (wu > 0 ? lane_read(sc, wu - 1) : 0u) + inc - v;
+}
+
+// ---------------------------------------------------------------- the row's elements
+
+// A workgroup's 4096 J positions of a row in groups of four, thread t's
+// group j at position (j kNucThreads + t) 4 - shift of the tile: `shift` (0 to
+// 3) places the groups on 16-byte boundaries whatever the row's alignment, and
+// a group that crosses either end of the row is loaded element by element
+// (in[j], bit e: element e lies in the row).
+template <int J>
+struct NucTile {
+    uint32_t v[J][4];
+    int32_t pos0;   // row position of v[0][0]
+    uint32_t in;    // bit 4 j + e, when not `full`
+    bool full;      // uniform: every position lies in the row
+    __device__ __forceinline__ uint32_t pos(int j, int e) const {
+        return (uint32_t)(pos0 + j * (kNucThreads * 4) + e);
+    }
+    __device__ __forceinline__ void load(const uint32_t* xr, int32_t len, uint32_t seg) {
+        static_assert(J * 4 <= 32, "one bit per element");
+        const int32_t shift = (int32_t)((uintptr_t)xr / 4 % 4);
+        const int32_t base = (int32_t)(seg * (4096u * J)) - shift;
+        pos0 = base + (int32_t)threadIdx.x * 4;
+        full = base >= 0 && base + 4096 * J <= len;
+        in = ~0u;
+        if (full) {
+            const uint32_t* p = xr + base;
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+                load_vec<uint32_t, uint32_t, 4, true>(p + (j * kNucThreads + threadIdx.x) * 4, v[j]);
+        } else {
+            in = 0u;
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int32_t q = pos0 + j * (kNucThreads * 4);
+                if (q >= 0 && q + 4 <= len) {
+                    load_vec<uint32_t, uint32_t, 4, true>(xr + q, v[j]);
+                    in |= 15u << (4 * j);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const bool ok = q + e >= 0 && q + e < len;
+                        v[j][e] = ok ? xr[q + e] : 0u;
+                        in |= (ok ? 1u : 0u) << (4 * j + e);
+                    }
+                }
+            }
+        }
+    }
+    // f(bits, position, in the row) for every position, in uniform control flow
+    template <class F>
+    __device__ __forceinline__ void each(F f) const {
+        uint32_t q0 = (uint32_t)pos0;
+        asm volatile("" : "+v"(q0));  // no per-group positions kept live from the loads
+        if (full) {
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    f(v[j][e], q0 + (uint32_t)(j * kNucThreads * 4 + e), true);
+        } else {
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    f(v[j][e], q0 + (uint32_t)(j * kNucThreads * 4 + e),
+                      ((in >> (4 * j + e)) & 1u) != 0);
+        }
+    }
+};
+
+// ---------------------------------------------------------------- histogram
+
+// Tile counts per bin (16-bit: a tile has at most 32768 elements), and, from
+// the row's first tile, the row's map.  Every tile of a row derives the same
+// map from the same sample: 512 groups of 4 consecutive elements spread over
+// the row.  The sampled range is cut into at most 2048 cells; a cell with s
+// samples is cut into the least power of two >= s / 2 bins: at most s - 1 of
+// them for s > 2, so at most 4094 in all.  Where no cell has more samples than
+// stand for `fine` elements the cells are the bins, and the map is not looked up
+// (one LDS read less per element).
+//
+// Elements above the sampled range are counted in bin kNucAbove, and their sum
+// kept (above[tile]): the largest probabilities, few and mostly not in the
+// sample, carry much of the mass.  Bin kNucNan is 1 if the tile has a NaN with
+// its sign bit clear: it sorts before everything, and no running sum of its row
+// reaches p.
+template <int J>
+__global__ __launch_bounds__(kNucThreads) LS_OCCUPANCY8 void k_nuc_hist(
+    const uint32_t* x, int32_t len, uint32_t nrows, uint32_t segs, uint16_t* hist, NucRow* rows,
+    uint32_t* maps, double* above, uint32_t fine) {
+    __shared__ uint32_t s_map[kNucCells];
+    __shared__ uint32_t s_h[kNucBins];
+    __shared__ uint32_t s_w[kNucWaves], s_w2[kNucWaves];
+    __shared__ uint32_t s_dense;
+    __shared__ double s_above;
+    const uint32_t seg = blockIdx.x / nrows, row = blockIdx.x - seg * nrows;
+    const uint32_t tile_id = row * segs + seg;
+    const uint32_t* xr = x + (int64_t)row * len;
+    const uint32_t t = threadIdx.x;
+    // the sample (len > kNucGroupMax > kNucSample), loaded before the tile: it
+    // is waited for first
+    uint32_t smp[4];
+    uint32_t mn = 0xFFFFFFFFu, mx = 0u;
+    if (t < kNucSample / 4) {
+        const uint32_t q = (uint32_t)((uint64_t)t * (uint32_t)(len - 4) / (kNucSample / 4 - 1));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) smp[e] = xr[q + e];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    NucTile<J> tile;
+    tile.load(xr, len, seg);
+    __builtin_amdgcn_sched_barrier(0);
+    if (t < kNucSample / 4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) smp[e] = nuc_key(smp[e]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            mn = smp[e] < mn ? smp[e] : mn;
+            mx = smp[e] > mx ? smp[e] : mx;
+        }
+    }
+    mn = wave_reduce_min(mn);
+    mx = ~wave_reduce_min(~mx);
+    if (lane_id() == 0) {
+        s_w[t / kWave] = mn;
+        s_w2[t / kWave] = mx;
+    }
+    for (int i = t; i < kNucCells; i += kNucThreads) s_map[i] = 0;
+    for (int i = t; i < kNucBins; i += kNucThreads) s_h[i] = 0;
+    if (t == 0) {
+        s_dense = 0;
+        s_above = 0.0;
+    }
+    __syncthreads();
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll
+    for (int q = 0; q < kNucSample / 4 / kWave; ++q) {
+        lo = s_w[q] < lo ? s_w[q] : lo;
+        hi = s_w2[q] > hi ? s_w2[q] : hi;
+    }
+    lo = uni(lo);
+    hi = uni(hi);
+    const uint32_t range = hi - lo;
+    const int bits = range ? 32 - __builtin_clz(range) : 0;
+    const uint32_t shift = bits > 11 ? (uint32_t)(bits - 11) : 0u;  // range >> shift < 2048
+    if (t < kNucSample / 4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) atomicAdd(&s_map[(smp[e] - lo) >> shift], 1u);
+    }
+    __syncthreads();
+    // cells 2 t and 2 t + 1: their bins
+    uint32_t sub[2], n[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint32_t s = s_map[2 * t + i];
+        if ((uint64_t)s * (uint32_t)len > (uint64_t)kNucSample * fine) s_dense = 1;
+        const uint32_t b = s > 2 ? 32u - (uint32_t)__builtin_clz((s + 1) / 2 - 1) : 0u;
+        sub[i] = b < shift ? b : shift;
+    }
+    __syncthreads();
+    const bool direct = s_dense == 0;  // uniform over the row's tiles
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        sub[i] = direct ? 0u : sub[i];
+        n[i] = 1u << sub[i];
+    }
+    uint32_t total;
+    const uint32_t first = block_excl_scan(n[0] + n[1], s_w, &total);
+    s_map[2 * t] = first | sub[0] << 16;
+    s_map[2 * t + 1] = (first + n[0]) | sub[1] << 16;
+    __syncthreads();
+    int32_t top = 0;
+    auto count = [&](auto bin_of) {
+        tile.each([&](uint32_t b, uint32_t, bool ok) {
+            if (!ok) return;
+            top = top > (int32_t)b ? top : (int32_t)b;
+            const uint32_t k = nuc_key(b);
+            const bool over = k > hi;
+            if (over) atomicAdd(&s_above, (double)Bits<float>::from(b));
+            const uint32_t bin = bin_of(k > lo ? k - lo : 0u);
+            atomicAdd(&s_h[over ? kNucAbove : bin], 1u);
+        });
+    };
+    // keys above hi index no cell: the bin they would get is not used
+    if (direct)
+        count([&](uint32_t d) { return d >> shift; });
+    else
+        count([&](uint32_t d) {
+            const uint32_t c = d >> shift;
+            const uint32_t e = s_map[c < kNucCells ? c : kNucCells - 1];
+            return (e & 0xFFFFu) + ((d & ((1u << shift) - 1u)) >> (shift - (e >> 16)));
+        });
+    if (top > 0x7F800000) s_h[kNucNan] = 1;  // every such thread stores the same
+    if (seg == 0) {
+        uint32_t* m = maps + (int64_t)row * kNucCells;
+        m[2 * t] = s_map[2 * t];
+        m[2 * t + 1] = s_map[2 * t + 1];
+        if (t == 0) {
+            rows[row].lo = lo;
+            rows[row].hi = hi;
+            rows[row].shift = shift;
+            rows[row].direct = direct;
+        }
+    }
+    __syncthreads();
+    // bins 4 t .. 4 t + 3 (as 8 bytes)
+    ushort4 c;
+    c.x = (uint16_t)s_h[4 * t];
+    c.y = (uint16_t)s_h[4 * t + 1];
+    c.z = (uint16_t)s_h[4 * t + 2];
+    c.w = (uint16_t)s_h[4 * t + 3];
+    reinterpret_cast<ushort4*>(hist + (int64_t)tile_id * kNucBins)[t] = c;
+    if (t == 0) above[tile_id] = s_above;
+}
+
+// ---------------------------------------------------------------- how far to sort
+
+// Positions of the sorted row that the draw reads when its crossing lies in
+// the first n: whole tiles of 4096 among the row's `heads` first ones, whole
+// steps of 8192 after them.
+__device__ __forceinline__ uint32_t nuc_reads(uint32_t n, uint32_t heads, uint32_t len) {
+    const uint32_t h = heads * 4096u;
+    const uint32_t m = n <= h ? (n + 4095u) / 4096u * 4096u : h + (n - h + 8191u) / 8192u * 8192u;
+    return m < len ? m : len;
+}
+
+// One workgroup per row.  Thread t takes the four bins at descending places
+// 4 t .. 4 t + 3 (bin kNucBins - 1 - place).
+__global__ __launch_bounds__(kNucThreads) void k_nuc_pick(const uint16_t* hist, uint32_t segs,
+                                                          const uint32_t* maps, float p,
+                                                          int32_t len, uint32_t heads,
+                                                          NucRow* rows, const double* above,
+                                                          uint32_t window, uint32_t ngroups,
+                                                          uint2* groups) {
+    __shared__ uint32_t s_cell[kNucBins], s_map[kNucCells];
+    __shared__ uint32_t s_w[kNucWaves];
+    __shared__ double s_d[kNucWaves];
+    __shared__ uint32_t s_need, s_sorted, s_key, s_nan;
+    __shared__ uint32_t s_g[kNucMaxGroups + 1], s_low[kNucMaxGroups];
+    const int64_t row = blockIdx.x;
+    const uint32_t t = threadIdx.x;
+    const int w = t / kWave;
+    const uint16_t* rh = hist + row * segs * kNucBins;
+    // counts: the bins at places 4 t .. 4 t + 3 are bins b0 + 3 .. b0
+    const uint32_t b0 = kNucBins - 4 - 4 * t;
+    uint32_t cnt[4] = {0u, 0u, 0u, 0u};
+#pragma unroll 16
+    for (uint32_t s = 0; s < segs; ++s) {
+        const ushort4 c = *reinterpret_cast<const ushort4*>(rh + (int64_t)s * kNucBins + b0);
+        cnt[0] += c.w;
+        cnt[1] += c.z;
+        cnt[2] += c.y;
+        cnt[3] += c.x;
+    }
+    double over = 0.0;  // thread 0: the sum of the elements above the range
+    if (t < kWave) {
+        static_assert(kNucMaxSegs <= kWave, "one lane per tile");
+        over = t < segs ? above[row * segs + t] : 0.0;
+        for (int d = kWave / 2; d >= 1; d /= 2) over += __shfl_xor(over, d);
+    }
+    if (t == 0) {
+        s_nan = cnt[0];  // bin kNucNan: a flag, not a count
+        cnt[0] = 0;
+    }
+    const NucRow r = rows[row];
+    if (t == 0) {
+        s_need = (uint32_t)len;
+        s_sorted = (uint32_t)len;
+        s_key = 0u;
+    }
+    for (uint32_t i = t; i <= ngroups; i += kNucThreads) {
+        s_g[i] = UINT_MAX;
+        if (i < ngroups) s_low[i] = UINT_MAX;
+    }
+    // every bin's least key
+    uint32_t low[4];
+    if (r.direct) {  // uniform: bin b is cell b
+#pragma unroll
+        for (int i = 0; i < 4; ++i) low[i] = r.lo + ((b0 + 3 - i) << r.shift);
+    } else {
+        // the cell a bin belongs to is the last one whose first bin is not
+        // after it: a running maximum over the bins of the cells' marks
+        const uint2 e2 = reinterpret_cast<const uint2*>(maps + row * kNucCells)[t];
+        for (int i = t; i < kNucBins; i += kNucThreads) s_cell[i] = 0;
+        s_map[2 * t] = e2.x;
+        s_map[2 * t + 1] = e2.y;
+        __syncthreads();
+        s_cell[e2.x & 0xFFFFu] = 2 * t;  // distinct bins
+        s_cell[e2.y & 0xFFFFu] = 2 * t + 1;
+        __syncthreads();
+        uint32_t run = 0, cell[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {  // bins 4 t + i
+            const uint32_t c = s_cell[4 * t + i];
+            run = c > run ? c : run;
+            cell[i] = run;
+        }
+        // wave maximum scan (maxima of ~v by the minimum's moves)
+        uint32_t inc = ~run;
+        inc = dpp_umin<0x111, 0xf>(inc);
+        inc = dpp_umin<0x112, 0xf>(inc);
+        inc = dpp_umin<0x114, 0xf>(inc);
+        inc = dpp_umin<0x118, 0xf>(inc);
+        inc = dpp_umin<0x142, 0xa>(inc);
+        inc = dpp_umin<0x143, 0xc>(inc);
+        inc = ~inc;
+        if (lane_id() == kWave - 1) s_w[w] = inc;
+        uint32_t before = wave_shr1(inc);
+        __syncthreads();
+        for (int q = 0; q < w; ++q) before = s_w[q] > before ? s_w[q] : before;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s_cell[4 * t + i] = cell[i] > before ? cell[i] : before;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t b = b0 + 3 - i, c = s_cell[b];
+            const uint32_t e = s_map[c];
+            low[i] = r.lo + (c << r.shift) + ((b - (e & 0xFFFFu)) << (r.shift - (e >> 16)));
+        }
+    }
+    double mass = 0.0, m[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t b = b0 + 3 - i;
+        if (b == 0) low[i] = 0u;  // the first bin takes every key below lo
+        if (b == kNucAbove) low[i] = r.hi + 1u;  // not empty: hi is not the last key
+        // the least value; a bin that reaches below the finite ones bounds nothing
+        const float v = Bits<float>::from(nuc_bits(low[i]));
+        m[i] = cnt[i] ? (v >= -3.4028235e38f ? (double)cnt[i] * (double)v : -__builtin_inf()) : 0.0;
+        if (b == kNucAbove) m[i] = over;
+        mass += m[i];
+    }
+    __syncthreads();  // s_w free
+    uint32_t total;
+    const uint32_t own = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+    uint32_t start[4];
+    start[0] = block_excl_scan(own, s_w, &total);
+#pragma unroll
+    for (int i = 1; i < 4; ++i) start[i] = start[i - 1] + cnt[i - 1];
+    // running lower bound before this thread's bins
+    auto add = [](double a, uint64_t o) { return a + __builtin_bit_cast(double, o); };
+    auto moved = [](double v, auto c, auto m) {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        return ((uint64_t)dpp0<c(), m()>((uint32_t)(u >> 32)) << 32) | dpp0<c(), m()>((uint32_t)u);
+    };
+    double inc = mass;
+#define LS_STEP(C, M) \
+    inc = add(inc, moved(inc, std::integral_constant<int, C>{}, std::integral_constant<int, M>{}))
+    LS_STEP(0x111, 0xf);
+    LS_STEP(0x112, 0xf);
+    LS_STEP(0x114, 0xf);
+    LS_STEP(0x118, 0xf);
+    LS_STEP(0x142, 0xa);
+    LS_STEP(0x143, 0xc);
+#undef LS_STEP
+    if (lane_id() == kWave - 1) s_d[w] = inc;
+    double before = __builtin_bit_cast(
+        double, moved(inc, std::integral_constant<int, 0x138>{}, std::integral_constant<int, 0xf>{}));
+    __syncthreads();
+    for (int q = 0; q < w; ++q) before += s_d[q];
+    // Should rounding in 32 bits (at most 64 additions deep: 4e-6 of the sum,
+    // all terms up to the crossing having one sign) lose a little, the running
+    // sum has still reached p where the bound reaches p (1 + 1e-5).
+    const double goal = (double)p + 1e-5 * (p < 0.f ? -(double)p : (double)p);
+    if (!s_nan) {
+        double s = before;
+        uint32_t n = UINT_MAX;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            s += m[i];
+            if (n == UINT_MAX && cnt[i] && s >= goal) n = start[i] + cnt[i];
+        }
+        if (n != UINT_MAX) atomicMin(&s_need, nuc_reads(n, heads, (uint32_t)len));
+    }
+    __syncthreads();
+    const uint32_t need = s_need;
+    // the bins that start before `need` are sorted; group g takes those that
+    // start in [g window, (g + 1) window)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (cnt[i] && start[i] < need) {
+            const uint32_t g = start[i] / window;
+            atomicMin(&s_g[g], start[i]);
+            atomicMin(&s_low[g], low[i]);
+            if (start[i] + cnt[i] >= need) {  // the last one
+                s_sorted = start[i] + cnt[i];
+                s_key = low[i];
+            }
+        }
+    }
+    __syncthreads();
+    // {first position, least key} of every group, and the end
+    if (t < kWave) {
+        const uint32_t sorted = s_sorted;
+        uint32_t next = sorted;  // first position of the nearest group after these
+        for (int32_t c = (int32_t)(ngroups / kWave * kWave); c >= 0; c -= kWave) {
+            const uint32_t i = (uint32_t)c + t;
+            uint32_t g = i < ngroups ? s_g[i] : UINT_MAX;
+            for (int d = 1; d < kWave; d *= 2) {  // suffix minimum
+                const uint32_t o = __shfl_down(g, d);
+                if (t + d < kWave && o < g) g = o;
+            }
+            g = g < next ? g : next;
+            if (i <= ngroups)
+                groups[row * (ngroups + 1) + i] = make_uint2(g, i < ngroups ? s_low[i] : 0u);
+            next = uni(g);
+        }
+        if (t == 0) {
+            rows[row].key_min = s_key;
+            rows[row].sorted = sorted;
+            rows[row].cursor = 0;
+        }
+    }
+}
+
+// ---------------------------------------------------------------- gather
+
+// The tile's elements with keys from key_min up, keys and source indices, to
+// the row's list, at slots reserved by one atomic per tile (in any order: the
+// list is searched by key).  Per element of a lane the wave's kept ones are a
+// ballot, and go to consecutive slots.
+template <int J>
+__global__ __launch_bounds__(kNucThreads) LS_OCCUPANCY8 void k_nuc_gather(
+    const uint32_t* x, int32_t len, uint32_t nrows, uint32_t segs, NucRow* rows, uint32_t* keys,
+    uint32_t* idx, uint32_t stride) {
+    __shared__ uint32_t s_w[kNucWaves];
+    __shared__ uint32_t s_first;
+    const uint32_t seg = blockIdx.x / nrows, row = blockIdx.x - seg * nrows;
+    NucTile<J> tile;
+    tile.load(x + (int64_t)row * len, len, seg);
+    const uint32_t key_min = rows[row].key_min;
+    uint32_t n = 0;  // the lane's kept elements
+    tile.each([&](uint32_t b, uint32_t, bool ok) { n += ok && nuc_key(b) >= key_min ? 1u : 0u; });
+    uint32_t total;
+    uint32_t at = block_excl_scan(n, s_w, &total);
+    if (total == 0) return;  // uniform
+    if (threadIdx.x == 0)
+        s_first = __hip_atomic_fetch_add(&rows[row].cursor, total, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    // the wave's first slot
+    at = uni(s_first + at);
+    uint32_t* kr = keys + (int64_t)row * stride;
+    uint32_t* ir = idx + (int64_t)row * stride;
+    tile.each([&](uint32_t b, uint32_t pos, bool ok) {
+        const uint32_t key = nuc_key(b);
+        const bool q = ok && key >= key_min;
+        const uint64_t m = __ballot(q);
+        const uint32_t to = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+        if (q && to < (uint32_t)len) {  // always below len; checked all the same
+            kr[to] = key;
+            ir[to] = pos;
+        }
+        at += (uint32_t)__builtin_popcountll(m);
+    });
+}
+
+// ---------------------------------------------------------------- a group's sort
+
+// Sorts n <= kNucGroupMax keys, key[e] being number threadIdx.x + e kNucThreads,
+// in descending order to out[0, n) (as float bits).  The key range [lo, hi] is
+// spread over kNucSlots slots (linearly, and keys are about evenly dense in it:
+// about one key a slot); the keys are counted per slot, moved to their slots'
+// places in LDS, and each finds its rank among the keys of its slot by looking
+// at them all.  A slot of more than kNucFew keys that are all equal needs no look.
+// The thread's number, as a value that nothing is hoisted out of loops for
+// (addresses derived from it would stay live through the whole kernel).
+__device__ __forceinline__ uint32_t nuc_thread() {
+    uint32_t t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+constexpr uint32_t kNucFew = 64;
+struct NucSortLds {
+    uint32_t key[kNucGroupMax];
+    uint32_t slot[kNucSlots / 2];  // two 16-bit counters a word
+    uint32_t w[kNucWaves];
+    uint32_t mixed;
+};
+__device__ void nuc_sort(const uint32_t (&key)[kNucPer], uint32_t n, uint32_t lo, uint32_t hi,
+                         uint32_t* out, NucSortLds& L) {
+    const uint32_t t = nuc_thread();
+    const uint32_t range = hi - lo;
+    const bool direct = range < kNucSlots;
+    const uint32_t mult = uni((uint32_t)((double)kNucSlots * 4294967296.0 / ((double)range + 1.0)));
+    auto slot_of = [&](uint32_t k) {
+        const uint32_t d = hi - k;
+        const uint32_t s = direct ? d : __umulhi(d, mult);
+        return s < kNucSlots ? s : kNucSlots - 1;
+    };
+    __syncthreads();  // L free
+    for (uint32_t i = t; i < kNucSlots / 2; i += kNucThreads) L.slot[i] = 0;
+    if (t == 0) L.mixed = 0;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kNucPer; ++e)
+        if (t + e * kNucThreads < n) {
+            const uint32_t s = slot_of(key[e]);
+            atomicAdd(&L.slot[s / 2], 1u << (16 * (s & 1)));
+        }
+    __syncthreads();
+    // thread t: kWords words of two slots, counts to first places
+    constexpr int kWords = kNucSlots / 2 / kNucThreads;
+    uint32_t c[kWords], sum = 0;
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) {
+        c[i] = L.slot[kWords * t + i];
+        sum += (c[i] & 0xFFFFu) + (c[i] >> 16);
+    }
+    uint32_t total;
+    uint32_t at = block_excl_scan(sum, L.w, &total);
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) {
+        const uint32_t a = c[i] & 0xFFFFu, b = c[i] >> 16;
+        if ((a > b ? a : b) > kNucFew) L.mixed = 1;
+        L.slot[kWords * t + i] = at | (at + a) << 16;
+        at += a + b;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kNucPer; ++e)
+        if (t + e * kNucThreads < n) {
+            const uint32_t s = slot_of(key[e]);
+            const uint32_t old = atomicAdd(&L.slot[s / 2], 1u << (16 * (s & 1)));
+            const uint32_t i = (old >> (16 * (s & 1))) & 0xFFFFu;
+            if (i < kNucGroupMax) L.key[i] = key[e];  // always; checked all the same
+        }
+    __syncthreads();
+    // a slot's counter is now its end, the one before it its first place
+    auto end_of = [&](uint32_t s) { return (L.slot[s / 2] >> (16 * (s & 1))) & 0xFFFFu; };
+    if (L.mixed) {  // uniform: some slot has many keys; are they equal?
+        __syncthreads();
+        for (uint32_t i = t; i < n; i += kNucThreads) {
+            const uint32_t k = L.key[i], s = slot_of(k);
+            const uint32_t first = s ? end_of(s - 1) : 0u;
+            if (end_of(s) - first > kNucFew && L.key[first] != k) L.mixed = 2;
+        }
+        __syncthreads();
+    }
+    const bool mixed = L.mixed == 2;
+#pragma unroll 4
+    for (uint32_t i = t; i < n; i += kNucThreads) {
+        const uint32_t k = L.key[i], s = slot_of(k);
+        const uint32_t first = s ? end_of(s - 1) : 0u, last = end_of(s);
+        uint32_t r = i;
+        if (last - first > 1u && (last - first <= kNucFew || mixed)) {
+            r = first;
+            for (uint32_t j = first; j < last; ++j) {
+                const uint32_t o = L.key[j];
+                r += (o > k || (o == k && j < i)) ? 1u : 0u;
+            }
+        }
+        out[r] = nuc_bits(k);
+    }
+}
+
+// Least and largest of the workgroup's keys.
+__device__ __forceinline__ void nuc_range(const uint32_t (&key)[kNucPer], uint32_t n, uint32_t* lo,
+                                          uint32_t* hi, NucSortLds& L) {
+    uint32_t mn = 0xFFFFFFFFu, mx = 0u;
+    const uint32_t t = nuc_thread();
+#pragma unroll
+    for (int e = 0; e < kNucPer; ++e)
+        if (t + e * kNucThreads < n) {
+            mn = key[e] < mn ? key[e] : mn;
+            mx = key[e] > mx ? key[e] : mx;
+        }
+    mn = wave_reduce_min(mn);
+    mx = ~wave_reduce_min(~mx);
+    __syncthreads();
+    if (lane_id() == 0) {
+        L.key[threadIdx.x / kWave] = mn;
+        L.key[kNucWaves + threadIdx.x / kWave] = mx;
+    }
+    __syncthreads();
+    for (int q = 0; q < kNucWaves; ++q) {
+        mn = L.key[q] < mn ? L.key[q] : mn;
+        mx = L.key[kNucWaves + q] > mx ? L.key[kNucWaves + q] : mx;
+    }
+    *lo = uni(mn);
+    *hi = uni(mx);
+}
+
+// A group too large for LDS (a bin of many elements: most of them equal, or so
+// close together that the sample's map did not part them) is sorted in windows
+// of at most kNucGroupMax keys from the top down.  nuc_window finds the next
+// one among the m keys at lk in [floor, cap]: keys in [*from, *hi]; *fits 0:
+// the key *hi alone, more often than that.  The keys left are
+// counted in at most 4096 equal parts of their range; the parts from the top
+// that fit together are the window, and a first part that does not fit is cut
+// up again.
+__device__ void nuc_window(const uint32_t* lk, uint32_t m, uint32_t floor, uint32_t cap,
+                           uint32_t* from, uint32_t* hi, uint32_t* fits, uint32_t* s_v,
+                           NucSortLds& L) {
+    const uint32_t t = nuc_thread();
+    constexpr uint32_t kParts = 4096;
+    static_assert(kParts <= kNucSlots / 2, "parts fit the slots");
+    uint32_t mn = 0xFFFFFFFFu, mx = 0u;
+    for (uint32_t i = t; i < m; i += kNucThreads) {
+        const uint32_t k = lk[i];
+        if (k >= floor && k <= cap) {
+            mn = k < mn ? k : mn;
+            mx = k > mx ? k : mx;
+        }
+    }
+    __syncthreads();
+    if (t < 2) s_v[t] = t - 1u;  // the largest value, 0
+    __syncthreads();
+    mn = wave_reduce_min(mn);
+    mx = ~wave_reduce_min(~mx);
+    if (lane_id() == 0) {
+        atomicMin(&s_v[0], mn);
+        atomicMax(&s_v[1], mx);
+    }
+    __syncthreads();
+    uint32_t lo = uni(s_v[0]);
+    const uint32_t top = uni(s_v[1]);
+    while (true) {  // the range [lo, top] gets 4096 times smaller each time
+        const uint32_t range = top - lo;
+        const int bits = range ? 32 - __builtin_clz(range) : 0;
+        const uint32_t sh = bits > 12 ? (uint32_t)(bits - 12) : 0u;
+        __syncthreads();
+        for (uint32_t i = t; i < kParts; i += kNucThreads) L.slot[i] = 0;
+        if (t < 2) s_v[2 + t] = 0;
+        __syncthreads();
+        for (uint32_t i = t; i < m; i += kNucThreads) {
+            const uint32_t k = lk[i];
+            if (k >= lo && k <= top) atomicAdd(&L.slot[(top - k) >> sh], 1u);
+        }
+        __syncthreads();
+        uint32_t total;
+        uint32_t inc = block_excl_scan(L.slot[4 * t] + L.slot[4 * t + 1] + L.slot[4 * t + 2] +
+                                           L.slot[4 * t + 3], L.w, &total);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            inc += L.slot[4 * t + i];
+            if (inc <= kNucGroupMax) {
+                atomicMax(&s_v[2], inc);
+                atomicMax(&s_v[3], 4 * t + i + 1);  // parts that fit
+            }
+        }
+        __syncthreads();
+        *fits = uni(s_v[2]);
+        *hi = top;
+        if (*fits > 0) {
+            const uint64_t span = (uint64_t)uni(s_v[3]) << sh;
+            *from = span > range ? lo : top + 1u - (uint32_t)span;
+            return;
+        }
+        if (sh == 0) {  // the largest key alone does not fit
+            *from = top;
+            return;
+        }
+        const uint32_t part = 1u << sh;  // the largest key's part
+        lo = range >= part ? top - part + 1u : lo;
+    }
+}
+
+// The keys of group g: those in [lo, hi].
+__device__ __forceinline__ void group_keys(const uint2* gr, uint32_t g, uint32_t* lo, uint32_t* hi) {
+    *lo = uni(gr[g].y);
+    *hi = UINT_MAX;
+    for (uint32_t j = g; j > 0;) {  // below the nearest group before it that is not empty
+        const uint32_t b = uni(gr[--j].y);
+        if (b != UINT_MAX) {
+            *hi = b - 1u;
+            break;
+        }
+    }
+}
+
+// The list's keys in [lo, hi] (at most kNucGroupMax; of more only the number
+// is right) to L.key, in any order; returns their number.  16-byte loads; per
+// element of a lane the wave's kept ones go to consecutive LDS slots.
+__device__ __forceinline__ uint32_t nuc_select(const uint32_t* keys, uint32_t m, uint32_t lo,
+                                               uint32_t hi, uint32_t* s_n, NucSortLds& L) {
+    const uint32_t t = nuc_thread();
+    const u32x4* k4 = reinterpret_cast<const u32x4*>(keys);
+    __syncthreads();
+    if (t == 0) *s_n = 0;
+    __syncthreads();
+    const uint32_t range = hi - lo;
+    constexpr int kLoads = 2, kEach = kLoads * 4;
+    for (uint32_t b = 0; b < m; b += kEach * kNucThreads) {
+        u32x4 v[kLoads];
+#pragma unroll
+        for (int q = 0; q < kLoads; ++q) {
+            const uint32_t i = b + (q * kNucThreads + t) * 4;
+            // the list's row is a multiple of 4 long: what lies past m is masked
+            v[q] = i < m ? k4[i / 4] : u32x4{0u, 0u, 0u, 0u};
+        }
+        uint64_t mk[kEach];  // the wave's kept lanes, per element
+        uint32_t cnt = 0;
+        if (b + kEach * kNucThreads <= m) {  // uniform
+#pragma unroll
+            for (int q = 0; q < kEach; ++q) mk[q] = __ballot(v[q / 4][q % 4] - lo <= range);
+        } else {
+#pragma unroll
+            for (int q = 0; q < kEach; ++q)
+                mk[q] = __ballot(b + (q / 4 * kNucThreads + t) * 4 + q % 4 < m &&
+                                 v[q / 4][q % 4] - lo <= range);
+        }
+#pragma unroll
+        for (int q = 0; q < kEach; ++q) cnt += (uint32_t)__builtin_popcountll(mk[q]);
+        if (cnt == 0) continue;  // uniform in the wave
+        uint32_t at = 0;
+        if (lane_id() == 0) at = atomicAdd(s_n, cnt);
+        at = uni(at);
+        if (at + cnt > kNucGroupMax) continue;  // only their number is wanted
+#pragma unroll
+        for (int q = 0; q < kEach; ++q) {
+            const uint32_t to =
+                at + __builtin_amdgcn_mbcnt_hi((uint32_t)(mk[q] >> 32),
+                                               __builtin_amdgcn_mbcnt_lo((uint32_t)mk[q], 0));
+            if ((mk[q] >> lane_id()) & 1u) L.key[to] = v[q / 4][q % 4];
+            at += (uint32_t)__builtin_popcountll(mk[q]);
+        }
+    }
+    __syncthreads();
+    return uni(*s_n);
+}
+
+// Workgroup blockIdx.x / rows of row blockIdx.x % rows takes every parts-th
+// group of the row: its keys out of the row's list, then the sort; a group too
+// large for LDS window by window.  Workgroups without a group cost 9 ns each
+// to start, so there are about as many as the draw reads head tiles.
+__global__ __launch_bounds__(kNucThreads) LS_OCCUPANCY8 void k_nuc_sort(
+    const uint32_t* keys, uint32_t stride, int32_t len, uint32_t rows, uint32_t parts,
+    const NucRow* info, const uint2* groups, uint32_t ngroups, float* sorted) {
+    __shared__ NucSortLds L;
+    __shared__ uint32_t s_v[4];
+    const uint32_t part = blockIdx.x / rows, row = blockIdx.x - part * rows;
+    const uint2* gr = groups + (int64_t)row * (ngroups + 1);
+    const uint32_t m = uni(info[row].sorted);
+    const uint32_t* lk = keys + (int64_t)row * stride;
+    for (uint32_t g = part; g < ngroups; g += parts) {
+        uint32_t a = uni(gr[g].x);
+        const uint32_t end = uni(gr[g + 1].x);
+        if (a == end) continue;  // uniform
+        const bool big = end - a > kNucGroupMax;
+        uint32_t floor, cap;
+        group_keys(gr, g, &floor, &cap);
+        while (a < end) {  // once, unless big; every step writes a key
+            uint32_t from = floor, hi = cap, fits = 1;
+            if (big) nuc_window(lk, m, floor, cap, &from, &hi, &fits, s_v, L);
+            const uint32_t n = nuc_select(lk, m, from, hi, s_v, L);
+            uint32_t* out = reinterpret_cast<uint32_t*>(sorted) + (int64_t)row * len + a;
+            cap = from - 1u;
+            a += n;
+            if (fits == 0) {  // one key, more often than fits
+                for (uint32_t i = nuc_thread(); i < n && a <= end; i += kNucThreads)
+                    out[i] = nuc_bits(hi);
+                continue;
+            }
+            uint32_t key[kNucPer];
+            const uint32_t t0 = nuc_thread();
+#pragma unroll
+            for (int e = 0; e < kNucPer; ++e) {
+                const uint32_t i = t0 + e * kNucThreads;
+                key[e] = i < n ? L.key[i] : 0u;
+            }
+            if (n <= kNucGroupMax && a <= end) {  // always; checked all the same
+                nuc_range(key, n, &from, &hi, L);
+                nuc_sort(key, n, from, hi, out, L);
+            }
+            if (n == 0) return;  // cannot happen; the loop ends whatever the list holds
+        }
+    }
+}
+
+// Rows of up to kNucGroupMax elements, whole.
+__global__ __launch_bounds__(kNucThreads) void k_nuc_sort_row(const uint32_t* x, int32_t len,
+                                                              float* sorted) {
+    __shared__ NucSortLds L;
+    const int64_t row = blockIdx.x;
+    const uint32_t* xr = x + row * len;
+    uint32_t key[kNucPer];
+#pragma unroll
+    for (int e = 0; e < kNucPer; ++e) {
+        const uint32_t i = threadIdx.x + e * kNucThreads;
+        key[e] = i < (uint32_t)len ? nuc_key(xr[i]) : 0u;
+    }
+    uint32_t lo, hi;
+    nuc_range(key, (uint32_t)len, &lo, &hi, L);
+    nuc_sort(key, (uint32_t)len, lo, hi, reinterpret_cast<uint32_t*>(sorted) + row * len, L);
+}
+
+// ---------------------------------------------------------------- launch
+
+static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
+
+// Tiles of 32768 positions when they occupy the chip, of 8192 otherwise (rows
+// of up to 40960 take the large ones always: a tile's counts have to fit the 4
+// bytes per element of scratch beside the list and the result).
+static uint32_t nucleus_tile(int64_t rows, int64_t len) {
+    return rows * len >= int64_t(256) * 32768 || len > (1 << 18) || len <= 40960 ? 32768u : 8192u;
+}
+// Elements per group: large groups read the list fewer times (four a row at
+// p = 0.9 over softmax rows, so that the two workgroups of every CU sort the
+// 512 of 128 rows in one round), small ones occupy the chip when there are few
+// rows.  The rest up to kNucGroupMax is room for the group's last bin.
+static uint32_t nucleus_window(int64_t rows, int64_t len) {
+    return rows * len >= int64_t(256) * 32768 ? 11264u : kNucMinGroup;
+}
+
+struct NucLayout {
+    uint32_t segs, window, ngroups, stride;
+    size_t keys, idx, hist, above, maps, rows, groups, end;  // after the sorted keys
+};
+static NucLayout nucleus_layout(int64_t rows, int64_t len) {
+    NucLayout l{};
+    const size_t n = (size_t)rows * (size_t)len;
+    l.keys = align256(n * 4);
+    if (len <= (int64_t)kNucGroupMax) {
+        l.end = l.keys;
+        return l;
+    }
+    const uint32_t tile = nucleus_tile(rows, len);
+    // rows that start off 16-byte boundaries: up to 3 positions before them
+    l.segs = (uint32_t)((len + 3 + tile - 1) / tile);
+    l.window = nucleus_window(rows, len);
+    l.ngroups = (uint32_t)((len + l.window - 1) / l.window);
+    l.stride = (uint32_t)((len + 3) / 4 * 4);
+    const size_t tiles = (size_t)rows * l.segs;
+    l.idx = l.keys + align256((size_t)rows * l.stride * 4);
+    l.hist = l.idx + align256((size_t)rows * l.stride * 4);
+    l.above = l.hist + tiles * kNucBins * sizeof(uint16_t);
+    l.maps = l.above + align256(tiles * sizeof(double));
+    l.rows = l.maps + (size_t)rows * kNucCells * sizeof(uint32_t);
+    l.groups = l.rows + (size_t)rows * sizeof(NucRow);
+    l.end = l.groups + (size_t)rows * (l.ngroups + 1) * sizeof(uint2);
+    return l;
+}
+
+template <int J>
+static void nucleus_bins(const uint32_t* x, int64_t rows, int64_t len, float p, uint32_t heads,
+                         const NucLayout& l, char* s, hipStream_t stream) {
+    uint16_t* hist = reinterpret_cast<uint16_t*>(s + l.hist);
+    double* above = reinterpret_cast<double*>(s + l.above);
+    uint32_t* maps = reinterpret_cast<uint32_t*>(s + l.maps);
+    NucRow* info = reinterpret_cast<NucRow*>(s + l.rows);
+    uint2* groups = reinterpret_cast<uint2*>(s + l.groups);
+    uint32_t* keys = reinterpret_cast<uint32_t*>(s + l.keys);
+    uint32_t* idx = reinterpret_cast<uint32_t*>(s + l.idx);
+    float* sorted = reinterpret_cast<float*>(s);
+    const int32_t n = (int32_t)len;
+    // 16-byte aligned rows need no room before their start
+    const bool vec = len % 4 == 0 && (uintptr_t)x % 16 == 0;
+    const uint32_t segs = vec ? (uint32_t)((len + 4096 * J - 1) / (4096 * J)) : l.segs;
+    const unsigned tiles = (unsigned)(rows * segs);
+    hipLaunchKernelGGL(k_nuc_hist<J>, dim3(tiles), dim3(kNucThreads), 0, stream, x, n,
+                       (uint32_t)rows, segs, hist, info, maps, above,
+                       kNucGroupMax - l.window < 4096u ? kNucGroupMax - l.window : 4096u);
+    hipLaunchKernelGGL(k_nuc_pick, dim3((unsigned)rows), dim3(kNucThreads), 0, stream,
+                       (const uint16_t*)hist, segs, (const uint32_t*)maps, p, n, heads, info,
+                       (const double*)above, l.window, l.ngroups, groups);
+    hipLaunchKernelGGL(k_nuc_gather<J>, dim3(tiles), dim3(kNucThreads), 0, stream, x, n,
+                       (uint32_t)rows, segs, info, keys, idx, l.stride);
+    const uint32_t want = (heads * 4096u * 5 / 4 + l.window - 1) / l.window;
+    const uint32_t parts = want < l.ngroups ? want : l.ngroups;
+    hipLaunchKernelGGL(k_nuc_sort, dim3((unsigned)rows * parts), dim3(kNucThreads), 0, stream,
+                       (const uint32_t*)keys, l.stride, n, (uint32_t)rows, parts,
+                       (const NucRow*)info, (const uint2*)groups, l.ngroups, sorted);
+}
+
+// The sorted rows (stride len) at the start of scratch (16-byte aligned; 16
+// bytes per element hold everything): in every row as many elements as a draw
+// at p with `heads` head tiles reads; *src: where their source indices are
+// found.  Rows of up to kNucMaxLen elements.
+hipError_t launch_nucleus_sort(const float* probs, float p, uint32_t heads, int64_t rows,
+                               int64_t len, void* scratch, size_t scratch_bytes, NucSource* src,
+                               hipStream_t stream) {
+    const uint32_t* x = reinterpret_cast<const uint32_t*>(probs);
+    char* s = reinterpret_cast<char*>(scratch);
+    const NucLayout l = nucleus_layout(rows, len);
+    if (len > kNucMaxLen || l.end > scratch_bytes) return hipErrorInvalidValue;  // not its rows
+    *src = NucSource{};
+    src->x = x;
+    if (len <= (int64_t)kNucGroupMax) {
+        hipLaunchKernelGGL(k_nuc_sort_row, dim3((unsigned)rows), dim3(kNucThreads), 0, stream, x,
+                           (int32_t)len, reinterpret_cast<float*>(s));
+        return hipGetLastError();
+    }
+    if (nucleus_tile(rows, len) == 32768u)
+        nucleus_bins<8>(x, rows, len, p, heads, l, s, stream);
+    else
+        nucleus_bins<2>(x, rows, len, p, heads, l, s, stream);
+    src->keys = reinterpret_cast<const uint32_t*>(s + l.keys);
+    src->idx = reinterpret_cast<const uint32_t*>(s + l.idx);
+    src->rows = reinterpret_cast<const NucRow*>(s + l.rows);
+    src->stride = l.stride;
+    return hipGetLastError();
+}
+
+}  // namespace ls

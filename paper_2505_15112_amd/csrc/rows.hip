@@ -20,6 +20,7 @@
 #include <limits.h>
 
 #include "launch.hpp"
+#include "nucleus.hpp"
 #include "rowtile.hpp"
 
 namespace ls {
@@ -656,15 +657,124 @@ __device__ int64_t topp_head_find(const float* xr, int64_t len, const uint64_t* 
     return -1;
 }
 
+// Source index of the element at position j of a row's sorted elements: of the
+// elements of that value the one with as many before it, by index, as the
+// sorted row has equal ones before j.  The whole workgroup (kThreads); s_t:
+// 1027 words of LDS.
+template <int kThreads>
+__device__ __forceinline__ int32_t topp_token(const NucSource& src, uint32_t row, int64_t len,
+                                              const float* sorted, uint32_t j, uint32_t* s_t) {
+    const uint32_t t = threadIdx.x;
+    const uint32_t* xr = src.x + (int64_t)row * len;
+    const uint32_t* kr = src.keys + (int64_t)row * src.stride;
+    const uint32_t* ir = src.idx + (int64_t)row * src.stride;
+    const uint32_t n = src.keys ? src.rows[row].sorted : (uint32_t)len;
+    const uint32_t key = nuc_key(Bits<float>::to(sorted[j]));
+    uint32_t* s_c = s_t + 1024;  // matches, equal before j, equal in all
+    if (t < 3) s_c[t] = 0;
+    __syncthreads();
+    // equal elements next to j in the sorted row, up to kThreads each side
+    const bool eb = t < j && nuc_key(Bits<float>::to(sorted[j - 1 - t])) == key;
+    const bool ea = t + j + 1 < n && nuc_key(Bits<float>::to(sorted[j + 1 + t])) == key;
+    const uint32_t cb = (uint32_t)__builtin_popcountll(__ballot(eb));
+    const uint32_t ca = (uint32_t)__builtin_popcountll(__ballot(ea));
+    if (lane_id() == 0 && (cb || ca)) {
+        atomicAdd(&s_c[1], cb);
+        atomicAdd(&s_c[2], cb + ca);
+    }
+    __syncthreads();
+    const uint32_t tie = s_c[1], equal = s_c[2] + 1;
+    // f(key, place in the list or row) for every element, until done()
+    auto each = [&](auto f, auto done) {
+        if (src.keys) {
+            constexpr int kLoads = 12;  // 16-byte loads in flight
+            for (uint32_t b = 0; b < n && !done(); b += kLoads * 4 * kThreads) {
+                u32x4 v[kLoads];
+#pragma unroll
+                for (int q = 0; q < kLoads; ++q) {
+                    const uint32_t i = b + (q * kThreads + t) * 4;
+                    v[q] = i < n ? reinterpret_cast<const u32x4*>(kr)[i / 4] : u32x4{0u, 0u, 0u, 0u};
+                }
+#pragma unroll
+                for (int q = 0; q < kLoads; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t i = b + (q * kThreads + t) * 4 + e;
+                        if (v[q][e] == key && i < n) f(i);
+                    }
+            }
+        } else {
+            for (uint32_t i = t; i < n; i += kThreads)
+                if (nuc_key(xr[i]) == key) f(i);
+        }
+    };
+    auto source = [&](uint32_t i) { return src.keys ? ir[i] : i; };
+    if (tie < (uint32_t)kThreads && equal <= (uint32_t)kThreads) {  // uniform: all of them counted
+        each(
+            [&](uint32_t i) {
+                const uint32_t at = atomicAdd(&s_c[0], 1u);
+                if (at < (uint32_t)kThreads) s_t[at] = source(i);
+            },
+            [&] { return *(volatile uint32_t*)&s_c[0] >= equal; });
+        __syncthreads();
+        if (equal > 1 && t < equal) {  // the tie-th smallest index
+            const uint32_t mine = s_t[t];
+            uint32_t r = 0;
+            for (uint32_t i = 0; i < equal; ++i) r += s_t[i] < mine ? 1u : 0u;
+            if (r == tie) s_c[1] = mine;
+        }
+        __syncthreads();
+        return (int32_t)(equal > 1 ? s_c[1] : s_t[0]);
+    }
+    // many: how many equal elements precede j (a search for the first of them
+    // in the sorted row), then the index of that rank (below 2^20), 10 bits at
+    // a time
+    uint32_t lo = 0, hi = j;
+    while (lo < hi) {  // uniform
+        const uint32_t mid = (lo + hi) / 2;
+        if (nuc_key(Bits<float>::to(sorted[mid])) > key) lo = mid + 1; else hi = mid;
+    }
+    uint32_t need = j - lo, prefix = 0;
+    for (int sh = 10; sh >= 0; sh -= 10) {
+        __syncthreads();
+        for (uint32_t i = t; i < 1024; i += kThreads) s_t[i] = 0;
+        __syncthreads();
+        each(
+            [&](uint32_t i) {
+                const uint32_t s = source(i);
+                if (sh == 10 || (s >> 10) == prefix) atomicAdd(&s_t[(s >> sh) & 1023u], 1u);
+            },
+            [] { return false; });
+        __syncthreads();
+        if (t < kWave) {  // lane t: counts 16 t .. 16 t + 15
+            uint32_t c = 0;
+            for (int i = 0; i < 16; ++i) c += s_t[16 * t + i];
+            const uint32_t inc = wave_incl_scan(c);
+            uint32_t left = need - (inc - c);
+            if (inc - c <= need && need < inc) {  // one lane
+                uint32_t i = 16 * t;
+                while (left >= s_t[i]) left -= s_t[i++];
+                s_c[0] = i;
+                s_c[1] = left;
+            }
+        }
+        __syncthreads();
+        prefix = (prefix << 10) | s_c[0];
+        need = s_c[1];
+    }
+    return (int32_t)prefix;
+}
+
 // The cutoff k (len - 1 when no running sum reaches p); SAMPLE: the top-p
 // draw on the sorted rows as well -- with C the running sum at k, the first
 // index j <= k whose running sum exceeds theta * C (j = k when rounding
-// leaves none), found the same way; the token is idx[j] (idx null: j
-// itself), and the cutoff is stored only when asked for.
+// leaves none), found the same way; the token is that element's source index
+// (topp_token), and the cutoff is stored only when asked for.
 template <bool VEC, bool SAMPLE>
 __global__ __launch_bounds__(kFinishThreads<VEC>) LS_OCCUPANCY4 void k_topp_finish(
     const float* probs, int32_t* cutoff, int64_t len, uint32_t heads, float p,
-    const uint64_t* words, const int32_t* idx, const float* theta, int32_t* token) {
+    const uint64_t* words, NucSource src, const float* theta, int32_t* token) {
+    __shared__ uint32_t s_t[SAMPLE ? 1027 : 1];
     __shared__ int32_t s_tile;
     __shared__ float s_e;
     __shared__ float s_wtot[kFinishThreads<VEC> / kWave];
@@ -687,9 +797,10 @@ __global__ __launch_bounds__(kFinishThreads<VEC>) LS_OCCUPANCY4 void k_topp_fini
     int64_t j = topp_head_find<VEC, true>(xr, len, hw, heads, theta[row32] * c, k, &at, &s_tile,
                                           &s_e, s_wtot, s_min, &s_val);
     if (j < 0) j = k;
+    const int32_t tok = topp_token<kFinishThreads<VEC>>(src, row32, len, xr, (uint32_t)j, s_t);
     if (threadIdx.x == 0) {
         if (cutoff) cutoff[row32] = (int32_t)k;
-        token[row32] = idx ? idx[(int64_t)row32 * len + j] : (int32_t)j;
+        token[row32] = tok;
     }
 }
 
@@ -900,11 +1011,11 @@ static void topp_cutoff_early(bool vec, const float* probs, int32_t* cutoff, int
     hipLaunchKernelGGL(kf, dim3((unsigned)rows),
                        dim3(vec ? kFinishThreads<true> : kFinishThreads<false>), 0,
                        stream, probs, cutoff,
-                       len, heads, p, words, nullptr, nullptr, nullptr);
+                       len, heads, p, words, NucSource{}, nullptr, nullptr);
 }
 
 // The top-p draw on sorted rows by the same two kernels (rows as topp_early).
-static void topp_sample_early(bool vec, const float* sorted, const int32_t* idx,
+static void topp_sample_early(bool vec, const float* sorted, const NucSource& src,
                               const float* theta, int32_t* cutoff, int32_t* token, int64_t rows,
                               int64_t len, float p, void* ws, hipStream_t stream) {
     using TV = RowTile<float, RGeomS, true>;
@@ -918,7 +1029,7 @@ static void topp_sample_early(bool vec, const float* sorted, const int32_t* idx,
     hipLaunchKernelGGL(kf, dim3((unsigned)rows),
                        dim3(vec ? kFinishThreads<true> : kFinishThreads<false>), 0,
                        stream, sorted, cutoff,
-                       len, heads, p, words, idx, theta, token);
+                       len, heads, p, words, src, theta, token);
 }
 
 template <ToppMode MODE>
@@ -927,10 +1038,6 @@ static void topp_any(bool vec, const float* probs, const int32_t* idx, const flo
                      void* ws, hipStream_t stream) {
     if (MODE == ToppMode::Cutoff && topp_early(len)) {
         topp_cutoff_early(vec, probs, cutoff, rows, len, p, ws, stream);
-        return;
-    }
-    if (MODE == ToppMode::Sample && topp_early(len)) {
-        topp_sample_early(vec, probs, idx, theta, cutoff, token, rows, len, p, ws, stream);
         return;
     }
     const int64_t t = row_tile(len);
@@ -1035,7 +1142,8 @@ hipError_t launch_weighted_sample(const float* w, const float* theta, int32_t* o
 }
 
 // The top-p draw on rows already sorted in descending order: cutoff k, then
-// the draw among 0..k, reported through idx (workspace topp_ws_bytes).
+// the draw among 0..k, reported through idx (workspace topp_ws_bytes); rows of
+// up to 4096 elements or more than 2^20.
 hipError_t launch_topp_draw_sorted(const float* sorted, const int32_t* idx, const float* theta,
                                    float p, int32_t* token, int32_t* cutoff, int64_t rows,
                                    int64_t len, void* ws, hipStream_t stream) {
@@ -1049,16 +1157,23 @@ hipError_t launch_topp_draw_sorted(const float* sorted, const int32_t* idx, cons
         return hipGetLastError();
     }
     const bool vec = (len % 4 == 0) && aligned16(sorted);
-    topp_any<ToppMode::Sample>(vec, sorted, idx, theta, cutoff, token, rows, len, p, ws, stream);
+    if (len <= kRowTile)
+        topp_long<RGeomS, ToppMode::Sample>(vec, sorted, idx, theta, cutoff, token, rows, len, p,
+                                            ws, stream);
+    else
+        topp_long<RGeomL, ToppMode::Sample>(vec, sorted, idx, theta, cutoff, token, rows, len, p,
+                                            ws, stream);
     return hipGetLastError();
 }
 
-// The top-p sampler on unsorted rows (Section 5 "Top-p or Nucleus Sampling"):
-// a stable descending radix sort of each row, keeping source indices, then
-// the cutoff and the draw on the sorted row.  Workspace: the sort's and the
-// draw's common head.  Scratch (caller memory with no invariant, since it
-// ends up holding sort codes): four rows x len arrays -- sorted keys, their
-// source indices, and the sort's two ping-pong buffers.
+// The top-p sampler on unsorted rows (Section 5 "Top-p or Nucleus Sampling").
+// Rows of 4097 to 2^20: as much of each row as the draw reads is sorted
+// (nucleus.hip), then the early-exit kernels draw on it.  Other rows: a stable
+// descending radix sort of each row, keeping source indices, then the cutoff
+// and the draw on the sorted row.  Workspace: the sort's and the draw's common
+// head.  Scratch (caller memory with no invariant, since it ends up holding
+// sort codes): four rows x len arrays -- sorted keys, their source indices, and
+// the sort's two ping-pong buffers; the partial sort fits in it too.
 static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 size_t topp_sample_ws_bytes(int64_t rows, int64_t len) {
     const size_t a = radix_rows_ws_bytes(rows, len), b = scan_rows_ws_bytes(rows, len);
@@ -1074,6 +1189,16 @@ hipError_t launch_topp_sample(const float* probs, const float* theta, float p, i
     if (len == 0)
         return launch_topp_draw_sorted(probs, nullptr, theta, p, token, cutoff, rows, len, ws,
                                        stream);
+    if (topp_early(len)) {
+        const uint32_t heads = topp_heads(len);
+        NucSource src;
+        const hipError_t e = launch_nucleus_sort(
+            probs, p, heads, rows, len, scratch, topp_sample_scratch_bytes(rows, len), &src, stream);
+        if (e != hipSuccess) return e;
+        topp_sample_early(len % 4 == 0, reinterpret_cast<const float*>(scratch), src, theta, cutoff,
+                          token, rows, len, p, ws, stream);
+        return hipGetLastError();
+    }
     const size_t mb = align256((size_t)rows * (size_t)len * 4);
     char* base = reinterpret_cast<char*>(scratch);
     float* sorted = reinterpret_cast<float*>(base);

@@ -268,3 +268,72 @@ def test_weighted_sample_config_128x131072(ops):
     theta = W.sample_theta(128, seed=5)
     g = to_host(ops.weighted_sample_f32(to_dev(w), to_dev(theta)))
     _check_weighted(g, w, theta, "weighted config")
+
+
+# ---------------------------------------------------------------- the sampler's partial sort
+
+PARTIAL_LENGTHS = [4097, 12_288, 12_289, 32_768, 40_961, 100_003, 131_072, 262_145, 1 << 20]
+
+
+def _partial_rows(kind, rows, length, rng):
+    """Small integers (every running sum exact in fp32 up to 2^21) whose order
+    and density try the bins and groups of the partial sort."""
+    if kind == "ties":  # a few values, many times each: bins larger than LDS
+        x = rng.integers(0, 4, (rows, length))
+    elif kind == "equal":
+        x = np.ones((rows, length), np.int64)
+    elif kind == "top":  # one element holds most of the mass, in no sample
+        x = rng.integers(0, 2, (rows, length))
+        x[np.arange(rows), rng.integers(0, length, rows)] = 1 << 20
+    elif kind == "signed":
+        x = rng.integers(-3, 4, (rows, length))
+    else:  # special
+        x = rng.integers(0, 4, (rows, length)).astype(np.float32)
+        for r, v in enumerate([np.inf, np.nan, -np.inf, -np.nan, -0.0]):
+            x[r % rows, rng.integers(0, length)] = v
+    return np.ascontiguousarray(x, dtype=np.float32)
+
+
+@pytest.mark.parametrize("length", PARTIAL_LENGTHS)
+@pytest.mark.parametrize("kind", ["ties", "equal", "top", "signed", "special"])
+def test_topp_sample_partial_sort_exact(ops, length, kind):
+    """Rows of 4097 to 2^20 are sorted as far as the draw reads them; with
+    exact sums cutoff and token must be the oracle's: p met early, late, at the
+    last element and never."""
+    rows = 6 if length < (1 << 18) else 2
+    announce("topp partial sort", length, kind)
+    rng = np.random.default_rng(length)
+    x = _partial_rows(kind, rows, length, rng)
+    theta = (rng.integers(0, 8, rows) / 8.0).astype(np.float32)
+    total = float(np.nanmin(np.where(np.isfinite(x), x, 0).astype(np.float64).sum(axis=1)))
+    for p in (1.0, np.floor(abs(total) / 2), abs(total), 2.0**22):
+        rt, rc = oracle.topp_sample_f32(x, theta, p)
+        tok, cut = ops.topp_sample_f32(to_dev(x), to_dev(theta), p, with_cutoff=True)
+        assert_equal_first_diff(to_host(cut), rc, f"cutoff {length} {kind} {p}")
+        assert_equal_first_diff(to_host(tok), rt, f"token {length} {kind} {p}")
+
+
+@pytest.mark.parametrize("length", PARTIAL_LENGTHS)
+@pytest.mark.parametrize("rows", [1, 9, 300])
+def test_topp_sample_cutoff_as_sorted_rows(ops, length, rows):
+    """On any data the cutoff is the one that the same additions find on the
+    whole sorted rows (row sort, then the top-p cutoff): flat, peaked, bf16 and
+    masked probabilities, small and large batches (both tile and group sizes)."""
+    if rows * length > 1 << 24:
+        pytest.skip("the largest batches add nothing")
+    import torch
+    announce("topp cutoff as on sorted rows", rows, length)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(length + rows)
+    z = torch.randn((rows, length), device="cuda", generator=g)
+    theta = torch.rand(rows, device="cuda", generator=g)
+    for x in (torch.softmax(2 * z, 1), torch.softmax(1e-4 * z, 1), torch.softmax(8 * z, 1),
+              torch.softmax((2 * z).bfloat16().float(), 1), torch.softmax(z, 1) * (z > 1.5)):
+        srt, perm = ops.radix_sort_rows_f32(x.contiguous(), descending=True)
+        for p in (0.1, 0.9, 0.999, 1.0):
+            tok, cut = ops.topp_sample_f32(x.contiguous(), theta, p, with_cutoff=True)
+            want = ops.topp_cutoff_f32(srt, p)
+            assert torch.equal(cut, want), (rows, length, p, cut[:4], want[:4])
+            # the token lies at or before the cutoff in the sorted row
+            pos = (perm == tok[:, None]).int().argmax(dim=1)
+            assert bool((pos <= cut).all()), (rows, length, p)
