@@ -933,21 +933,15 @@ static void rows_tiles(bool exclusive, const typename TileT::T* x, typename Tile
 //   16 x 131072:  8192 8.5, 16384 7.7, 32768 8.2, 65536 10.8
 //   16 x 262144:  16384 10.7, 32768 9.9, 65536 12.1
 //   32 x 262144:  32768 15.2, 65536 14.8;  512 x 131072: 97 / 81
-// Misaligned rows (element-wise loads) stop at 32768 elements a tile:
-//   4 x 20003: look-back 4096 3.9, whole row 5.2;  64 x 20003: 9.3 / 6.2
 // The workspace holds (per row) one status word per 4096 elements up to
 // 65536, per 8192 up to 2^20, per 32768 above: smaller tiles are not taken.
 template <class T, bool VEC>
 static void rows_any(bool exclusive, const T* x, T* y, int64_t rows, int64_t len, void* ws,
                      size_t ws_bytes, hipStream_t stream) {
-    // C chunks a lane and W waves when aligned, half the chunks and twice the
-    // waves when not (at most 16 of 8)
-#define LS_ROWS(W, C)                                                                    \
-    rows_tiles<Tile<T, T, kRVec, VEC ? (C) : ((W) < 16 ? (C) / 2 : 8),                    \
-                    VEC ? (W) : ((W) < 16 ? (W) * 2 : 16)>,                               \
-               VEC>(exclusive, x, y, rows, len, ws, ws_bytes, stream)
+#define LS_ROWS(W, C) \
+    rows_tiles<Tile<T, T, kRVec, C, W>, VEC>(exclusive, x, y, rows, len, ws, ws_bytes, stream)
     const int64_t n = rows * len;
-    const bool whole = len <= 8192 || (len <= 32768 && n > (VEC ? int64_t(1) << 15 : int64_t(1) << 20)) ||
+    const bool whole = len <= 8192 || (len <= 32768 && n > (int64_t(1) << 15)) ||
                        (len <= 65536 && n >= int64_t(1) << 20);
     if (len <= kRowTile)
         LS_ROWS(4, 4);
@@ -957,7 +951,7 @@ static void rows_any(bool exclusive, const T* x, T* y, int64_t rows, int64_t len
         LS_ROWS(8, 8);
     else if (whole && len <= 32768)
         LS_ROWS(16, 8);
-    else if (VEC && whole)
+    else if (whole)
         LS_ROWS(16, 16);
     else if (len <= 65536 && n < int64_t(1) << 18)
         LS_ROWS(4, 4);
@@ -965,7 +959,7 @@ static void rows_any(bool exclusive, const T* x, T* y, int64_t rows, int64_t len
         LS_ROWS(8, 4);
     else if (len <= int64_t(1) << 20 && n < int64_t(1) << 22)
         LS_ROWS(8, 8);
-    else if (!VEC || n < int64_t(1) << 23)
+    else if (n < int64_t(1) << 23)
         LS_ROWS(16, 8);
     else
         LS_ROWS(16, 16);

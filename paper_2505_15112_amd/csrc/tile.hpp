@@ -11,12 +11,17 @@
 // chunks of the wave, and the wave totals combined through LDS.
 #pragma once
 
+#include <type_traits>
+
 #include "device.hpp"
 
 namespace ls {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// Four words at a 4-byte aligned address: the global memory instructions need
+// no more for a 16-byte access.
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 // ---------------------------------------------------------------- conversion
 
@@ -43,15 +48,18 @@ struct Conv<uint8_t, uint32_t> {  // unsigned byte value
     __device__ static uint32_t f(uint8_t v) { return v; }
 };
 
-// Aligned vector load of V elements of In, converted to T.  NT: 16-byte
+// Vector load of V elements of In, converted to T, at an address aligned to the
+// whole vector, or (A4: 16-byte vectors only) to 4 bytes.  NT: 16-byte
 // loads are nontemporal (data read once, kept out of the caches' way).
-template <class In, class T, int V, bool NT = false>
+template <class In, class T, int V, bool NT = false, bool A4 = false>
 __device__ __forceinline__ void load_vec(const In* p, T (&out)[V]) {
     constexpr int kBytes = V * (int)sizeof(In);
+    static_assert(!A4 || kBytes == 16, "4-byte aligned vectors are 16 bytes");
     In e[V];
     if constexpr (kBytes == 16) {
-        const u32x4 r = NT ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p))
-                           : *reinterpret_cast<const u32x4*>(p);
+        using Vec = typename std::conditional<A4, u32x4_a4, u32x4>::type;
+        const Vec r = NT ? __builtin_nontemporal_load(reinterpret_cast<const Vec*>(p))
+                         : *reinterpret_cast<const Vec*>(p);
         __builtin_memcpy(e, &r, 16);
     } else if constexpr (kBytes == 8) {
         const u32x2 r = *reinterpret_cast<const u32x2*>(p);
@@ -66,15 +74,17 @@ __device__ __forceinline__ void load_vec(const In* p, T (&out)[V]) {
     for (int i = 0; i < V; ++i) out[i] = Conv<In, T>::f(e[i]);
 }
 
-// Aligned vector store of V 32-bit elements (V/4 16-byte stores).
-template <class T, int V>
+// Vector store of V 32-bit elements (V/4 16-byte stores), at an address aligned
+// to 16 bytes or (A4) to 4.
+template <class T, int V, bool A4 = false>
 __device__ __forceinline__ void store_vec(T* p, const T (&v)[V]) {
     static_assert(sizeof(T) == 4 && V % 4 == 0, "16-byte stores of 32-bit elements");
+    using Vec = typename std::conditional<A4, u32x4_a4, u32x4>::type;
 #pragma unroll
     for (int q = 0; q < V / 4; ++q) {
-        u32x4 r;
+        Vec r;
         __builtin_memcpy(&r, v + 4 * q, 16);
-        __builtin_nontemporal_store(r, reinterpret_cast<u32x4*>(p) + q);
+        __builtin_nontemporal_store(r, reinterpret_cast<Vec*>(p) + q);
     }
 }
 
@@ -101,17 +111,22 @@ struct Tile {
     __device__ static int64_t offset(int64_t base, int j) { return base + lane_offset(j); }
 
     // Load the tile starting at `base`; elements at or past n read as zero.
-    // NT: nontemporal 16-byte loads (see load_vec).
+    // NT: nontemporal 16-byte loads (see load_vec).  VEC: x is aligned to whole
+    // vectors; otherwise to its elements, and 16-byte vectors of 32-bit elements
+    // are loaded all the same (they need 4-byte alignment only; element-wise
+    // loads of 4 neighbours a lane touch every cache line four times).
+    static constexpr bool kAnyVec = sizeof(In) == 4 && V * sizeof(In) == 16;
     template <bool VEC, bool NT = false>
     __device__ static void load(const In* x, int64_t n, int64_t base, T (&v)[J][V]) {
         const In* xt = x + base;  // wave-uniform
-        if (VEC && base + kElems <= n) {  // uniform: all vector loads issued back to back
+        constexpr bool A4 = !VEC && kAnyVec;
+        if ((VEC || A4) && base + kElems <= n) {  // uniform: all vector loads issued back to back
 #pragma unroll
-            for (int j = 0; j < J; ++j) load_vec<In, T, V, NT>(xt + lane_offset(j), v[j]);
+            for (int j = 0; j < J; ++j) load_vec<In, T, V, NT, A4>(xt + lane_offset(j), v[j]);
         } else {
             // Ragged last tile (or unaligned data): per chunk, a lane with all
             // V elements in range loads them without per-element tests (one
-            // vector load when aligned), a lane straddling the end loads
+            // vector load where there is one), a lane straddling the end loads
             // element by element.  Counts are 32-bit (valid <= kElems).
             const int32_t valid = (int32_t)(n - base < kElems ? n - base : kElems);
 #pragma unroll
@@ -119,8 +134,8 @@ struct Tile {
                 const int32_t off = (int32_t)lane_offset(j);
                 const int32_t rem = valid - off;
                 if (rem >= V) {  // one branch per chunk, not one predicate per element
-                    if (VEC) {
-                        load_vec<In, T, V, NT>(xt + off, v[j]);
+                    if (VEC || A4) {
+                        load_vec<In, T, V, NT, A4>(xt + off, v[j]);
                     } else {
 #pragma unroll
                         for (int e = 0; e < V; ++e) v[j][e] = Conv<In, T>::f(xt[off + e]);
@@ -201,13 +216,14 @@ struct Tile {
     template <bool VEC>
     __device__ static void store(T* y, int64_t n, int64_t base, const T (&v)[J][V], T carry) {
         T* yt = y + base;  // wave-uniform
-        if (VEC && base + kElems <= n) {
+        constexpr bool A4 = !VEC && kAnyVec;  // as in load
+        if ((VEC || A4) && base + kElems <= n) {
 #pragma unroll
             for (int j = 0; j < J; ++j) {
                 T o[V];
 #pragma unroll
                 for (int e = 0; e < V; ++e) o[e] = carry + v[j][e];
-                store_vec<T, V>(yt + lane_offset(j), o);
+                store_vec<T, V, A4>(yt + lane_offset(j), o);
             }
         } else {
             const int32_t valid = (int32_t)(n - base < kElems ? n - base : kElems);
@@ -219,8 +235,8 @@ struct Tile {
 #pragma unroll
                 for (int e = 0; e < V; ++e) o[e] = carry + v[j][e];
                 if (rem >= V) {
-                    if (VEC) {
-                        store_vec<T, V>(yt + off, o);
+                    if (VEC || A4) {
+                        store_vec<T, V, A4>(yt + off, o);
                     } else {
 #pragma unroll
                         for (int e = 0; e < V; ++e) yt[off + e] = o[e];
