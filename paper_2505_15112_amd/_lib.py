@@ -133,7 +133,7 @@ def using(lib):
 
 def call(name: str, *args):
     """Call an entry point; raise LibscanError on a non-zero status."""
-    lib = load()
+    lib = _LIB or load()
     st = getattr(lib, name)(*args)
     if st != OK:
         raise LibscanError(name, st, lib)
