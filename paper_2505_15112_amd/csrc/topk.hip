@@ -433,8 +433,11 @@ __device__ __forceinline__ void stage_candidates(const V& v, Mask take, uint32_t
     uint32_t* dk = staged ? s_ck : ck;
     uint32_t* di = staged ? s_ci : ci;
     const uint32_t lim = staged ? kTopkStage : room;
-    uint32_t lane0 = base + (uint32_t)TileT::lane_offset(0);
-    asm volatile("" : "+v"(lane0));  // no per-chunk offsets kept live from the loads
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // no offsets kept live from the loads
+    // the lane's chunk-0 elements (Tile::lane_offset(0))
+    const uint32_t lane0 =
+        base + ((tid / kWave) * TileT::J * kWave + tid % kWave) * TileT::V;
     if (take) {
 #pragma unroll
         for (int j = 0; j < TileT::J; ++j) {
@@ -516,8 +519,9 @@ __global__ __launch_bounds__(TileT::kThreads) LS_OCCUPANCY8 void k_topk_gather(
 // read of each row.  Every tile keeps as candidates its keys whose top 16
 // bits are at least those of the tile's own k-th largest key.  That is a
 // superset of the tile's share of the row's top k: a key below it has k keys
-// of its own tile above it.  Two digit rounds over the tile, held in
-// registers, find that 16-bit prefix (LDS histograms as in k_topk_count0);
+// of its own tile above it.  Two digit rounds over the largest keys of the
+// tile's 512 groups (or, failing that, over the whole tile, held in registers)
+// find a prefix that is no larger (LDS histograms as in k_topk_count0);
 // the tile writes its candidates to its own kTopkTileSlots slots (keys and
 // complemented indices, the two halves of their composites) and their number
 // to tcount (more than the slots: none written, and the row is finished the
@@ -534,7 +538,8 @@ static_assert(kTopkTileSlots * kTopkGatherSegs <= kTopkCand, "a row's candidates
 template <int COPIES>
 __device__ __forceinline__ void tile_bucket(const uint32_t* s_h, uint32_t need, uint32_t* s_part,
                                             uint32_t* s_out) {
-    const int t = threadIdx.x;
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));  // nothing derived from it kept live between calls
     const int w = t / kWave;
     uint32_t c = 0;
     if (t < kTopkDigits) {
@@ -576,8 +581,6 @@ __global__ __launch_bounds__(TileT::kThreads) LS_OCCUPANCY8 void k_topk_tilesel(
     uint32_t v[TileT::J][TileT::V];
     TileT::template load<VEC, true>(x + row * len, len, base, v);
     const int32_t valid = (int32_t)(len - base < TileT::kElems ? len - base : TileT::kElems);
-    __syncthreads();  // histograms cleared
-    uint32_t* h = s_h + (lane_id() & (kTopkCopies - 1)) * kTopkCopyStride;
     // bit j V + e: element (j, e) of this lane lies in the row (one register;
     // opaque, so that the compiler keeps no per-element flags beside it)
     using Mask = typename std::conditional<(TileT::J * TileT::V > 32), uint64_t, uint32_t>::type;
@@ -591,10 +594,9 @@ __global__ __launch_bounds__(TileT::kThreads) LS_OCCUPANCY8 void k_topk_tilesel(
             inrow |= (Mask)(off + e < valid ? 1u : 0u) << (j * TileT::V + e);
     }
     asm volatile("" : "+v"(inrow));
-    // round 0: the top byte of every key of the tile.  Positions past the
-    // row's end count as key 0, the smallest: need <= valid, so they do not
-    // move the need-th largest key, and the candidates are taken below with
-    // the bound checked.
+    // the keys; positions past the row's end count as key 0, the smallest:
+    // need <= valid, so they do not move the need-th largest key, and the
+    // candidates are taken below with the bound checked
 #pragma unroll
     for (int j = 0; j < TileT::J; ++j) {
 #pragma unroll
@@ -602,48 +604,117 @@ __global__ __launch_bounds__(TileT::kThreads) LS_OCCUPANCY8 void k_topk_tilesel(
             const uint32_t key = topk_key(v[j][e], largest);
             v[j][e] = (inrow >> (j * TileT::V + e)) & 1u ? key : 0u;
             asm volatile("" : "+v"(v[j][e]));  // the unmasked key is dead here
-            atomicAdd(&h[v[j][e] >> 24], 1u);
         }
     }
-    __syncthreads();
+    __syncthreads();  // histograms cleared
     const uint32_t need = k < (uint32_t)valid ? k : (uint32_t)valid;
-    tile_bucket<kTopkCopies>(s_h, need, s_part, &s_sel);
-    __syncthreads();  // s_sel written
-    const uint32_t d = s_sel & 255u, need1 = s_sel >> 8;
-    // round 1: the second byte of the keys in bucket d
-    uint32_t* h1 = s_h1 + (lane_id() & (kCopies1 - 1)) * kTopkCopyStride;
-#pragma unroll
-    for (int j = 0; j < TileT::J; ++j) {
-#pragma unroll
-        for (int e = 0; e < TileT::V; ++e)
-            if ((v[j][e] >> 24) == d) atomicAdd(&h1[(v[j][e] >> 16) & 255u], 1u);
-    }
-    __syncthreads();
-    tile_bucket<kCopies1>(s_h1, need1, s_part, &s_sel);
-    __syncthreads();
-    const uint32_t p16 = (d << 8) | (s_sel & 255u);
+    // First the tile's 512 groups (a thread's keys, or two halves of them) stand
+    // in for the keys: the need-th largest of their largest keys is no more
+    // than the tile's need-th largest key, since need groups hold a key at
+    // least that large.  Two LDS atomics a thread instead of one a key: the
+    // tile kernel of 128 x 131072 at k = 64 takes 16.6 instead of 19.6 us (the
+    // call 26.2 -> 23.8).  On
+    // keys in no order about need (1 + need / 1024) are kept; should the large
+    // keys lie together (or a ragged tile have too few groups) so that more than
+    // the tile's slots are, every key is counted.
+    constexpr int kParts = 512 / TileT::kThreads;
+    static_assert(kParts >= 1 && TileT::J % kParts == 0, "512 groups of whole chunks");
     Mask take = 0;
-    uint32_t cnt = 0;
-#pragma unroll
-    for (int j = 0; j < TileT::J; ++j) {
-#pragma unroll
-        for (int e = 0; e < TileT::V; ++e) {
-            const bool t = ((inrow >> (j * TileT::V + e)) & 1u) && (v[j][e] >> 16) >= p16;
-            take |= (Mask)(t ? 1u : 0u) << (j * TileT::V + e);
-            cnt += t ? 1u : 0u;
+    uint32_t lpos = 0, total = 0;  // this lane's first slot in the tile
+    for (bool all = false;; all = true) {  // at most twice, uniform
+        uint32_t tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));  // as the keys below
+        const uint32_t w = tid / kWave;
+        if (all) {
+            for (uint32_t i = tid; i < kHist; i += TileT::kThreads) s_h[i] = 0;
+            for (uint32_t i = tid; i < kHist1; i += TileT::kThreads) s_h1[i] = 0;
+            __syncthreads();  // histograms cleared
         }
-    }
-    // this lane's first slot within the tile: lanes before it in its wave,
-    // then the waves before it
-    const uint32_t incl = wave_incl_scan(cnt);
-    const int w = threadIdx.x / kWave;
-    if (lane_id() == kWave - 1) s_wtot[w] = incl;
-    __syncthreads();
-    uint32_t lpos = incl - cnt, total = 0;  // this lane's first slot in the tile
 #pragma unroll
-    for (int q = 0; q < TileT::WAVES; ++q) {
-        lpos += q < w ? s_wtot[q] : 0u;
-        total += s_wtot[q];
+        for (int j = 0; j < TileT::J; ++j)
+#pragma unroll
+            for (int e = 0; e < TileT::V; ++e)  // nothing derived from the keys outlives a round
+                asm volatile("" : "+v"(v[j][e]));
+        uint32_t top[kParts];  // the largest key of each of the thread's groups
+#pragma unroll
+        for (int q = 0; q < kParts; ++q) {
+            top[q] = 0;
+#pragma unroll
+            for (int j = q * TileT::J / kParts; j < (q + 1) * TileT::J / kParts; ++j)
+#pragma unroll
+                for (int e = 0; e < TileT::V; ++e) top[q] = v[j][e] > top[q] ? v[j][e] : top[q];
+        }
+        // round 0: the top byte of every counted key
+        if (all) {
+            uint32_t* h = s_h + (tid & (kTopkCopies - 1)) * kTopkCopyStride;
+#pragma unroll
+            for (int j = 0; j < TileT::J; ++j)
+#pragma unroll
+                for (int e = 0; e < TileT::V; ++e) atomicAdd(&h[v[j][e] >> 24], 1u);
+            __syncthreads();
+            tile_bucket<kTopkCopies>(s_h, need, s_part, &s_sel);
+        } else {  // few atomics: two copies, quicker added up
+            uint32_t* h = s_h + (tid & (kCopies1 - 1)) * kTopkCopyStride;
+#pragma unroll
+            for (int q = 0; q < kParts; ++q) atomicAdd(&h[top[q] >> 24], 1u);
+            __syncthreads();
+            tile_bucket<kCopies1>(s_h, need, s_part, &s_sel);
+        }
+        __syncthreads();  // s_sel written
+        const uint32_t sel = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_sel);
+        const uint32_t d = sel & 255u, need1 = sel >> 8;
+        // round 1: the second byte of those in bucket d
+        uint32_t* h1 = s_h1 + (tid & (kCopies1 - 1)) * kTopkCopyStride;
+        if (all) {
+#pragma unroll
+            for (int j = 0; j < TileT::J; ++j)
+#pragma unroll
+                for (int e = 0; e < TileT::V; ++e)
+                    if ((v[j][e] >> 24) == d) atomicAdd(&h1[(v[j][e] >> 16) & 255u], 1u);
+        } else {
+#pragma unroll
+            for (int q = 0; q < kParts; ++q)
+                if ((top[q] >> 24) == d) atomicAdd(&h1[(top[q] >> 16) & 255u], 1u);
+        }
+        __syncthreads();
+        tile_bucket<kCopies1>(s_h1, need1, s_part, &s_sel);
+        __syncthreads();
+        const uint32_t p16 =
+            (d << 8) | ((uint32_t)__builtin_amdgcn_readfirstlane((int)s_sel) & 255u);
+        const uint32_t least = p16 << 16;
+        take = 0;
+#pragma unroll
+        for (int j = 0; j < TileT::J; ++j) {
+#pragma unroll
+            for (int e = 0; e < TileT::V; ++e)
+                take |= (Mask)(v[j][e] >= least ? 1u : 0u) << (j * TileT::V + e);
+        }
+        if (valid < TileT::kElems) {  // uniform: key 0 may be taken, but no padding
+            const int32_t lane0 =
+                (int32_t)(((tid / kWave) * TileT::J * kWave + tid % kWave) * TileT::V);
+#pragma unroll
+            for (int j = 0; j < TileT::J; ++j)
+#pragma unroll
+                for (int e = 0; e < TileT::V; ++e)
+                    if (lane0 + j * kWave * TileT::V + e >= valid)
+                        take &= ~((Mask)1 << (j * TileT::V + e));
+        }
+        asm volatile("" : "+v"(take));  // one register, not a flag per key
+        const uint32_t cnt = (uint32_t)__builtin_popcountll((uint64_t)take);
+        // this lane's first slot within the tile: lanes before it in its wave,
+        // then the waves before it
+        const uint32_t incl = wave_incl_scan(cnt);
+        if ((tid & (kWave - 1)) == kWave - 1) s_wtot[w] = incl;
+        __syncthreads();
+        lpos = incl - cnt;
+        total = 0;
+#pragma unroll
+        for (int q = 0; q < TileT::WAVES; ++q) {
+            lpos += (uint32_t)q < w ? s_wtot[q] : 0u;
+            total += s_wtot[q];
+        }
+        if (all || total <= kTopkTileSlots) break;
+        __syncthreads();  // s_wtot and the histograms are rewritten
     }
     if (threadIdx.x == 0) tcount[blockIdx.x] = total;
     if (total > kTopkTileSlots) return;  // uniform: the row goes the long way

@@ -191,3 +191,24 @@ def test_topk_long_way_close_values(ops, k):
     x[:, ::97] = x[:, 5:6]  # exact ties across the row
     _check(ops, x, k, True, f"long way k={k}")
     _check(ops, x, k, False, f"long way smallest k={k}")
+
+
+@pytest.mark.parametrize("length", [4096, 8192, 16_384, 20_000, 24_576 + 300, 131_072])
+@pytest.mark.parametrize("order", ["descending", "ascending", "blocks"])
+def test_topk_tile_groups(ops, length, order):
+    """The small-k route first lets the largest keys of a tile's 512 groups stand
+    in for its keys: rows whose large keys lie together (sorted, or in blocks)
+    keep too many that way and are counted whole; k on both sides of that, whole
+    and ragged last tiles, tiles with fewer groups than k."""
+    announce("topk tile groups", length, order)
+    x = W.values_f32(3 * length, seed=length).reshape(3, length)
+    if order == "blocks":  # 300 large keys in a run across a tile edge
+        at = min(8192, length) - 150
+        x[:, at:at + 300] += 100.0
+    else:
+        x = np.sort(x, axis=1)
+        x = x[:, ::-1] if order == "descending" else x
+    x = np.ascontiguousarray(x)
+    for k in (1, 63, 64, 65, 100, 255, 256):
+        for largest in (True, False):
+            _check(ops, x, k, largest, f"tile groups {length} {order} k={k} {largest}")
