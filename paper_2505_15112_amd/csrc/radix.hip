@@ -25,6 +25,8 @@
 //    ranking goes through per-wave digit counts in LDS (see below).  Half the
 //    passes of the 4-bit sort, so half its key and index traffic.
 // All variants give identical output: a stable sort is unique.
+#include <type_traits>
+
 #include "launch.hpp"
 #include "tile.hpp"
 
@@ -774,6 +776,138 @@ __global__ __launch_bounds__(kR8Waves* kWave) LS_OCCUPANCY4 void k_radix8_scatte
         body(std::false_type{});
 }
 
+// ---------------------------------------------------------------- rows in one workgroup
+
+// Rows of up to kR8RowMax keys: one workgroup sorts a row whole, every pass
+// from registers through LDS back to registers, with one read and one write of
+// global memory and one launch instead of three per pass.  Ranking as in
+// k_radix8_scatter; the permutation is carried as 16-bit positions.  Such sorts
+// are bound by latency (a launch, then per pass four barriers and the ranking
+// of CH chunks a wave), not by bytes.  Against three kernels a pass (MI355X, us
+// a call with permutation): u32 n = 1000 69 -> 12, 4096 71 -> 13.5, 8192 55 ->
+// 21, 16384 57 -> 36.5; fp16 2000 35 -> 12; rows fp32 2000 x 1000 260 -> 30,
+// 300 x 4096 94 -> 20, 512 x 8192 87 -> 37, 1000 x 16384 248 -> 155.
+constexpr int64_t kR8RowMax = 16384;
+template <class K, int WAVES, int CH, bool WITH_PERM>
+__global__ __launch_bounds__(WAVES* kWave) void k_radix8_row(const K* keys, K* keys_out,
+                                                             const int32_t* perm_in,
+                                                             int32_t* perm_out, uint32_t len,
+                                                             int passes, KeyCode code,
+                                                             KeyDecode decode) {
+    constexpr uint32_t kThreads = WAVES * kWave, kTile = kThreads * CH;
+    static_assert(kThreads >= kR8Digits && kTile <= 65536, "a thread per digit, 16-bit positions");
+    __shared__ uint32_t s_wh[WAVES][kR8Digits];
+    __shared__ uint32_t s_part[kR8Digits / kWave];
+    __shared__ uint32_t s_key[kTile];
+    __shared__ uint16_t s_pos[WITH_PERM ? kTile : 1];
+    const int lane = lane_id();
+    const int w = threadIdx.x / kWave;
+    const int64_t rbase = (int64_t)blockIdx.x * len;
+    const uint32_t wbase = (uint32_t)w * CH * kWave;
+    // Places past the row's end hold the largest code: a stable sort leaves
+    // them last in every pass, so every lane ranks a key and no test is needed.
+    uint32_t key[CH], pos[CH];
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+        const uint32_t i = wbase + j * kWave + lane;
+        pos[j] = i;
+        key[j] = i < len ? (uint32_t)keys[rbase + i] : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < CH; ++j)
+        key[j] = wbase + j * kWave + lane < len ? code.apply(key[j]) : 0xFFFFFFFFu;
+#pragma unroll 1
+    for (int p = 0; p < passes; ++p) {
+        const int shift = 8 * p;
+#pragma unroll
+        for (int i = 0; i < kR8Digits / kWave; ++i) s_wh[w][i * kWave + lane] = 0;
+        wave_lds_sync();
+        uint32_t rank[CH];
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            const uint32_t d = (key[j] >> shift) & 255u;
+            const uint64_t peers = peers8_all(d);
+            const uint32_t below = lanes_below(peers);
+            const uint32_t size = (uint32_t)__builtin_popcountll(peers);
+            if (below == 0) atomicAdd(&s_wh[w][d], size);
+            rank[j] = s_wh[w][d] - size + below;
+        }
+        __syncthreads();
+        // digit d (thread d): each wave's first slot
+        uint32_t tot = 0, inc = 0;
+        if (threadIdx.x < kR8Digits) {
+#pragma unroll
+            for (int k = 0; k < WAVES; ++k) tot += s_wh[k][threadIdx.x];
+            inc = wave_incl_scan(tot);
+            if (lane == kWave - 1) s_part[w] = inc;
+        }
+        __syncthreads();
+        if (threadIdx.x < kR8Digits) {
+            uint32_t first = inc - tot;
+            for (int k = 0; k < w; ++k) first += s_part[k];
+#pragma unroll
+            for (int k = 0; k < WAVES; ++k) {
+                const uint32_t c = s_wh[k][threadIdx.x];
+                s_wh[k][threadIdx.x] = first;
+                first += c;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            const uint32_t slot = rank[j] + s_wh[w][(key[j] >> shift) & 255u];
+            if (slot < kTile) {  // always; checked all the same
+                s_key[slot] = key[j];
+                if (WITH_PERM) s_pos[slot] = (uint16_t)pos[j];
+            }
+        }
+        __syncthreads();
+        if (p == passes - 1) break;
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            const uint32_t i = wbase + j * kWave + lane;
+            key[j] = s_key[i];
+            if (WITH_PERM) pos[j] = s_pos[i];
+        }
+    }
+    for (uint32_t i = threadIdx.x; i < len; i += kThreads) {
+        keys_out[rbase + i] = (K)decode.apply(s_key[i]);
+        if (WITH_PERM) {
+            const uint32_t q = s_pos[i];
+            perm_out[rbase + i] = perm_in ? perm_in[rbase + q] : (int32_t)q;
+        }
+    }
+}
+
+template <class K>
+static void radix8_rows(const K* keys, K* keys_out, const int32_t* perm_in, int32_t* perm_out,
+                        int64_t rows, int64_t len, int passes, KeyCode code, KeyDecode decode,
+                        hipStream_t stream) {
+    auto go = [&](auto waves_c, auto ch_c) {
+        constexpr int WAVES = decltype(waves_c)::value, CH = decltype(ch_c)::value;
+        auto k = perm_out ? k_radix8_row<K, WAVES, CH, true> : k_radix8_row<K, WAVES, CH, false>;
+        constexpr int64_t kPart = (int64_t(1) << 31) / (WAVES * kWave);  // threads per launch
+        for (int64_t r = 0; r < rows; r += kPart) {
+            const int64_t o = r * len;
+            hipLaunchKernelGGL(k, dim3((unsigned)(rows - r < kPart ? rows - r : kPart)),
+                               dim3(WAVES * kWave), 0, stream, keys + o, keys_out + o,
+                               perm_in ? perm_in + o : nullptr, perm_out ? perm_out + o : nullptr,
+                               (uint32_t)len, passes, code, decode);
+        }
+    };
+    using std::integral_constant;
+    if (len <= 512)
+        go(integral_constant<int, 4>{}, integral_constant<int, 2>{});
+    else if (len <= 2048)
+        go(integral_constant<int, 8>{}, integral_constant<int, 4>{});
+    else if (len <= 4096)
+        go(integral_constant<int, 8>{}, integral_constant<int, 8>{});
+    else if (len <= 8192)
+        go(integral_constant<int, 16>{}, integral_constant<int, 8>{});
+    else
+        go(integral_constant<int, 16>{}, integral_constant<int, 16>{});
+}
+
 // ---------------------------------------------------------------- driver
 
 hipError_t launch_radix1_pass(const uint32_t* keys, const int32_t* idx_in, int bit,
@@ -830,6 +964,11 @@ static hipError_t radix8_sort(const K* keys, K* keys_out, const int32_t* perm_in
                               int32_t* perm_out, K* keys_tmp,
                               int32_t* perm_tmp, int64_t rows, int64_t len, int passes,
                               KeyCode code, KeyDecode decode, void* ws, hipStream_t stream) {
+    if (len <= kR8RowMax) {
+        radix8_rows<K>(keys, keys_out, perm_out ? perm_in : nullptr, perm_out, rows, len, passes,
+                       code, decode, stream);
+        return hipGetLastError();
+    }
     const uint32_t tpr = r8_tpr(len);
     const uint32_t nt = (uint32_t)(rows * tpr);
     const int64_t entries = (int64_t)kR8Digits * tpr;  // per row

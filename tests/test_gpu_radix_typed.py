@@ -127,3 +127,44 @@ def test_sort_f32_desc_n2_24(ops):
     rk, rp = oracle.sort_f32(probs, descending=True)
     assert_equal_first_diff(to_host(po), rp, "f32 desc 2^24 perm")
     assert_equal_first_diff(to_host(ko).view(np.uint32), rk.view(np.uint32), "f32 desc 2^24 keys")
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 255, 511, 512, 513, 2047, 2048, 2049, 4096, 4097, 8191,
+                               8192, 8193, 16_383, 16_384, 16_385])
+@pytest.mark.parametrize("desc", [False, True])
+def test_one_workgroup_rows(ops, n, desc):
+    """Rows of up to 16384 keys are sorted by one workgroup each: every size it
+    comes in, and one more than the largest.  The places past a row's end hold the largest
+    code, so many keys share it here (the largest integer ascending, the least
+    descending, NaNs of both signs): ties with the padding keep index order."""
+    import torch
+    announce("one-workgroup rows", n, desc)
+    rng = np.random.default_rng(n)
+    edge = np.int32(-2**31) if desc else np.int32(2**31 - 1)
+    k = np.where(rng.random(n) < 0.4, edge, rng.integers(-5, 5, n)).astype(np.int32)
+    ko, po = ops.radix_sort_i32(to_dev(k), descending=desc)
+    order = np.argsort(-k.astype(np.int64) if desc else k, kind="stable")
+    assert_equal_first_diff(to_host(po), order.astype(np.int32), f"i32 perm {n}")
+    assert_equal_first_diff(to_host(ko), k[order], f"i32 keys {n}")
+    only, none = ops.radix_sort_i32(to_dev(k), descending=desc, with_perm=False)
+    assert none is None
+    assert_equal_first_diff(to_host(only), k[order], f"i32 keys only {n}")
+    u = np.where(rng.random(n) < 0.5, 0xFFFFFFFF, rng.integers(0, 2**32, n)).astype(np.uint32)
+    ko, po = ops.radix_sort_u32(to_dev(u.view(np.int32)))
+    order = np.argsort(u, kind="stable")
+    assert_equal_first_diff(to_host(po), order.astype(np.int32), f"u32 perm {n}")
+    # rows of floats with NaNs, and half keys
+    f = rng.integers(-3, 4, (3, n)).astype(np.float32)
+    f[rng.random((3, n)) < 0.2] = np.nan
+    f[rng.random((3, n)) < 0.2] = -np.float32(np.nan)
+    ko, po = ops.radix_sort_rows_f32(to_dev(f), descending=desc)
+    rk, rp = oracle.sort_rows_f32(f, descending=desc)
+    assert_equal_first_diff(to_host(po), rp, f"row perm {n}")
+    assert_equal_first_diff(to_host(ko).view(np.uint32), rk.view(np.uint32), f"row keys {n}")
+    h = f[0].astype(np.float16)
+    ko, po = ops.radix_sort_f16(to_dev(h), descending=desc)
+    b = h.view(np.uint16).astype(np.int64)
+    code = np.where(b >= 0x8000, 0xFFFF - b, b + 0x8000)
+    order = np.argsort(-code if desc else code, kind="stable")
+    assert_equal_first_diff(to_host(po), order.astype(np.int32), f"f16 perm {n}")
+    assert torch.equal(ko.cpu().view(torch.int16), torch.from_numpy(h[order]).view(torch.int16))
