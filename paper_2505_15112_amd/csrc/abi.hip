@@ -220,7 +220,7 @@ int libscan_workspace_bytes(int op, int64_t n, int64_t rows, int64_t len, int bi
         case LIBSCAN_OP_RADIX_SORT:
             if (n > ls::kMaxRadixKeys) return LIBSCAN_ERANGE;
             if (bits != 1 && bits != 4 && bits != 8) return LIBSCAN_EINVAL;
-            *bytes = ls::radix_ws_bytes(n, bits);
+            *bytes = bits == 8 ? ls::radix_rows_ws_want(1, n) : ls::radix_ws_bytes(n, bits);
             return LIBSCAN_OK;
         case LIBSCAN_OP_SCAN_ROWS: {
             const int r = check_rows(rows, len);
@@ -230,7 +230,7 @@ int libscan_workspace_bytes(int op, int64_t n, int64_t rows, int64_t len, int bi
         }
         case LIBSCAN_OP_SORT_ROWS:
             if (!ls::radix_rows_fit(rows, len)) return LIBSCAN_ERANGE;
-            *bytes = ls::radix_rows_ws_bytes(rows, len);
+            *bytes = ls::radix_rows_ws_want(rows, len);
             return LIBSCAN_OK;
         case LIBSCAN_OP_TOPK: {
             const int r = check_topk(rows, len, n);

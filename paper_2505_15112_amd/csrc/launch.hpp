@@ -101,7 +101,11 @@ hipError_t launch_radix_sort_typed(KeyType type, bool descending, const void* ke
                                    void* keys_tmp,
                                    int32_t* perm_tmp, int64_t rows, int64_t len, void* ws,
                                    size_t ws_bytes, hipStream_t stream);
+// The least workspace of a sort of rows of 8-bit digits, and the one with room
+// for the count table of the tiles that suit the size (reported to callers; with
+// less the sort takes its largest tiles).
 size_t radix_rows_ws_bytes(int64_t rows, int64_t len);
+size_t radix_rows_ws_want(int64_t rows, int64_t len);
 
 // LSD radix sort (1, 4 or 8 bits per pass), caller-provided ping-pong buffers.
 size_t radix_ws_bytes(int64_t n, int bits);

@@ -474,10 +474,10 @@ struct KeyDecode {
 // in lower lanes.  A wave's LDS operations execute in issue order, so ranks
 // follow the index order.
 constexpr int kR8Waves = 8;
-constexpr int kR8Chunks = 16;
-constexpr int64_t kR8Tile = kR8Waves * kR8Chunks * kWave;  // 8192 keys
+constexpr int kR8Chunks = 16;  // of the largest tile (see r8_chunks)
+template <int CH>
+constexpr int64_t kR8TileOf = (int64_t)kR8Waves * CH * kWave;
 constexpr int kR8Digits = 256;
-
 
 // Lanes holding the same 8-bit digit as this lane, when every lane of the
 // wave holds a key: the AND over the digit bits of that bit's ballot,
@@ -510,17 +510,6 @@ __device__ __forceinline__ uint64_t peers8_all(uint32_t d) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-// The same among the `ok` lanes (a ragged tile).
-__device__ __forceinline__ uint64_t peers8(uint32_t d, bool ok) {
-    uint64_t m = __ballot(ok);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        const uint64_t bb = __ballot(ok && ((d >> b) & 1u));
-        m &= ((d >> b) & 1u) ? bb : ~bb;
-    }
-    return m;
-}
-
 // Per-tile counts of the 256 digits.  Keys form rows of `len` (one row of n
 // for a 1-D sort; tiles never straddle rows, tpr tiles per row), and the count
 // of digit d in tile tr of row r goes to counts[(r * 256 + d) * tpr + tr]: per
@@ -530,10 +519,11 @@ __device__ __forceinline__ uint64_t peers8(uint32_t d, bool ok) {
 // with plain LDS atomics, into 4 histograms per wave (picked by lane & 3) so
 // that equal digits in one instruction collide at most 16 ways.
 constexpr int kR8Sub = 4;
-template <class K>
+template <class K, int CH>
 __global__ __launch_bounds__(kR8Waves* kWave) LS_OCCUPANCY4 void k_radix8_count(
     const K* keys, int64_t len, uint32_t tpr, int shift, bool vec, uint32_t* counts,
     KeyCode code) {
+    constexpr int64_t kTile = kR8TileOf<CH>;
     __shared__ uint32_t s_h[kR8Waves * kR8Sub][kR8Digits];
     const int lane = lane_id();
     const int w = threadIdx.x / kWave;
@@ -543,23 +533,24 @@ __global__ __launch_bounds__(kR8Waves* kWave) LS_OCCUPANCY4 void k_radix8_count(
     // block index they went to HBM as 8x the table's bytes)
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
     const uint32_t row = tile / tpr, tr = tile - row * tpr;
-    const int64_t tstart = (int64_t)tr * kR8Tile;  // within the row
+    const int64_t tstart = (int64_t)tr * kTile;  // within the row
     const K* kr = keys + (int64_t)row * len;
-    const int64_t wbase = tstart + (int64_t)w * kR8Chunks * kWave;
-    const bool fast = vec && tstart + kR8Tile <= len;
+    const int64_t wbase = tstart + (int64_t)w * CH * kWave;
+    // small tiles of 16-bit keys: a wave's keys do not fill a 16-byte load per lane
+    const bool fast = CH % (16 / (int)sizeof(K)) == 0 && vec && tstart + kTile <= len;
     // The key loads first: clearing the histograms runs under their latency.
     // Fast path: 16-byte loads, 4 of 32-bit keys or 8 of 16-bit keys each.
     constexpr int kPer = 16 / (int)sizeof(K);
-    constexpr int kLoads = kR8Chunks / kPer;
+    constexpr int kLoads = CH >= kPer ? CH / kPer : 1;
     u32x4 v[kLoads];
-    uint32_t k[kR8Chunks];
+    uint32_t k[CH];
     if (fast) {
         const u32x4* k4 = reinterpret_cast<const u32x4*>(kr + wbase);
 #pragma unroll
         for (int j = 0; j < kLoads; ++j) v[j] = k4[j * kWave + lane];
     } else {
 #pragma unroll
-        for (int j = 0; j < kR8Chunks; ++j) {
+        for (int j = 0; j < CH; ++j) {
             const int64_t i = wbase + j * kWave + lane;
             k[j] = i < len ? (uint32_t)kr[i] : 0u;
         }
@@ -587,7 +578,7 @@ __global__ __launch_bounds__(kR8Waves* kWave) LS_OCCUPANCY4 void k_radix8_count(
                 }
         } else {
 #pragma unroll
-            for (int j = 0; j < kR8Chunks; ++j)
+            for (int j = 0; j < CH; ++j)
                 if (wbase + j * kWave + lane < len) atomicAdd(&h[(enc(k[j]) >> shift) & 255u], 1u);
         }
     };
@@ -604,32 +595,33 @@ __global__ __launch_bounds__(kR8Waves* kWave) LS_OCCUPANCY4 void k_radix8_count(
     }
 }
 
-// Rank and scatter one tile of 8192 keys (one key per lane per chunk, so the
+// Rank and scatter one tile of 8 x CH x 64 keys (one key per lane per chunk, so the
 // chunk's index order is the lane order) with the offsets from the scanned
 // table; rows and tiles as in k_radix8_count, the permutation holding indices
 // within the row.
-template <class K, bool HAS_PERM_IN, bool WITH_PERM>
+template <class K, int CH, bool HAS_PERM_IN, bool WITH_PERM>
 __global__ __launch_bounds__(kR8Waves* kWave) LS_OCCUPANCY4 void k_radix8_scatter(
     const K* keys_in, const int32_t* perm_in, K* keys_out, int32_t* perm_out, int64_t len,
     uint32_t tpr, int shift, uint32_t* offsets, KeyCode code, KeyDecode decode) {
+    constexpr int64_t kTile = kR8TileOf<CH>;
     // per-wave digit counts during ranking, then each wave's first slot per digit
     __shared__ uint32_t s_wh[kR8Waves][kR8Digits];
     __shared__ uint32_t s_off[kR8Digits];  // global row position minus tile slot, per digit
     __shared__ uint32_t s_part[kR8Digits / kWave];
-    __shared__ uint32_t s_stage[kR8Tile];
+    __shared__ uint32_t s_stage[kTile];
     // the tile's source indices, loaded straight into LDS at the start (in
     // the tile's index order) so that they arrive while the keys are ranked
-    __shared__ int32_t s_pin[WITH_PERM && HAS_PERM_IN ? kR8Tile : 1];
+    __shared__ int32_t s_pin[WITH_PERM && HAS_PERM_IN ? kTile : 1];
 
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
     const int lane = lane_id();
     const int w = threadIdx.x / kWave;
     const uint32_t row = tile / tpr, tr = tile - row * tpr;
     const int64_t rbase = (int64_t)row * len;
-    const int64_t tstart = (int64_t)tr * kR8Tile;  // within the row
-    const int64_t wbase = tstart + (int64_t)w * kR8Chunks * kWave;
-    const bool full = tstart + kR8Tile <= len;
-    const uint32_t valid = full ? (uint32_t)kR8Tile : (uint32_t)(len - tstart);
+    const int64_t tstart = (int64_t)tr * kTile;  // within the row
+    const int64_t wbase = tstart + (int64_t)w * CH * kWave;
+    const bool full = tstart + kTile <= len;
+    const uint32_t valid = full ? (uint32_t)kTile : (uint32_t)(len - tstart);
     const K* kw = keys_in + rbase + wbase;  // this wave's keys
     K* kout = keys_out + rbase;
 
@@ -653,28 +645,34 @@ __global__ __launch_bounds__(kR8Waves* kWave) LS_OCCUPANCY4 void k_radix8_scatte
         // nothing and their slots are never read.
         if (WITH_PERM && HAS_PERM_IN) {
             const int32_t* pw = perm_in + rbase + wbase;
-            int32_t* lw = s_pin + w * kR8Chunks * kWave;
+            int32_t* lw = s_pin + w * CH * kWave;
             if (FULL) {
                 // one address pair: the immediate offset moves both sides
-                indices_to_lds(pw + lane, lw, std::make_integer_sequence<int, kR8Chunks>{});
+                indices_to_lds(pw + lane, lw, std::make_integer_sequence<int, CH>{});
             } else {
 #pragma unroll
-                for (int j = 0; j < kR8Chunks; ++j)
+                for (int j = 0; j < CH; ++j)
                     if (in_range(j))
                         __builtin_amdgcn_global_load_lds((const void*)(pw + j * kWave + lane),
                                                          lw + j * kWave, 4, 0, 0);
             }
         }
         // All key loads, then the encoding: applied inside a per-key branch
-        // it would make each load wait for the one before.  (Lanes past the
-        // end get a code of 0; they are masked out everywhere below.)
-        uint32_t key[kR8Chunks];
+        // it would make each load wait for the one before.
+        uint32_t key[CH];
 #pragma unroll
-        for (int j = 0; j < kR8Chunks; ++j)
+        for (int j = 0; j < CH; ++j)
             key[j] = in_range(j) ? (uint32_t)__builtin_nontemporal_load(&kw[j * kWave + lane]) : 0u;
         if (code.pos | code.neg) {  // only the first pass of signed or float keys
 #pragma unroll
-            for (int j = 0; j < kR8Chunks; ++j) key[j] = code.apply(key[j]);
+            for (int j = 0; j < CH; ++j) key[j] = code.apply(key[j]);
+        }
+        // Places past the row's end take the largest code: ranked after every
+        // key, in slots past the valid ones, they need no mask until the stores.
+        if (!FULL) {
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+                if (!in_range(j)) key[j] = 0xFFFFFFFFu;
         }
         __syncthreads();
 
@@ -684,14 +682,14 @@ __global__ __launch_bounds__(kR8Waves* kWave) LS_OCCUPANCY4 void k_radix8_scatte
         // wave's operations in issue order, so the read sees this chunk's
         // add and no later one, and the key's rank is the count before the
         // group plus its peers in lower lanes.  No chunk waits on another.
-        uint32_t rank[kR8Chunks];
+        uint32_t rank[CH];
 #pragma unroll
-        for (int j = 0; j < kR8Chunks; ++j) {
+        for (int j = 0; j < CH; ++j) {
             const uint32_t d = (key[j] >> shift) & 255u;
-            const uint64_t peers = FULL ? peers8_all(d) : peers8(d, in_range(j));
+            const uint64_t peers = peers8_all(d);
             const uint32_t below = lanes_below(peers);
             const uint32_t size = (uint32_t)__builtin_popcountll(peers);
-            if (in_range(j) && below == 0) atomicAdd(&s_wh[w][d], size);
+            if (below == 0) atomicAdd(&s_wh[w][d], size);
             rank[j] = s_wh[w][d] - size + below;
         }
         // the index loads were issued first: long done, and no stores yet
@@ -728,9 +726,9 @@ __global__ __launch_bounds__(kR8Waves* kWave) LS_OCCUPANCY4 void k_radix8_scatte
         // Sort the tile by digit in LDS, then write it out with consecutive
         // threads (each digit's keys form one contiguous output run).
 #pragma unroll
-        for (int j = 0; j < kR8Chunks; ++j) {
+        for (int j = 0; j < CH; ++j) {
             rank[j] += s_wh[w][(key[j] >> shift) & 255u];  // now the slot
-            if (FULL || (in_range(j) && rank[j] < kR8Tile)) s_stage[rank[j]] = key[j];
+            if (FULL || rank[j] < kTile) s_stage[rank[j]] = key[j];
         }
         __syncthreads();
         // All staged keys, then their positions, then the stores: every LDS
@@ -738,35 +736,35 @@ __global__ __launch_bounds__(kR8Waves* kWave) LS_OCCUPANCY4 void k_radix8_scatte
         // the row (it is inside always; the clamp keeps a corrupted offsets
         // table from writing out of bounds).
         const uint32_t last = (uint32_t)(len - 1);  // len <= INT32_MAX
-        uint32_t sk[kR8Chunks], pos[kR8Chunks];
+        uint32_t sk[CH], pos[CH];
 #pragma unroll
-        for (int j = 0; j < kR8Chunks; ++j) sk[j] = s_stage[threadIdx.x + j * kR8Waves * kWave];
+        for (int j = 0; j < CH; ++j) sk[j] = s_stage[threadIdx.x + j * kR8Waves * kWave];
 #pragma unroll
-        for (int j = 0; j < kR8Chunks; ++j) {
+        for (int j = 0; j < CH; ++j) {
             const uint32_t t = (uint32_t)threadIdx.x + j * kR8Waves * kWave;
             pos[j] = min(s_off[(sk[j] >> shift) & 255u] + t, last);
         }
         if (decode.pre | decode.one | decode.zero) {  // only the last pass of signed or float keys
 #pragma unroll
-            for (int j = 0; j < kR8Chunks; ++j) sk[j] = decode.apply(sk[j]);
+            for (int j = 0; j < CH; ++j) sk[j] = decode.apply(sk[j]);
         }
 #pragma unroll
-        for (int j = 0; j < kR8Chunks; ++j)
+        for (int j = 0; j < CH; ++j)
             if (FULL || threadIdx.x + j * kR8Waves * kWave < valid) kout[pos[j]] = (K)sk[j];
         if (WITH_PERM) {
             __syncthreads();
 #pragma unroll
-            for (int j = 0; j < kR8Chunks; ++j) {
-                const int32_t pv = HAS_PERM_IN ? s_pin[(w * kR8Chunks + j) * kWave + lane]
+            for (int j = 0; j < CH; ++j) {
+                const int32_t pv = HAS_PERM_IN ? s_pin[(w * CH + j) * kWave + lane]
                                                : (int32_t)(wbase + j * kWave + lane);
-                if (FULL || (in_range(j) && rank[j] < kR8Tile)) s_stage[rank[j]] = (uint32_t)pv;
+                if (FULL || rank[j] < kTile) s_stage[rank[j]] = (uint32_t)pv;
             }
             __syncthreads();
             int32_t* pout = perm_out + rbase;
 #pragma unroll
-            for (int j = 0; j < kR8Chunks; ++j) sk[j] = s_stage[threadIdx.x + j * kR8Waves * kWave];
+            for (int j = 0; j < CH; ++j) sk[j] = s_stage[threadIdx.x + j * kR8Waves * kWave];
 #pragma unroll
-            for (int j = 0; j < kR8Chunks; ++j)
+            for (int j = 0; j < CH; ++j)
                 if (FULL || threadIdx.x + j * kR8Waves * kWave < valid) pout[pos[j]] = (int32_t)sk[j];
         }
     };
@@ -940,11 +938,18 @@ constexpr KeyDecode kIdentityDecode{0u, 0u, 0u, 31};
 // for 16-bit), ping-ponging keys_tmp / keys_out (an even number of passes ends
 // in keys_out); the first pass encodes the keys, the last one decodes them.
 // Workspace: header | the table scan's workspace body | the count table.
-static uint32_t r8_tpr(int64_t len) { return (uint32_t)((len + kR8Tile - 1) / kR8Tile); }
-static size_t radix8_table_offset(int64_t rows, int64_t len) {
-    const int64_t entries = (int64_t)kR8Digits * r8_tpr(len);
+static uint32_t r8_tpr(int64_t len, int chunks = kR8Chunks) {
+    const int64_t tile = (int64_t)kR8Waves * chunks * kWave;
+    return (uint32_t)((len + tile - 1) / tile);
+}
+static size_t radix8_table_offset(int64_t rows, int64_t len, int chunks) {
+    const int64_t entries = (int64_t)kR8Digits * r8_tpr(len, chunks);
     const size_t scan = rows == 1 ? scan1d_ws_bytes(entries) : scan_rows_ws_bytes(rows, entries);
     return (scan + 15) / 16 * 16;
+}
+static size_t radix8_ws_bytes(int64_t rows, int64_t len, int chunks) {
+    return radix8_table_offset(rows, len, chunks) +
+           (size_t)rows * kR8Digits * r8_tpr(len, chunks) * sizeof(uint32_t);
 }
 // rows x len keys within kMaxRadixKeys and a tile grid that fits one launch
 // (the count table's row scan then fits its limits too).
@@ -955,24 +960,39 @@ bool radix_rows_fit(int64_t rows, int64_t len) {
     return rows * (int64_t)r8_tpr(len) <= kMaxGridTiles;
 }
 size_t radix_rows_ws_bytes(int64_t rows, int64_t len) {
-    return radix8_table_offset(rows, len) +
-           (size_t)rows * kR8Digits * r8_tpr(len) * sizeof(uint32_t);
+    return radix8_ws_bytes(rows, len, kR8Chunks);
+}
+// Chunks per wave of the tiles. A pass over few keys is latency: a wave takes
+// its chunks one after another, and 2^20 keys are only 128 tiles of 8192 on 256
+// CUs, so smaller tiles end sooner; over many keys a larger tile writes longer
+// runs per digit and leaves a shorter table to scan. Sort with its permutation,
+// us at tiles of 8192 / 4096 / 2048 keys:
+//   u32   20000: 63 / 51 / 46     2^18: 64 / 54 / 50     2^20: 79 / 70 / 69
+//         2^21:  88 / 84 / 91   3 2^20: 100 / 90 / 104   2^22: 102 / 108 / 121
+//   f16   2^18:  31 / 27 / 26     2^20: 36 / 33 / 32   3 2^20: 51 / 47 / 52
+//         2^22:  52 / 54 / 58     2^23: 73 / 76 / 88
+// Rows follow their total: 4 x 200003 71 / 66 / 68, 30 x 32000 70 / 56 / 52,
+// 64 x 65536 96 / 91 / 105, 32 x 131072 93 / 94 / 109.
+static int r8_chunks(int64_t rows, int64_t len) {
+    const int64_t n = rows * len;
+    return n >= int64_t(1) << 22 ? 16 : (n > int64_t(3) << 19 ? 8 : 4);
+}
+size_t radix_rows_ws_want(int64_t rows, int64_t len) {
+    const size_t a = radix_rows_ws_bytes(rows, len);
+    if (rows == 0 || len <= kR8RowMax) return a;
+    const size_t b = radix8_ws_bytes(rows, len, r8_chunks(rows, len));
+    return a > b ? a : b;
 }
 
-template <class K>
-static hipError_t radix8_sort(const K* keys, K* keys_out, const int32_t* perm_in,
-                              int32_t* perm_out, K* keys_tmp,
-                              int32_t* perm_tmp, int64_t rows, int64_t len, int passes,
-                              KeyCode code, KeyDecode decode, void* ws, hipStream_t stream) {
-    if (len <= kR8RowMax) {
-        radix8_rows<K>(keys, keys_out, perm_out ? perm_in : nullptr, perm_out, rows, len, passes,
-                       code, decode, stream);
-        return hipGetLastError();
-    }
-    const uint32_t tpr = r8_tpr(len);
+template <class K, int CH>
+static hipError_t radix8_tiles(const K* keys, K* keys_out, const int32_t* perm_in,
+                               int32_t* perm_out, K* keys_tmp, int32_t* perm_tmp, int64_t rows,
+                               int64_t len, int passes, KeyCode code, KeyDecode decode, void* ws,
+                               hipStream_t stream) {
+    const uint32_t tpr = r8_tpr(len, CH);
     const uint32_t nt = (uint32_t)(rows * tpr);
     const int64_t entries = (int64_t)kR8Digits * tpr;  // per row
-    const size_t toff = radix8_table_offset(rows, len);
+    const size_t toff = radix8_table_offset(rows, len, CH);
     uint32_t* counts = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(ws) + toff);
     const K* src_k = keys;
     const int32_t* src_p = perm_out ? perm_in : nullptr;
@@ -984,16 +1004,17 @@ static hipError_t radix8_sort(const K* keys, K* keys_out, const int32_t* perm_in
         // 16-byte loads need every row start 16-byte aligned
         const bool vec = ((uintptr_t)src_k % 16) == 0 &&
                          (rows == 1 || ((size_t)len * sizeof(K)) % 16 == 0);
-        hipLaunchKernelGGL(k_radix8_count<K>, dim3(nt), dim3(kR8Waves * kWave), 0, stream, src_k,
-                           len, tpr, 8 * p, vec, counts, c);
+        hipLaunchKernelGGL((k_radix8_count<K, CH>), dim3(nt), dim3(kR8Waves * kWave), 0, stream,
+                           src_k, len, tpr, 8 * p, vec, counts, c);
         hipError_t e = rows == 1
                            ? launch_scan1d(Kind::I32, true, counts, counts, entries, nullptr,
                                            nullptr, ws, toff, stream)
                            : launch_scan_rows(Kind::I32, true, counts, counts, rows, entries, ws,
                                               toff, stream);
         if (e != hipSuccess) return e;
-        auto k = dp ? (src_p ? k_radix8_scatter<K, true, true> : k_radix8_scatter<K, false, true>)
-                    : k_radix8_scatter<K, false, false>;
+        auto k = dp ? (src_p ? k_radix8_scatter<K, CH, true, true>
+                             : k_radix8_scatter<K, CH, false, true>)
+                    : k_radix8_scatter<K, CH, false, false>;
         hipLaunchKernelGGL(k, dim3(nt), dim3(kR8Waves * kWave), 0, stream, src_k, src_p, dk, dp,
                            len, tpr, 8 * p, counts, c, d);
         e = hipGetLastError();
@@ -1002,6 +1023,23 @@ static hipError_t radix8_sort(const K* keys, K* keys_out, const int32_t* perm_in
         src_p = dp;
     }
     return hipSuccess;
+}
+
+template <class K>
+static hipError_t radix8_sort(const K* keys, K* keys_out, const int32_t* perm_in,
+                              int32_t* perm_out, K* keys_tmp, int32_t* perm_tmp, int64_t rows,
+                              int64_t len, int passes, KeyCode code, KeyDecode decode, void* ws,
+                              size_t ws_bytes, hipStream_t stream) {
+    if (len <= kR8RowMax) {
+        radix8_rows<K>(keys, keys_out, perm_out ? perm_in : nullptr, perm_out, rows, len, passes,
+                       code, decode, stream);
+        return hipGetLastError();
+    }
+    int ch = r8_chunks(rows, len);
+    if (radix8_ws_bytes(rows, len, ch) > ws_bytes) ch = kR8Chunks;  // a workspace of the least size
+    auto go = ch == 4 ? radix8_tiles<K, 4> : (ch == 8 ? radix8_tiles<K, 8> : radix8_tiles<K, 16>);
+    return go(keys, keys_out, perm_in, perm_out, keys_tmp, perm_tmp, rows, len, passes, code,
+              decode, ws, stream);
 }
 
 hipError_t launch_radix_sort(const uint32_t* keys, uint32_t* keys_out, int32_t* perm_out,
@@ -1046,7 +1084,8 @@ hipError_t launch_radix_sort(const uint32_t* keys, uint32_t* keys_out, int32_t* 
             if (e != hipSuccess) return e;
         } else {
             return radix8_sort<uint32_t>(keys, keys_out, nullptr, perm_out, keys_tmp, perm_tmp, 1,
-                                         n, 4, kIdentityCode, kIdentityDecode, ws, stream);
+                                         n, 4, kIdentityCode, kIdentityDecode, ws, ws_bytes,
+                                         stream);
         }
         src_k = dk;
         src_p = dp;
@@ -1059,7 +1098,6 @@ hipError_t launch_radix_sort_typed(KeyType type, bool descending, const void* ke
                                    void* keys_tmp,
                                    int32_t* perm_tmp, int64_t rows, int64_t len, void* ws,
                                    size_t ws_bytes, hipStream_t stream) {
-    (void)ws_bytes;
     if (rows == 0 || len == 0) return hipSuccess;
     const bool wide = type != KeyType::F16;
     const uint32_t all = wide ? 0xFFFFFFFFu : 0xFFFFu;
@@ -1090,10 +1128,10 @@ hipError_t launch_radix_sort_typed(KeyType type, bool descending, const void* ke
     if (wide)
         return radix8_sort<uint32_t>((const uint32_t*)keys, (uint32_t*)keys_out, perm_in, perm_out,
                                      (uint32_t*)keys_tmp, perm_tmp, rows, len, 4, code, decode, ws,
-                                     stream);
+                                     ws_bytes, stream);
     return radix8_sort<uint16_t>((const uint16_t*)keys, (uint16_t*)keys_out, perm_in, perm_out,
                                  (uint16_t*)keys_tmp, perm_tmp, rows, len, 2, code, decode, ws,
-                                 stream);
+                                 ws_bytes, stream);
 }
 
 }  // namespace ls

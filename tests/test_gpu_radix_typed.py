@@ -168,3 +168,41 @@ def test_one_workgroup_rows(ops, n, desc):
     order = np.argsort(-code if desc else code, kind="stable")
     assert_equal_first_diff(to_host(po), order.astype(np.int32), f"f16 perm {n}")
     assert torch.equal(ko.cpu().view(torch.int16), torch.from_numpy(h[order]).view(torch.int16))
+
+
+@pytest.mark.parametrize("n", [16_385, 18_432, 65_537, 3 << 19, (3 << 19) + 1, (1 << 22) - 1,
+                               1 << 22])
+@pytest.mark.parametrize("least", [False, True])
+def test_tile_choice(ops, n, least):
+    """Sorts of more than 16384 keys take tiles of 2048, 4096 or 8192 keys by
+    their size, and 8192 whatever the size in a workspace that has no room for
+    the longer count table: both sides of each line, on one workspace."""
+    import torch
+    from paper_2505_15112_amd import _lib
+    announce("tile choice", n, least)
+    rng = np.random.default_rng(n)
+    want = _lib.workspace_bytes(_lib.OP_RADIX_SORT, n, bits=8)
+    if least:  # tiles of 8192 keys: 256 counts each, and the scan of that table
+        entries = 256 * -(-n // 8192)
+        want = (_lib.workspace_bytes(_lib.OP_SCAN, entries) + 15) // 16 * 16 + 4 * entries
+    ws = torch.zeros((want + 7) // 8 * 8, dtype=torch.uint8, device="cuda")[:want]
+    k = rng.integers(-2**31, 2**31, n, dtype=np.int64).astype(np.int32)
+    ko, po = ops.radix_sort_i32(to_dev(k), ws=ws)
+    order = np.argsort(k, kind="stable")
+    assert_equal_first_diff(to_host(po), order.astype(np.int32), f"i32 perm {n}")
+    assert_equal_first_diff(to_host(ko), k[order], f"i32 keys {n}")
+    only, _ = ops.radix_sort_i32(to_dev(k), descending=True, with_perm=False, ws=ws)
+    assert_equal_first_diff(to_host(only), k[order][::-1], f"i32 keys only {n}")
+    h = rng.integers(-9, 10, n).astype(np.float16)  # many ties
+    ko, po = ops.radix_sort_f16(to_dev(h), descending=True, ws=ws)
+    b = h.view(np.uint16).astype(np.int64)
+    order = np.argsort(-np.where(b >= 0x8000, 0xFFFF - b, b + 0x8000), kind="stable")
+    assert_equal_first_diff(to_host(po), order.astype(np.int32), f"f16 perm {n}")
+    assert torch.equal(ko.cpu().view(torch.int16), torch.from_numpy(h[order]).view(torch.int16))
+    # rows that share the total, their ends inside a tile
+    rows = 3 if n > 65_537 else 1
+    f = rng.integers(-9, 10, (rows, n // rows)).astype(np.float32)
+    ko, po = ops.radix_sort_rows_f32(to_dev(f), descending=True)
+    rk, rp = oracle.sort_rows_f32(f, descending=True)
+    assert_equal_first_diff(to_host(po), rp, f"row perm {n}")
+    assert_equal_first_diff(to_host(ko).view(np.uint32), rk.view(np.uint32), f"row keys {n}")
