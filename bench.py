@@ -503,11 +503,11 @@ def main():
             ms = T.flushed(scan_call("scan_inclusive_f16f32", x16, y16, n2), K, Wm)
             opsd["scan_f16f32_n2^24"] = entry("f16", ms, b2, memcpy_ms(b2, True),
                                               "n*(2+4), cache-flushed; the default dispatch "
-                                              "(wavefront tiles below n = 2^27)")
+                                              "(wavefront tiles)")
             outputs["f16"] = (x16_host, y16)
             # the same scan with its whole 32768-element tiles on the matrix
-            # cores, cold at 2^24, and both forms back to back at 2^28 (where
-            # the default takes the matrix cores)
+            # cores, cold at 2^24, and the default and the wavefront entry
+            # point (the same kernel) back to back at 2^28
             y16m = torch.empty_like(y16)
             ms = T.flushed(scan_call("scan_inclusive_f16f32_mfma", x16, y16m, n2), K, Wm)
             opsd["scan_f16f32_mfma_n2^24"] = entry("f16 mfma", ms, b2, memcpy_ms(b2, True),

@@ -120,9 +120,8 @@ int scan_exclusive_f32(const float* x, float* y, int64_t n, void* ws, size_t ws_
 
 /* fp16 input (IEEE binary16 bit patterns), fp32 accumulation and output
  * (Section 3.1: the cube takes fp16 in and gives fp32 out; Section 6 scans
- * fp16).  x and y may not overlap.  The inclusive scan of a 16-byte aligned
- * x with n >= 2^27 takes its tile-local scans on the matrix cores (see
- * scan_inclusive_f16f32_mfma), otherwise the wavefront tiles. */
+ * fp16).  x and y may not overlap.  Both run on the wavefront tiles (the
+ * matrix-core form is scan_inclusive_f16f32_mfma). */
 int scan_inclusive_f16f32(const uint16_t* x, float* y, int64_t n, void* ws, size_t ws_bytes,
                           void* stream);
 int scan_exclusive_f16f32(const uint16_t* x, float* y, int64_t n, void* ws, size_t ws_bytes,
@@ -138,17 +137,17 @@ int scan_exclusive_f16f32(const uint16_t* x, float* y, int64_t n, void* ws, size
  * and y 4-byte aligned, else LIBSCAN_EINVAL; x and y may not overlap.  Whole
  * 32768-element tiles take the matrix-core kernel, a shorter tail the
  * wavefront one.  Results agree with the wavefront scan within the float
- * tolerance (exactly on {-1, 0, 1} inputs); measured faster than it from
- * n = 2^27 on (slower below), which is why scan_inclusive_f16f32 uses this
- * path for such arrays.  A tile holding
- * an infinity or a NaN is scanned on the vector units instead (in the
+ * tolerance (exactly on {-1, 0, 1} inputs).  Measured slower than the
+ * wavefront tiles (171 against 158 us at n = 2^27, 340 against 309 at 2^28), so
+ * scan_inclusive_f16f32 does not use it; kept as the paper's form.  A tile
+ * holding an infinity or a NaN is scanned on the vector units instead (in the
  * product it would meet the zeros of U_32, and inf * 0 is NaN). */
 int scan_inclusive_f16f32_mfma(const uint16_t* x, float* y, int64_t n, void* ws,
                                size_t ws_bytes, void* stream);
 
 /* The inclusive fp16 -> fp32 scan on the wavefront tiles only (lane-serial,
- * DPP and LDS tile scan), whatever n and the alignment: the baseline the
- * matrix-core path is measured against.  Arguments and errors as
+ * DPP and LDS tile scan), which is what scan_inclusive_f16f32 runs: the
+ * baseline the matrix-core path is measured against.  Arguments and errors as
  * scan_inclusive_f16f32. */
 int scan_inclusive_f16f32_wave(const uint16_t* x, float* y, int64_t n, void* ws,
                                size_t ws_bytes, void* stream);

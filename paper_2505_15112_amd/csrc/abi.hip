@@ -160,7 +160,7 @@ int scan_u8_variant(bool mfma, const uint8_t* x, int32_t* y, int64_t n, int32_t*
     if (mfma && n > 0)
         return hip_status(ls::launch_scan1d_mfma_u8(x, (uint32_t*)y, n, (uint32_t*)total_dev, ws,
                                                     ws_bytes, s));
-    return hip_status(ls::launch_scan1d_tiles(Kind::U8I32, true, x, y, n, nullptr, total_dev, ws,
+    return hip_status(ls::launch_scan1d(Kind::U8I32, true, x, y, n, nullptr, total_dev, ws,
                                               ws_bytes, s));
 }
 
@@ -290,7 +290,7 @@ int scan_inclusive_f16f32_wave(const uint16_t* x, float* y, int64_t n, void* ws,
     if (n == 0) return LIBSCAN_OK;
     const int w = check_ws(ws, ws_bytes, ls::scan1d_ws_bytes(n));
     if (w != LIBSCAN_OK) return w;
-    return hip_status(ls::launch_scan1d_tiles(Kind::F16F32, false, x, y, n, nullptr, nullptr, ws,
+    return hip_status(ls::launch_scan1d(Kind::F16F32, false, x, y, n, nullptr, nullptr, ws,
                                               ws_bytes, (hipStream_t)stream));
 }
 

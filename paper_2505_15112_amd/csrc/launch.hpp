@@ -21,16 +21,11 @@ hipError_t launch_workspace_init(void* ws, size_t ws_bytes, hipStream_t stream);
 // Copy the workspace's error word into *out (device int32), clearing it if reset.
 hipError_t launch_workspace_error(void* ws, int32_t* out, bool reset, hipStream_t stream);
 
-// 1-D decoupled look-back scan: launch_scan1d picks the kernel (the
-// matrix-core one for inclusive fp16 scans of at least one whole tile),
-// launch_scan1d_tiles always the wavefront tiles.
+// 1-D decoupled look-back scan on the wavefront tiles.
 size_t scan1d_ws_bytes(int64_t n);
 hipError_t launch_scan1d(Kind kind, bool exclusive, const void* x, void* y, int64_t n,
                          const void* carry_in, void* total_out, void* ws, size_t ws_bytes,
                          hipStream_t stream);
-hipError_t launch_scan1d_tiles(Kind kind, bool exclusive, const void* x, void* y, int64_t n,
-                               const void* carry_in, void* total_out, void* ws, size_t ws_bytes,
-                               hipStream_t stream);
 
 // 1-D inclusive scan of fp16 with the tile-local row scans on the matrix
 // cores (ScanU) on whole tiles of kMfmaTileElems, the tail on the wavefront

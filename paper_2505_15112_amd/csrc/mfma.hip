@@ -349,7 +349,7 @@ hipError_t launch_scan1d_mfma_u8(const uint8_t* x, uint32_t* y, int64_t n, uint3
                            stream, x, y, hdr, status, status_words, (uint32_t)full,
                            done < n ? carry : total_out);
     if (done < n)
-        return launch_scan1d_tiles(Kind::U8I32, true, x + done, y + done, n - done,
+        return launch_scan1d(Kind::U8I32, true, x + done, y + done, n - done,
                                    full > 0 ? carry : nullptr, total_out, ws, ws_bytes, stream);
     return hipGetLastError();
 }
@@ -368,7 +368,7 @@ hipError_t launch_scan1d_mfma_f16(const uint16_t* x, float* y, int64_t n, void* 
                            stream, x, y, hdr, status, status_words, (uint32_t)full,
                            done < n ? carry : nullptr);
     if (done < n)
-        return launch_scan1d_tiles(Kind::F16F32, false, x + done, y + done, n - done,
+        return launch_scan1d(Kind::F16F32, false, x + done, y + done, n - done,
                                    full > 0 ? carry : nullptr, nullptr, ws, ws_bytes, stream);
     return hipGetLastError();
 }

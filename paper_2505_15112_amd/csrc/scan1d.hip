@@ -18,31 +18,33 @@
 namespace ls {
 
 // Tile geometries (waves x chunks x 64 lanes x 4 elements).  Every tile costs
-// one ticket and one look-back, so big arrays want big tiles: measured on
-// MI355X at n = 2^28, 4096-element tiles reach half the device memcpy rate
-// and 32768-element tiles match it.  A tile's data stays in registers from
-// its loads until its stores, so the bytes in flight per CU are set by how
-// much of the register file holds data: the large integer tile keeps 80 of
-// at most 128 VGPRs per lane as data (16 waves per CU); the
-// float scans need more scratch registers and keep 64.  Small arrays want
-// more, smaller tiles to occupy the 256 CUs.  Between 2^22 and 2^27 integer
-// elements the 32768-element tile is faster than the 40960-element one
-// (measured cold: 7.4 against 14.3 us at 2^22, 119 against 138 us at 2^26:
-// the larger tile leaves CUs without a tile at the small end, and its fewer
-// tiles fill the last round of workgroups unevenly).
+// one ticket and one look-back, so big arrays want big tiles, and a tile's data
+// stays in registers from its loads until its stores, so the bytes in flight per
+// CU are set by how much of the register file holds data: 64 of at most 128
+// VGPRs per lane, 16 waves per CU.  One workgroup of 16 waves per CU holds what
+// two of 8 waves do with half the tickets and look-back steps; in small tiles
+// 16 waves of few chunks end sooner than 4 waves of many (a wave scans its
+// chunks one after another).  Measured, tiles of 16384 (n < 2^22) and 32768
+// elements in 4 and 8 waves before, and now, us: int32 2^21 8.0 -> 7.0,
+// 3 2^20 9.4 -> 8.4, 2^22 9.8 -> 9.3, 2^23 15.3 -> 14.1, 2^24 30.2 -> 25.1; fp16
+// 2^22 9.1 -> 8.8, 2^24 25.4 -> 20.2 (5 TB/s), 2^26 91.6 -> 79.0, 2^28 (exclusive)
+// 348 -> 307; bytes 2^24 22.6 -> 18.8, 2^28 282 -> 249.  Lines between them, at
+// 32768 / 65536 elements: int32 3 2^21 11.4 / 11.7, 2^23 14.8 / 14.1.
+// Misaligned data of less than 32 bits is loaded element by element and has no
+// registers for the largest tile (it spills): fp16 2^22 15.9 -> 15.2, 2^24 44.9 ->
+// 37.5, 2^27 322 -> 264; bytes 2^24 38.8 -> 30.8, 2^27 287 -> 247.
 struct GeomSmall { static constexpr int W = 4, J = 4; };   //  4096 elements
-struct GeomMid { static constexpr int W = 4, J = 16; };    // 16384 elements
-struct GeomBig { static constexpr int W = 8, J = 16; };    // 32768 elements
-template <class T>
-struct GeomLarge {  // 40960 (integer) / 32768 (float) elements
-    static constexpr int W = 8, J = std::is_same<T, float>::value ? 16 : 20;
-};
-// Misaligned data is loaded element by element: more registers per element,
-// so fewer elements per lane.
-struct GeomUnaligned { static constexpr int W = 8, J = 8; };  // 16384 elements
+struct GeomMid { static constexpr int W = 16, J = 4; };    // 16384 elements
+struct GeomBig { static constexpr int W = 16, J = 8; };    // 32768 elements
+struct GeomLarge { static constexpr int W = 16, J = 16; };  // 65536 elements
+template <class In, class T>
+using GeomLargeAny = typename std::conditional<sizeof(In) == sizeof(T), GeomLarge, GeomBig>::type;
+// Reduce-then-scan: its two tile passes have no look-back to shorten.
+struct GeomRss { static constexpr int W = 4, J = 16; };  // 16384 elements
+struct GeomRssUnaligned { static constexpr int W = 8, J = 8; };
 constexpr int kVec = 4;
 constexpr int64_t kMinTileElems = GeomSmall::W * GeomSmall::J * kWave * kVec;
-constexpr int64_t kRssTileElems = GeomMid::W * GeomMid::J * kWave * kVec;
+constexpr int64_t kRssTileElems = GeomRss::W * GeomRss::J * kWave * kVec;
 
 // Workspaces are sized for the smallest tile, so any geometry fits.
 static inline int64_t num_tiles(int64_t n, int64_t tile) { return (n + tile - 1) / tile; }
@@ -349,24 +351,42 @@ static void scan1d_geom(bool exclusive, const In* x, T* y, int64_t n, const T* c
                        status_words, nt, carry_in, total_out);
 }
 
-// Register + LDS tiles for the largest 32-bit arrays: 114688 (integer) or
-// 102400 (float) elements per tile, one 16-wave workgroup per CU, the most
-// that fits 128 VGPRs per lane without spilling and 160 KB of LDS.
-template <class T>
-struct LdsChunks {
-    static constexpr int J = std::is_same<T, float>::value ? 16 : 19, L = 9, W = 16;
-};
-
-template <class T>
+// Register + LDS tiles of 32-bit arrays beyond 2^24 elements, one 16-wave
+// workgroup per CU: the largest from 2^28 elements on (114688 integer or 102400
+// float elements, the most that fits 128 VGPRs per lane without spilling and
+// 160 KB of LDS), smaller ones below, see lds_chunks.
+template <class T, int J, int L>
 static void scan1d_lds(bool exclusive, const T* x, T* y, int64_t n, const T* carry_in,
                        T* total_out, WsHeader* hdr, uint64_t* status, int64_t status_words,
                        hipStream_t stream) {
-    constexpr int J = LdsChunks<T>::J, L = LdsChunks<T>::L, WV = LdsChunks<T>::W;
+    constexpr int WV = 16;
     using G = LdsGeom<T, J, L, WV>;
     const uint32_t nt = (uint32_t)num_tiles(n, G::kElems);
     auto k = exclusive ? k_scan_lookback_lds<T, J, L, WV, true> : k_scan_lookback_lds<T, J, L, WV, false>;
     hipLaunchKernelGGL(k, dim3(nt), dim3(G::kThreads), 0, stream, x, y, n, hdr, status,
                        status_words, nt, carry_in, total_out);
+}
+// Chunks per wave of the tiles of n < 2^28 32-bit elements.  A few rounds of
+// tiles over the 256 CUs run almost in step, and the part of the last round that
+// is left empty costs about a fifth of a full one; per element held, 20 and 25
+// chunks (fewer tiles) cost 3 and 5 % less than 16, the register tile.  Over more
+// rounds they drift apart and 20 stays ahead.  Measured, us, 16 / 20 / 25 chunks
+// and the 8-wave register tiles before, int32 at n / 2^20 = 20: 33.5 / 31.4 / 32.8,
+// before 37.5; 24: 40 / 45 / 37, 46; 28: 46 / 47 / 55, 54; 40: 69 / 60 / 63, 74; 48:
+// 80 / 80 / 75, 87; 64: 104 / 105 / 99, 113; 70: 116 / 112 / 118, 123; 80: 129 /
+// 123 / 134, 138; 90: 146 / 142 / 147, 153; 120: 196 / 186 / 198, 202; fp32 128:
+// 203 / 209 / 209, 219; 200: 20 chunks 317 (int32) and 319, the largest tile 321
+// and 317; 256: 403 and 408 against 405 and 411.
+static int lds_chunks(int64_t n) {
+    constexpr int64_t kRound = int64_t(256) * 16 * kWave * kVec;  // one chunk per wave, 256 CUs
+    if (n >= 68 * kRound) return 20;
+    auto cost = [n](int64_t chunks, int64_t weight) {
+        const int64_t round = chunks * kRound;
+        return weight * (4 * n + (n + round - 1) / round * round);
+    };
+    const int64_t c16 = cost(16, 100), c20 = cost(20, 97), c25 = cost(25, 95);
+    if (c25 < c16 && c25 < c20) return 25;
+    return c20 <= c16 ? 20 : 16;
 }
 
 template <class In, class T>
@@ -381,51 +401,39 @@ static hipError_t scan1d_typed(bool exclusive, const In* x, T* y, int64_t n, con
     const int64_t status_words = (int64_t)((ws_bytes - kWsHeader) / sizeof(uint64_t));
     // 16-byte vector loads and stores need both arrays 16-byte aligned.
     const bool vec = aligned(x, kVec * sizeof(In)) && aligned(y, kVec * sizeof(T));
-    if (!vec && n >= (int64_t(1) << 18))
-        scan1d_geom<In, T, GeomUnaligned, false>(exclusive, x, y, n, carry_in, total_out, hdr,
-                                                 status, status_words, stream);
-    else if (!vec)
-        scan1d_geom<In, T, GeomSmall, false>(exclusive, x, y, n, carry_in, total_out, hdr, status,
-                                             status_words, stream);
-    else if (n >= (int64_t(1) << 27) && std::is_same<In, T>::value)
-        scan1d_lds<T>(exclusive, reinterpret_cast<const T*>(x), y, n, carry_in, total_out, hdr,
-                      status, status_words, stream);
-    else if (n >= (int64_t(1) << 27))
-        scan1d_geom<In, T, GeomLarge<T>, true>(exclusive, x, y, n, carry_in, total_out, hdr,
-                                               status, status_words, stream);
-    else if (n >= (int64_t(1) << 22))
-        scan1d_geom<In, T, GeomBig, true>(exclusive, x, y, n, carry_in, total_out, hdr, status,
-                                          status_words, stream);
-    else if (n >= (int64_t(1) << 18))
-        scan1d_geom<In, T, GeomMid, true>(exclusive, x, y, n, carry_in, total_out, hdr, status,
-                                          status_words, stream);
-    else
-        scan1d_geom<In, T, GeomSmall, true>(exclusive, x, y, n, carry_in, total_out, hdr, status,
-                                            status_words, stream);
+    constexpr bool kSame = std::is_same<In, T>::value;
+    auto run = [&](auto tiles, auto tiles_any) {
+        (vec ? tiles : tiles_any)(exclusive, x, y, n, carry_in, total_out, hdr, status,
+                                  status_words, stream);
+    };
+    const int chunks = kSame && vec && n > (int64_t(1) << 24) && n < (int64_t(1) << 28)
+                           ? lds_chunks(n)
+                           : (kSame && vec && n >= (int64_t(1) << 28) ? 0 : 16);
+    if (chunks != 16) {
+        constexpr int kJ = std::is_same<T, float>::value ? 16 : 19;
+        auto lds = chunks == 0    ? scan1d_lds<T, kJ, 9>
+                   : chunks == 25 ? scan1d_lds<T, 16, 9>
+                                  : scan1d_lds<T, 16, 4>;
+        lds(exclusive, reinterpret_cast<const T*>(x), y, n, carry_in, total_out, hdr, status,
+            status_words, stream);
+    } else if (n >= (int64_t(1) << 23)) {
+        run(scan1d_geom<In, T, GeomLarge, true>, scan1d_geom<In, T, GeomLargeAny<In, T>, false>);
+    } else if (n >= (int64_t(1) << 22)) {
+        run(scan1d_geom<In, T, GeomBig, true>, scan1d_geom<In, T, GeomBig, false>);
+    } else if (n >= (int64_t(1) << 18)) {
+        run(scan1d_geom<In, T, GeomMid, true>, scan1d_geom<In, T, GeomMid, false>);
+    } else {
+        run(scan1d_geom<In, T, GeomSmall, true>, scan1d_geom<In, T, GeomSmall, false>);
+    }
     return hipGetLastError();
 }
 
+// fp16 and byte scans have matrix-core kernels too (mfma.hip, their own entry
+// points): fp16 inclusive 158 us here against 171 at 2^27 elements, 309 against 340
+// at 2^28; bytes 249 against 251 at 2^28.
 hipError_t launch_scan1d(Kind kind, bool exclusive, const void* x, void* y, int64_t n,
                          const void* carry_in, void* total_out, void* ws, size_t ws_bytes,
                          hipStream_t stream) {
-    // fp16 inclusive scans of 2^27 elements and more run on the matrix cores:
-    // measured against the wavefront tiles in one process (medians of 9
-    // alternating rounds), 337.0 against 346.8 us at n = 2^28, 152.7 against
-    // 153.7 us at 2^27, but slower below (79.0 against 80.1 us at 2^26, 28.9
-    // against 29.6 at 2^24 cold, 10.2 against 11.0 at 2^22 cold).  The byte
-    // scan on the matrix cores measured no faster (251 against 251 us at
-    // 2^28), so byte scans stay on the wavefront tiles.
-    if (kind == Kind::F16F32 && !exclusive && !carry_in && !total_out &&
-        n >= (int64_t(1) << 27) && aligned(x, 16) && aligned(y, 4))
-        return launch_scan1d_mfma_f16(reinterpret_cast<const uint16_t*>(x),
-                                      reinterpret_cast<float*>(y), n, ws, ws_bytes, stream);
-    return launch_scan1d_tiles(kind, exclusive, x, y, n, carry_in, total_out, ws, ws_bytes,
-                               stream);
-}
-
-hipError_t launch_scan1d_tiles(Kind kind, bool exclusive, const void* x, void* y, int64_t n,
-                               const void* carry_in, void* total_out, void* ws, size_t ws_bytes,
-                               hipStream_t stream) {
     switch (kind) {
         case Kind::I32:
             return scan1d_typed<uint32_t, uint32_t>(exclusive, (const uint32_t*)x, (uint32_t*)y, n,
@@ -449,8 +457,8 @@ hipError_t launch_scan1d_tiles(Kind kind, bool exclusive, const void* x, void* y
 
 template <class In, class T>
 static hipError_t rss_typed(const In* x, T* y, int64_t n, void* ws, hipStream_t stream) {
-    using TV = Tile<In, T, kVec, GeomMid::J, GeomMid::W>;
-    using TU = Tile<In, T, kVec, GeomUnaligned::J, GeomUnaligned::W>;  // misaligned data
+    using TV = Tile<In, T, kVec, GeomRss::J, GeomRss::W>;
+    using TU = Tile<In, T, kVec, GeomRssUnaligned::J, GeomRssUnaligned::W>;  // misaligned data
     static_assert(TV::kElems == kRssTileElems && TU::kElems == kRssTileElems, "rss tile");
     if (n == 0) return hipSuccess;
     const int64_t nt = num_tiles(n, kRssTileElems);

@@ -419,3 +419,37 @@ def test_metric_n2_28_f32(ops, seed):
     xe = W.exact_pm1(n, seed=1)
     ye = to_host(ops.scan_inclusive_f32(to_dev(xe)))
     assert_equal_first_diff(ye.astype(np.float64), oracle.scan_f32(xe)[0], "metric f32 exact")
+
+
+@pytest.mark.parametrize("n", [1 << 18, (1 << 22) - 1, 1 << 22, (1 << 23) - 1, 1 << 23,
+                               (1 << 24) + 1, (20 << 20) - 1, (24 << 20) + 7, 28 << 20,
+                               (1 << 26) + 17, (68 << 20) + 3, 1 << 28])
+@pytest.mark.parametrize("off", [0, 1])
+def test_tile_choice(ops, n, off):
+    """Both sides of each line between the tiles of a long scan, aligned and
+    not, on numbers whose sums every format holds exactly: any order of the
+    additions gives the same result."""
+    import torch
+    announce("scan tile choice", n, off)
+    g = torch.Generator(device="cuda").manual_seed(n + off)
+    x = torch.randint(-1, 2, (n + off,), device="cuda", generator=g, dtype=torch.int32)[off:]
+    incl = torch.cumsum(x, 0, dtype=torch.int32)  # |sums| < 2^24 by far: a random walk
+    assert int(incl.abs().max()) < 1 << 24
+    wide = x * 1234567891  # wraps
+    iw = torch.cumsum(wide, 0, dtype=torch.int32)
+    xs = torch.empty(n + off, dtype=torch.int32, device="cuda")[off:].copy_(wide)
+    assert torch.equal(ops.scan_inclusive_i32(xs), iw)
+    assert torch.equal(ops.scan_exclusive_i32(xs), iw - wide)
+    del wide, iw, xs
+    xf = torch.empty(n + off, dtype=torch.float32, device="cuda")[off:].copy_(x)
+    assert torch.equal(ops.scan_inclusive_f32(xf), incl.float())
+    assert torch.equal(ops.scan_exclusive_f32(xf), (incl - x).float())
+    del xf
+    xh = torch.empty(n + off, dtype=torch.float16, device="cuda")[off:].copy_(x)
+    assert torch.equal(ops.scan_inclusive_f16f32(xh), incl.float())
+    assert torch.equal(ops.scan_exclusive_f16f32(xh), (incl - x).float())
+    del xh, incl
+    xb = torch.empty(n + off, dtype=torch.uint8, device="cuda")[off:].copy_(x + 1)
+    yb = ops.scan_exclusive_u8i32(xb)
+    yb = yb[0] if isinstance(yb, tuple) else yb
+    assert torch.equal(yb, torch.cumsum(x + 1, 0, dtype=torch.int32) - (x + 1))
