@@ -328,7 +328,7 @@ int weighted_sample_f32(const float* w, const float* theta_dev, int32_t* out, in
  * NaN.  rows * len <= INT32_MAX, rows * ceil(len / 8192) <= 2^24.
  * scratch: caller device memory, 16-byte aligned, of at least
  * libscan_scratch_bytes(LIBSCAN_OP_TOPP_SAMPLE, rows, len, 0) bytes (16 per
- * element: the sorted copies and the sort's ping-pong buffers).  Unlike the
+ * element: sorted copies, histograms, ping-pong buffers).  Unlike the
  * workspace it needs no initialisation and carries nothing between calls; it
  * is clobbered and may not overlap any input, output or the workspace.
  * Workspace: LIBSCAN_OP_TOPP_SAMPLE with (rows, len). */
