@@ -928,7 +928,9 @@ static void rows_tiles(bool exclusive, const typename TileT::T* x, typename Tile
 // geometry at each shape):
 //   1 x 12000:    look-back 4096  3.3, whole row 3.7;  1 x 20000: 3.7 / 4.3
 //   4 x 32768:    look-back 4096  4.2, whole row 4.0;  64 x 32768: 11.3 / 4.9
-//   8 x 65536:    look-back 8192  5.3, whole row 6.4;  32 x 65536:  8.6 / 6.9
+//   8 x 65536:    look-back 8192  5.3, whole row 6.4;  32 x 65536:  8.6 / 6.9;
+//   rows not in a cache are bound by what one CU can load: 16 x 65536 8.6 / 11.3,
+//   32 x 65536 11.4 / 13.0, 64 x 65536 17.1 / 14.0, so the line is at 32 such rows
 //   8 x 131072:   8192 6.5, 16384 6.4, 32768 7.4
 //   16 x 131072:  8192 8.5, 16384 7.7, 32768 8.2, 65536 10.8
 //   16 x 262144:  16384 10.7, 32768 9.9, 65536 12.1
@@ -942,7 +944,7 @@ static void rows_any(bool exclusive, const T* x, T* y, int64_t rows, int64_t len
     rows_tiles<Tile<T, T, kRVec, C, W>, VEC>(exclusive, x, y, rows, len, ws, ws_bytes, stream)
     const int64_t n = rows * len;
     const bool whole = len <= 8192 || (len <= 32768 && n > (int64_t(1) << 15)) ||
-                       (len <= 65536 && n >= int64_t(1) << 20);
+                       (len <= 65536 && n > int64_t(1) << 21);
     if (len <= kRowTile)
         LS_ROWS(4, 4);
     else if (len <= 8192)
@@ -955,7 +957,7 @@ static void rows_any(bool exclusive, const T* x, T* y, int64_t rows, int64_t len
         LS_ROWS(16, 16);
     else if (len <= 65536 && n < int64_t(1) << 18)
         LS_ROWS(4, 4);
-    else if (len <= int64_t(1) << 20 && n < int64_t(1) << 20)
+    else if (len <= 65536 || (len <= int64_t(1) << 20 && n < int64_t(1) << 20))
         LS_ROWS(8, 4);
     else if (len <= int64_t(1) << 20 && n < int64_t(1) << 22)
         LS_ROWS(8, 8);

@@ -60,7 +60,8 @@ def test_rows_f32(ops, shape, excl):
 ROUTE_SHAPES = [(3, 8192), (3, 8193), (1, 12_000), (40, 16_384), (66, 16_385), (1, 20_004),
                 (2, 32_768), (33, 32_767), (40, 32_769), (3, 65_536), (9, 32_772), (17, 65_536),
                 (17, 65_533), (17, 65_540), (7, 131_072), (33, 131_068), (65, 131_076),
-                (70, 65_539), (2, (1 << 20) + 4), (9, (1 << 20) + 1)]
+                (70, 65_539), (2, (1 << 20) + 4), (9, (1 << 20) + 1), (32, 65_536), (33, 65_536),
+                (36, 65_533), (65, 32_769)]
 
 
 @pytest.mark.parametrize("shape", ROUTE_SHAPES, ids=lambda s: f"{s[0]}x{s[1]}")
