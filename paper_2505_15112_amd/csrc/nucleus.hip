@@ -839,6 +839,9 @@ __global__ __launch_bounds__(kNucThreads) LS_OCCUPANCY8 void k_nuc_sort(
             uint32_t from = floor, hi = cap, fits = 1;
             if (big) nuc_window(lk, m, floor, cap, &from, &hi, &fits, s_v, L);
             const uint32_t n = nuc_select(lk, m, from, hi, s_v, L);
+            // only when the row was rewritten while the call ran, so that the
+            // list and the histogram disagree; the loop ends all the same
+            if (n == 0) return;  // uniform
             uint32_t* out = reinterpret_cast<uint32_t*>(sorted) + (int64_t)row * len + a;
             cap = from - 1u;
             a += n;
@@ -858,7 +861,6 @@ __global__ __launch_bounds__(kNucThreads) LS_OCCUPANCY8 void k_nuc_sort(
                 nuc_range(key, n, &from, &hi, L);
                 nuc_sort(key, n, from, hi, out, L);
             }
-            if (n == 0) return;  // cannot happen; the loop ends whatever the list holds
         }
     }
 }
