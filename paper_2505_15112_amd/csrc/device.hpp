@@ -85,6 +85,42 @@ __device__ __forceinline__ T wave_sum(T v) {
 
 __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 
+// Set bits of m below this lane.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+}
+
+// Lanes holding the same 8-bit digit as this lane, when every lane of the
+// wave holds a key: the AND over the digit bits of that bit's ballot,
+// complemented where this lane's bit is 0.  Per bit: e = all ones if the bit
+// is 0 (a sign-extended bit field of ~d), the ballot of e == 0, and
+// m &= ballot ^ e for each 32-bit half.  The empty asm statements only hide
+// values from the optimiser (they emit nothing): the ballot then stays a
+// test of e, and each m &= ballot ^ e stays one three-input bit operation
+// instead of being regrouped with the next bit into more operations.
+__device__ __forceinline__ uint64_t peers8_all(uint32_t d) {
+    const int nd = (int)~d;
+    uint32_t e[8];
+    uint64_t bb[8];
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        e[b] = (uint32_t)__builtin_amdgcn_sbfe(nd, b, 1);
+        asm("" : "+v"(e[b]));
+    }
+    // all ballots first: each is read well after it is written, so no wait
+    // states go in between
+#pragma unroll
+    for (int b = 0; b < 8; ++b) bb[b] = __ballot(e[b] == 0u);
+    uint32_t lo = ~0u, hi = ~0u;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        lo &= (uint32_t)bb[b] ^ e[b];
+        hi &= (uint32_t)(bb[b] >> 32) ^ e[b];
+        asm("" : "+v"(lo), "+v"(hi));
+    }
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // Orders one wavefront's LDS writes before its later LDS reads of other
 // lanes' data (the LDS executes a wave's instructions in order; this keeps
 // the compiler from moving the accesses across).

@@ -540,8 +540,7 @@ __global__ __launch_bounds__(kNucThreads) LS_OCCUPANCY8 void k_nuc_gather(
         const uint32_t key = nuc_key(b);
         const bool q = ok && key >= key_min;
         const uint64_t m = __ballot(q);
-        const uint32_t to = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+        const uint32_t to = at + lanes_below(m);
         if (q && to < (uint32_t)len) {  // always below len; checked all the same
             kr[to] = key;
             ir[to] = pos;
@@ -552,12 +551,6 @@ __global__ __launch_bounds__(kNucThreads) LS_OCCUPANCY8 void k_nuc_gather(
 
 // ---------------------------------------------------------------- a group's sort
 
-// Sorts n <= kNucGroupMax keys, key[e] being number threadIdx.x + e kNucThreads,
-// in descending order to out[0, n) (as float bits).  The key range [lo, hi] is
-// spread over kNucSlots slots (linearly, and keys are about evenly dense in it:
-// about one key a slot); the keys are counted per slot, moved to their slots'
-// places in LDS, and each finds its rank among the keys of its slot by looking
-// at them all.  A slot of more than kNucFew keys that are all equal needs no look.
 // The thread's number, as a value that nothing is hoisted out of loops for
 // (addresses derived from it would stay live through the whole kernel).
 __device__ __forceinline__ uint32_t nuc_thread() {
@@ -572,6 +565,76 @@ struct NucSortLds {
     uint32_t w[kNucWaves];
     uint32_t mixed;
 };
+
+// The keys L.key[0, n), all in [hi - range, hi], to out[0, n) in descending
+// order (as float bits), by stable 8-bit digit passes over their distance below
+// hi, as many as the range has bytes; ranking as in k_radix8_scatter.  The time
+// does not depend on the keys: for crowded slots of nuc_sort.
+__device__ __forceinline__ void nuc_digits(uint32_t n, uint32_t hi, uint32_t range, uint32_t* out,
+                                        NucSortLds& L) {
+    static_assert(kNucWaves * 256 <= kNucSlots / 2, "digit counts of every wave fit the slots");
+#pragma unroll 1
+    for (int shift = 0; shift < 32 && (range >> shift) != 0; shift += 8) {
+        const uint32_t t = nuc_thread(), lane = t % kWave, w = uni(t / kWave);
+        const uint32_t place = w * kNucPer * kWave + lane;  // the lane's key of chunk e: + e kWave
+        uint32_t* wh = L.slot + w * 256;
+        // places from n on hold the largest distance: they stay last in every pass
+        uint32_t d[kNucPer], rank[kNucPer / 2];  // ranks in the wave, two a register
+        __syncthreads();  // L.key written, L.slot free
+#pragma unroll
+        for (int e = 0; e < kNucPer; ++e)
+            d[e] = place + e * kWave < n ? hi - L.key[place + e * kWave] : 0xFFFFFFFFu;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) wh[i * kWave + lane] = 0;
+        wave_lds_sync();
+#pragma unroll
+        for (int e = 0; e < kNucPer; ++e) {
+            const uint32_t q = (d[e] >> shift) & 255u;
+            const uint64_t peers = peers8_all(q);
+            const uint32_t below = lanes_below(peers);
+            const uint32_t size = (uint32_t)__builtin_popcountll(peers);
+            if (below == 0) atomicAdd(&wh[q], size);
+            const uint32_t r = wh[q] - size + below;
+            rank[e / 2] = e % 2 ? rank[e / 2] | r << 16 : r;
+            asm volatile("" : "+v"(rank[e / 2]));
+            __builtin_amdgcn_sched_barrier(0);  // one key's ballots at a time: registers
+        }
+        __syncthreads();
+        // digit t: every wave's first place
+        uint32_t tot = 0, total;
+        if (t < 256)
+#pragma unroll 4
+            for (int k = 0; k < kNucWaves; ++k) tot += L.slot[k * 256 + t];
+        uint32_t first = block_excl_scan(tot, L.w, &total);
+        if (t < 256)
+#pragma unroll 4
+            for (int k = 0; k < kNucWaves; ++k) {
+                const uint32_t c = L.slot[k * 256 + t];
+                L.slot[k * 256 + t] = first;
+                first += c;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < kNucPer; ++e) {
+            const uint32_t to = (e % 2 ? rank[e / 2] >> 16 : rank[e / 2] & 0xFFFFu) + wh[(d[e] >> shift) & 255u];
+            if (to < n) L.key[to] = hi - d[e];
+            if (e % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = nuc_thread(); i < n; i += kNucThreads) out[i] = nuc_bits(L.key[i]);
+}
+
+// Sorts n <= kNucGroupMax keys, key[e] being number threadIdx.x + e kNucThreads,
+// in descending order to out[0, n) (as float bits).  The key range [lo, hi] is
+// spread over kNucSlots slots (linearly: keys that are about evenly dense in it
+// are about one a slot); the keys are counted per slot, moved to their slots'
+// places in LDS, and each finds its rank among the keys of its slot by looking
+// at them all.  A slot of more than kNucFew keys that are all equal needs no
+// look; with any other such slot (keys far from evenly dense: one outlier is
+// enough) the group goes by digit passes, since the looks would be quadratic
+// (the call on 64 x 12288, softmax of N(0, 10^-6) with a tenth of every row zero:
+// 4700 us by looks, 73 so; softmax of N(0, 4): 37).
 __device__ void nuc_sort(const uint32_t (&key)[kNucPer], uint32_t n, uint32_t lo, uint32_t hi,
                          uint32_t* out, NucSortLds& L) {
     const uint32_t t = nuc_thread();
@@ -632,13 +695,16 @@ __device__ void nuc_sort(const uint32_t (&key)[kNucPer], uint32_t n, uint32_t lo
         }
         __syncthreads();
     }
-    const bool mixed = L.mixed == 2;
+    if (L.mixed == 2) {  // uniform
+        nuc_digits(n, hi, range, out, L);
+        return;
+    }
 #pragma unroll 4
     for (uint32_t i = t; i < n; i += kNucThreads) {
         const uint32_t k = L.key[i], s = slot_of(k);
         const uint32_t first = s ? end_of(s - 1) : 0u, last = end_of(s);
         uint32_t r = i;
-        if (last - first > 1u && (last - first <= kNucFew || mixed)) {
+        if (last - first > 1u && last - first <= kNucFew) {
             r = first;
             for (uint32_t j = first; j < last; ++j) {
                 const uint32_t o = L.key[j];
@@ -804,9 +870,7 @@ __device__ __forceinline__ uint32_t nuc_select(const uint32_t* keys, uint32_t m,
         if (at + cnt > kNucGroupMax) continue;  // only their number is wanted
 #pragma unroll
         for (int q = 0; q < kEach; ++q) {
-            const uint32_t to =
-                at + __builtin_amdgcn_mbcnt_hi((uint32_t)(mk[q] >> 32),
-                                               __builtin_amdgcn_mbcnt_lo((uint32_t)mk[q], 0));
+            const uint32_t to = at + lanes_below(mk[q]);
             if ((mk[q] >> lane_id()) & 1u) L.key[to] = v[q / 4][q % 4];
             at += (uint32_t)__builtin_popcountll(mk[q]);
         }

@@ -337,3 +337,142 @@ def test_topp_sample_cutoff_as_sorted_rows(ops, length, rows):
             # the token lies at or before the cutoff in the sorted row
             pos = (perm == tok[:, None]).int().argmax(dim=1)
             assert bool((pos <= cut).all()), (rows, length, p)
+
+
+def _check_as_sorted(ops, x, theta, p, what):
+    """Cutoff and token of the sampler against the rows sorted whole: the same
+    cutoff as the top-p cutoff finds there, and a token whose place in the sorted
+    row is the draw's, or in the rounding band around its threshold."""
+    import torch
+    srt, perm = ops.radix_sort_rows_f32(x, descending=True)
+    tok, cut = ops.topp_sample_f32(x, theta, p, with_cutoff=True)
+    want = ops.topp_cutoff_f32(srt, p)
+    assert torch.equal(cut, want), (what, p, cut[:4], want[:4])
+    pos = to_host((perm == tok[:, None]).int().argmax(dim=1))
+    assert torch.equal(perm.gather(1, to_dev(pos).long()[:, None]).squeeze(1), tok), (what, p)
+    csum = to_host(torch.cumsum(srt.double(), dim=1))
+    th = to_host(theta).astype(np.float64)
+    for r, k in enumerate(to_host(cut)):
+        total = float(csum[r, k])
+        assert draw_accept(int(pos[r]), csum[r], th[r] * total, draw_tol(th[r], total), int(k)), \
+            (what, p, r, int(pos[r]), int(k))
+
+
+def _crowded_rows(kind, rows, length, seed):
+    """Probabilities far from evenly spread over their range: flat rows (keys a
+    few hundred or thousand apart) with one large element or a share of zeros,
+    rows mostly zero, rows of one value, few values, and values at three scales."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    z = torch.randn((rows, length), device="cuda", generator=g)
+    u = torch.rand((rows, length), device="cuda", generator=g)
+    if kind.startswith("spike"):
+        x = torch.softmax(float(kind[5:]) * z, 1) * 0.95
+        return x.scatter_(1, torch.randint(0, length, (rows, 1), device="cuda", generator=g), 0.05)
+    if kind.startswith("mask"):
+        return torch.softmax((float(kind[4:]) * z).masked_fill(u < 0.1, float("-inf")), 1)
+    if kind == "rare":
+        return torch.softmax((2 * z).masked_fill(u < 0.99, float("-inf")), 1)
+    if kind == "equal":
+        return torch.full_like(z, 1.0 / length)
+    if kind == "flat":
+        return torch.softmax(1e-3 * z, 1)
+    if kind == "bf16":
+        return torch.softmax(2 * z, 1).bfloat16().float()
+    x = torch.softmax(1e-6 * z, 1) * 0.5  # scales
+    x = torch.where(u < 0.3, x * 1e-20, x)
+    return torch.where(u > 0.9, torch.softmax(z, 1), x).contiguous()
+
+
+@pytest.mark.parametrize("length", [4097, 8192, 12_288, 12_289, 131_072])
+@pytest.mark.parametrize("kind", ["spike.1", "spike.001", "mask.1", "mask.001", "mask.000001",
+                                  "rare", "equal", "scales"])
+def test_topp_sample_crowded(ops, length, kind):
+    """Rows whose keys crowd in a small part of their range, on both sides of the
+    row length up to which one workgroup sorts a row whole."""
+    import torch
+    announce("topp crowded", length, kind)
+    rows = 9
+    x = _crowded_rows(kind, rows, length, seed=length)
+    theta = torch.rand(rows, device="cuda", generator=torch.Generator("cuda").manual_seed(length))
+    for p in (0.3, 0.9, 1.0, 2.0):
+        _check_as_sorted(ops, x, theta, p, f"{kind} {length}")
+
+
+@pytest.mark.parametrize("length", [4097, 12_288])
+def test_topp_sample_crowded_exact(ops, length):
+    """Sixteen values 2^-10 apart and zeros, every sum exact: cutoff and token are
+    the oracle's.  The values share two slots of the sort in LDS with thousands
+    of keys each, so the row goes by digit passes."""
+    announce("topp crowded exact", length)
+    rows = 6
+    rng = np.random.default_rng(length)
+    x = (1.0 + rng.integers(0, 16, (rows, length)) * 2.0**-10).astype(np.float32)
+    x[rng.random((rows, length)) < 0.1] = 0.0
+    theta = (rng.integers(0, 8, rows) / 8.0).astype(np.float32)
+    for p in (1.0, np.floor(0.5 * length), 0.8 * length, 2.0**22):
+        p = float(np.float32(p))
+        rt, rc = oracle.topp_sample_f32(x, theta, p)
+        tok, cut = ops.topp_sample_f32(to_dev(x), to_dev(theta), p, with_cutoff=True)
+        assert_equal_first_diff(to_host(cut), rc, f"cutoff {length} {p}")
+        # theta in eighths of a sum with up to 14 + 10 bits: the product is rounded
+        same = to_host(tok) == rt
+        csum = np.cumsum(-np.sort(-x.astype(np.float64), axis=1), axis=1)
+        for r in np.flatnonzero(~same):
+            order = np.argsort(-x[r].astype(np.float64), kind="stable")
+            total = csum[r, rc[r]]
+            pos = int(np.flatnonzero(order == to_host(tok)[r])[0])
+            assert draw_accept(pos, csum[r], theta[r] * total, 2.0**-23 * theta[r] * total,
+                               int(rc[r])), (length, p, r)
+
+
+def _best_us(f, batches=8, calls=3):
+    import torch
+    for _ in range(4):
+        f()
+    best = float("inf")
+    for _ in range(batches):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        torch.cuda.synchronize()
+        a.record()
+        for _ in range(calls):
+            f()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1000 / calls)
+    return best
+
+
+TIMED = [((128, 8192), k) for k in ("spike.001", "mask.1", "mask.001", "mask.000001")] + \
+        [((64, 12_288), k) for k in ("spike.001", "mask.1", "mask.001", "mask.000001", "equal")]
+
+
+@pytest.mark.parametrize("shape,kind", TIMED, ids=lambda v: v if isinstance(v, str)
+                         else f"{v[0]}x{v[1]}")
+def test_topp_sample_time_bounded(ops, shape, kind):
+    """The partial sort never costs much more than the sort of whole rows that
+    it stands in for, whatever the values: the sampler takes at most 1.3 times the
+    row sort and a cutoff on its result, or 3 times its own time on softmax
+    rows of the same shape if that is longer (unbounded group sorts took 10 to 50
+    times as long)."""
+    import torch
+    from paper_2505_15112_amd import _lib
+    rows, length = shape
+    announce("topp time", shape, kind)
+    x = _crowded_rows(kind, rows, length, seed=5)
+    z = torch.softmax(2 * torch.randn(x.shape, device="cuda"), 1)
+    theta = torch.rand(rows, device="cuda")
+    ws = ops.workspace(_lib.OP_TOPP_SAMPLE, x.device, rows=rows, length=length)
+    scr = ops.scratch(_lib.OP_TOPP_SAMPLE, x.device, rows, length)
+    wss = ops.workspace(_lib.OP_SORT_ROWS, x.device, rows=rows, length=length)
+    wsc = ops.workspace(_lib.OP_SCAN_ROWS, x.device, rows=rows, length=length)
+    for p in (0.9, 1.0):
+        def sample(v):
+            return ops.topp_sample_f32(v, theta, p, with_cutoff=True, ws=ws, scratch_buf=scr)
+        srt = ops.radix_sort_rows_f32(x, descending=True)[0]
+        whole = _best_us(lambda: ops.radix_sort_rows_f32(x, descending=True, ws=wss)) + \
+            _best_us(lambda: ops.topp_cutoff_f32(srt, p, ws=wsc))
+        t, usual = _best_us(lambda: sample(x)), _best_us(lambda: sample(z))
+        print(f"[time] {shape} {kind} p={p}: {t:.1f} us, row sort and cutoff {whole:.1f}, "
+              f"softmax rows {usual:.1f}", flush=True)
+        assert t <= max(1.3 * whole, 3 * usual), (shape, kind, p, t, whole, usual)
