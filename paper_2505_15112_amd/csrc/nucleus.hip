@@ -13,10 +13,11 @@
 //    first at which a lower bound of the running sum (each element counted as
 //    its bin's least key) passes p, hence how many elements the draw reads, and
 //    where each tile's share of them goes;
-//  * k_nuc_gather: those elements, keys and source indices, to the row's list;
-//  * k_nuc_sort, one workgroup per group (some thousand elements: the bins that
-//    start in one window of the sorted row): picks its keys out of the list and
-//    sorts them in LDS, in descending order.
+//  * k_nuc_gather: those elements, keys and source indices, to the row's list,
+//    group by group (some thousand elements: the bins that start in one window of
+//    the sorted row);
+//  * k_nuc_sort, one workgroup per group: sorts its keys in LDS, in descending
+//    order.
 // Workgroups are numbered tile by tile (or group by group) of all rows, so that
 // with a multiple of 8 rows everything of one row runs on one XCD and finds the
 // row's list in its L2.  Rows of up to kNucGroupMax elements are one group, sorted whole by
@@ -25,9 +26,9 @@
 //
 // Bound: two reads of the rows from HBM (22 us for 128 x 131072) and the LDS
 // work of the sort.  Kernel times at 128 x 131072, p = 0.9 (about 38000
-// elements of each row gathered): histogram 19 us, pick 8, gather 22 (105 MB
-// moved), sort 33, and the draw 5 + 13; the call 272 us by the row sort, 101 us
-// this way.  4 x 200003: 93 -> 50 us, each of the six kernels a few us of
+// elements of each row gathered): histogram 19 us, pick 9, gather 27 (105 MB
+// moved), sort 25, and the draw 5 + 9; the call 272 us by the row sort, 94 us
+// this way.  4 x 200003: 93 -> 42 us, each of the six kernels a few us of
 // latency.  Measured on the way: the elements scattered to their bins by LDS
 // counters instead of gathered (one 8-byte store per lane and line): 62 us for
 // the scatter; a workgroup for every group a row could have, most of them
@@ -50,7 +51,9 @@ constexpr uint32_t kNucSlots = 14336;    // two sorts' LDS fits a CU
 static_assert(kNucSlots % (2 * kNucThreads) == 0, "whole words per thread");
 constexpr int64_t kNucMaxLen = int64_t(1) << 20;
 constexpr uint32_t kNucMinGroup = 4096;
-constexpr uint32_t kNucMaxGroups = (uint32_t)(kNucMaxLen / kNucMinGroup);
+constexpr uint32_t kNucMaxGroups = 1024;  // table room in LDS
+static_assert(kNucMaxLen / kNucMinGroup <= kNucMaxGroups, "a row's groups fit the tables");
+constexpr uint16_t kNucNoGroup = 0xFFFF;
 constexpr uint32_t kNucMaxSegs = 40;  // 2^20 + 3 positions of 32768, 2^18 + 3 of 8192: 33
 // The last two bins are in no map (see k_nuc_hist): the elements above the
 // sampled range, and the flag of a row that holds a NaN.
@@ -139,6 +142,16 @@ struct NucTile {
                 }
             }
         }
+    }
+    // f(bits of four elements, position of the first, which of them lie in the
+    // row), in uniform control flow
+    template <class F>
+    __device__ __forceinline__ void each4(F f) const {
+        uint32_t q0 = (uint32_t)pos0;
+        asm volatile("" : "+v"(q0));
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+            f(v[j], q0 + (uint32_t)(j * kNucThreads * 4), full ? 15u : (in >> (4 * j)) & 15u);
     }
     // f(bits, position, in the row) for every position, in uniform control flow
     template <class F>
@@ -324,13 +337,14 @@ __global__ __launch_bounds__(kNucThreads) void k_nuc_pick(const uint16_t* hist, 
                                                           const uint32_t* maps, float p,
                                                           int32_t len, uint32_t heads,
                                                           NucRow* rows, const double* above,
-                                                          uint32_t window, uint32_t ngroups,
-                                                          uint2* groups) {
+                                                          uint32_t window, uint32_t slots,
+                                                          uint2* groups, uint32_t* cursors,
+                                                          uint16_t* bin_groups) {
     __shared__ uint32_t s_cell[kNucBins], s_map[kNucCells];
     __shared__ uint32_t s_w[kNucWaves];
     __shared__ double s_d[kNucWaves];
     __shared__ uint32_t s_need, s_sorted, s_key, s_nan;
-    __shared__ uint32_t s_g[kNucMaxGroups + 1], s_low[kNucMaxGroups];
+    __shared__ uint32_t s_g[kNucMaxGroups], s_low[kNucMaxGroups], s_id[kNucMaxGroups];
     const int64_t row = blockIdx.x;
     const uint32_t t = threadIdx.x;
     const int w = t / kWave;
@@ -362,10 +376,7 @@ __global__ __launch_bounds__(kNucThreads) void k_nuc_pick(const uint16_t* hist, 
         s_sorted = (uint32_t)len;
         s_key = 0u;
     }
-    for (uint32_t i = t; i <= ngroups; i += kNucThreads) {
-        s_g[i] = UINT_MAX;
-        if (i < ngroups) s_low[i] = UINT_MAX;
-    }
+    if (t < slots) s_g[t] = s_low[t] = UINT_MAX;
     // every bin's least key
     uint32_t low[4];
     if (r.direct) {  // uniform: bin b is cell b
@@ -468,8 +479,8 @@ __global__ __launch_bounds__(kNucThreads) void k_nuc_pick(const uint16_t* hist, 
     }
     __syncthreads();
     const uint32_t need = s_need;
-    // the bins that start before `need` are sorted; group g takes those that
-    // start in [g window, (g + 1) window)
+    // the bins that start before `need` are sorted; those that start in one
+    // window of the sorted row are a group
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         if (cnt[i] && start[i] < need) {
@@ -483,70 +494,124 @@ __global__ __launch_bounds__(kNucThreads) void k_nuc_pick(const uint16_t* hist, 
         }
     }
     __syncthreads();
-    // {first position, least key} of every group, and the end
-    if (t < kWave) {
-        const uint32_t sorted = s_sorted;
-        uint32_t next = sorted;  // first position of the nearest group after these
-        for (int32_t c = (int32_t)(ngroups / kWave * kWave); c >= 0; c -= kWave) {
-            const uint32_t i = (uint32_t)c + t;
-            uint32_t g = i < ngroups ? s_g[i] : UINT_MAX;
-            for (int d = 1; d < kWave; d *= 2) {  // suffix minimum
-                const uint32_t o = __shfl_down(g, d);
-                if (t + d < kWave && o < g) g = o;
-            }
-            g = g < next ? g : next;
-            if (i <= ngroups)
-                groups[row * (ngroups + 1) + i] = make_uint2(g, i < ngroups ? s_low[i] : 0u);
-            next = uni(g);
-        }
-        if (t == 0) {
-            rows[row].key_min = s_key;
-            rows[row].sorted = sorted;
-            rows[row].cursor = 0;
-        }
+    // groups are numbered without the empty windows: {first position, least key},
+    // where its list slots start, and the end
+    static_assert(kNucMaxGroups <= kNucThreads, "a thread per group");
+    const uint32_t gs = t < slots ? s_g[t] : UINT_MAX;
+    uint32_t ng;
+    const uint32_t id = block_excl_scan(gs != UINT_MAX ? 1u : 0u, s_w, &ng);
+    uint2* gr = groups + row * (slots + 1);
+    if (gs != UINT_MAX) {
+        gr[id] = make_uint2(gs, s_low[t]);
+        cursors[row * slots + id] = gs;
+        s_id[t] = id;
     }
+    if (t == 0) {
+        gr[ng] = make_uint2(s_sorted, 0u);
+        rows[row].key_min = s_key;
+        rows[row].groups = ng;
+    }
+    __syncthreads();
+    // every bin's group (bins b0 .. b0 + 3, places 3 .. 0)
+    uint16_t bg[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        bg[3 - i] = cnt[i] && start[i] < need ? (uint16_t)s_id[start[i] / window] : kNucNoGroup;
+    reinterpret_cast<ushort4*>(bin_groups + row * kNucBins)[b0 / 4] =
+        make_ushort4(bg[0], bg[1], bg[2], bg[3]);
 }
 
 // ---------------------------------------------------------------- gather
 
 // The tile's elements with keys from key_min up, keys and source indices, to
-// the row's list, at slots reserved by one atomic per tile (in any order: the
-// list is searched by key).  Per element of a lane the wave's kept ones are a
-// ballot, and go to consecutive slots.
+// the row's list, group by group (in any order within a group), so that the sort
+// of a group reads its own keys only: group g has the list's slots [groups[g].x,
+// groups[g + 1].x).  The tile's share of each group is known from its bins'
+// counts, and reserved by one atomic per group; its elements take their slots by
+// LDS counters.  With one run of slots per tile instead, the sort picking its
+// group's keys out of the whole list, the gather takes 22 instead of 27 us at 128
+// x 131072 and p = 0.9, the sort 33 instead of 25 and the draw's lookup in the list
+// 15 instead of 9; and long rows read groups x list: 1 x 2^20, softmax of N(0,
+// 4), 117 us a call at p = 0.9 and 817 at p = 1, now 59 and 270.  Without the ring
+// (the search and the slot for every element of the tile) 36 us.
 template <int J>
 __global__ __launch_bounds__(kNucThreads) LS_OCCUPANCY8 void k_nuc_gather(
-    const uint32_t* x, int32_t len, uint32_t nrows, uint32_t segs, NucRow* rows, uint32_t* keys,
-    uint32_t* idx, uint32_t stride) {
-    __shared__ uint32_t s_w[kNucWaves];
-    __shared__ uint32_t s_first;
+    const uint32_t* x, int32_t len, uint32_t nrows, uint32_t segs, const NucRow* rows,
+    const uint16_t* hist, const uint16_t* bin_groups, const uint2* groups, uint32_t* cursors,
+    uint32_t slots, uint32_t* keys, uint32_t* idx, uint32_t stride) {
+    __shared__ uint32_t s_low[kNucMaxGroups], s_to[kNucMaxGroups];
     const uint32_t seg = blockIdx.x / nrows, row = blockIdx.x - seg * nrows;
+    const uint32_t t = threadIdx.x;
     NucTile<J> tile;
     tile.load(x + (int64_t)row * len, len, seg);
-    const uint32_t key_min = rows[row].key_min;
-    uint32_t n = 0;  // the lane's kept elements
-    tile.each([&](uint32_t b, uint32_t, bool ok) { n += ok && nuc_key(b) >= key_min ? 1u : 0u; });
-    uint32_t total;
-    uint32_t at = block_excl_scan(n, s_w, &total);
-    if (total == 0) return;  // uniform
-    if (threadIdx.x == 0)
-        s_first = __hip_atomic_fetch_add(&rows[row].cursor, total, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t key_min = rows[row].key_min, ng = uni(rows[row].groups);
+    const ushort4 c = reinterpret_cast<const ushort4*>(
+        hist + (int64_t)(row * segs + seg) * kNucBins)[t];
+    const ushort4 g = reinterpret_cast<const ushort4*>(bin_groups + (int64_t)row * kNucBins)[t];
+    // past the last group least keys of 0: the search below stays before them
+    s_low[t] = t < ng ? groups[(int64_t)row * (slots + 1) + t].y : 0u;
+    s_to[t] = 0;
     __syncthreads();
-    // the wave's first slot
-    at = uni(s_first + at);
+    auto add = [&](uint32_t n, uint32_t group) {
+        if (n != 0 && group != kNucNoGroup) atomicAdd(&s_to[group], n);
+    };
+    if (g.x == g.y && g.x == g.z && g.x == g.w) {
+        add((uint32_t)c.x + c.y + c.z + c.w, g.x);
+    } else {
+        add(c.x, g.x);
+        add(c.y, g.y);
+        add(c.z, g.z);
+        add(c.w, g.w);
+    }
+    __syncthreads();
+    if (t < ng && s_to[t] != 0)
+        s_to[t] = __hip_atomic_fetch_add(&cursors[(int64_t)row * slots + t], s_to[t],
+                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
     uint32_t* kr = keys + (int64_t)row * stride;
     uint32_t* ir = idx + (int64_t)row * stride;
-    tile.each([&](uint32_t b, uint32_t pos, bool ok) {
-        const uint32_t key = nuc_key(b);
-        const bool q = ok && key >= key_min;
-        const uint64_t m = __ballot(q);
-        const uint32_t to = at + lanes_below(m);
-        if (q && to < (uint32_t)len) {  // always below len; checked all the same
-            kr[to] = key;
-            ir[to] = pos;
+    // The wave's kept elements go through a ring in LDS, so that what follows is
+    // done 64 kept ones at a time, not for every element of the row: the group
+    // of a key (how many groups' least keys are above it), and its slot (the
+    // group of the first lane takes its lanes' slots by one atomic, lanes of other
+    // groups one each).
+    constexpr uint32_t kRing = 512;  // fewer than 64 left, and 256 more
+    __shared__ uint2 s_ring[kNucWaves][kRing];
+    uint2* ring = s_ring[uni(t / kWave)];
+    const uint32_t lane = lane_id();
+    const uint32_t step0 = ng > 1 ? 1u << (31 - __builtin_clz(ng - 1)) : 0u;
+    uint32_t head = 0, tail = 0;  // uniform
+    auto flush = [&](uint32_t n) {
+        wave_lds_sync();
+        const uint2 kp = ring[(head + lane) % kRing];
+        head += n;
+        if (lane >= n) return;
+        uint32_t grp = 0;
+        for (uint32_t d = step0; d != 0; d >>= 1) grp += s_low[grp + d - 1] > kp.x ? d : 0u;
+        const bool with = grp == uni(grp);  // lane 0 is among them
+        const uint64_t same = __ballot(with);
+        uint32_t to = 0;
+        if (!with || lane == 0)
+            to = atomicAdd(&s_to[grp], with ? (uint32_t)__builtin_popcountll(same) : 1u);
+        if (with) to = uni(to) + lanes_below(same);
+        if (to < (uint32_t)len) {  // always; checked all the same
+            kr[to] = kp.x;
+            ir[to] = kp.y;
         }
-        at += (uint32_t)__builtin_popcountll(m);
+    };
+    tile.each4([&](const uint32_t(&b)[4], uint32_t pos, uint32_t in) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t key = nuc_key(b[e]);
+            const bool q = ((in >> e) & 1u) && key >= key_min;
+            const uint64_t m = __ballot(q);
+            if (q) ring[(tail + lanes_below(m)) % kRing] = make_uint2(key, pos + e);
+            tail += (uint32_t)__builtin_popcountll(m);
+        }
+#pragma unroll 1
+        while (tail - head >= kWave) flush(kWave);
     });
+    if (tail != head) flush(tail - head);
 }
 
 // ---------------------------------------------------------------- a group's sort
@@ -817,38 +882,25 @@ __device__ void nuc_window(const uint32_t* lk, uint32_t m, uint32_t floor, uint3
     }
 }
 
-// The keys of group g: those in [lo, hi].
-__device__ __forceinline__ void group_keys(const uint2* gr, uint32_t g, uint32_t* lo, uint32_t* hi) {
-    *lo = uni(gr[g].y);
-    *hi = UINT_MAX;
-    for (uint32_t j = g; j > 0;) {  // below the nearest group before it that is not empty
-        const uint32_t b = uni(gr[--j].y);
-        if (b != UINT_MAX) {
-            *hi = b - 1u;
-            break;
-        }
-    }
-}
-
-// The list's keys in [lo, hi] (at most kNucGroupMax; of more only the number
-// is right) to L.key, in any order; returns their number.  16-byte loads; per
-// element of a lane the wave's kept ones go to consecutive LDS slots.
+// Of the m keys at `keys` (4-byte aligned; up to 3 words after them may be read)
+// those in [lo, hi] (at most kNucGroupMax; of more only the number is right) to
+// L.key, in any order; returns their number.  16-byte loads; per element of a
+// lane the wave's kept ones go to consecutive LDS slots.
 __device__ __forceinline__ uint32_t nuc_select(const uint32_t* keys, uint32_t m, uint32_t lo,
                                                uint32_t hi, uint32_t* s_n, NucSortLds& L) {
     const uint32_t t = nuc_thread();
-    const u32x4* k4 = reinterpret_cast<const u32x4*>(keys);
+    const u32x4_a4* k4 = reinterpret_cast<const u32x4_a4*>(keys);
     __syncthreads();
     if (t == 0) *s_n = 0;
     __syncthreads();
     const uint32_t range = hi - lo;
     constexpr int kLoads = 2, kEach = kLoads * 4;
     for (uint32_t b = 0; b < m; b += kEach * kNucThreads) {
-        u32x4 v[kLoads];
+        u32x4_a4 v[kLoads];
 #pragma unroll
         for (int q = 0; q < kLoads; ++q) {
-            const uint32_t i = b + (q * kNucThreads + t) * 4;
-            // the list's row is a multiple of 4 long: what lies past m is masked
-            v[q] = i < m ? k4[i / 4] : u32x4{0u, 0u, 0u, 0u};
+            const uint32_t i = b + (q * kNucThreads + t) * 4;  // what lies past m is masked
+            v[q] = i < m ? k4[i / 4] : u32x4_a4{0u, 0u, 0u, 0u};
         }
         uint64_t mk[kEach];  // the wave's kept lanes, per element
         uint32_t cnt = 0;
@@ -880,51 +932,48 @@ __device__ __forceinline__ uint32_t nuc_select(const uint32_t* keys, uint32_t m,
 }
 
 // Workgroup blockIdx.x / rows of row blockIdx.x % rows takes every parts-th
-// group of the row: its keys out of the row's list, then the sort; a group too
-// large for LDS window by window.  Workgroups without a group cost 9 ns each
-// to start, so there are about as many as the draw reads head tiles.
+// group of the row: its list slots, sorted; a group too large for LDS window by
+// window.
 __global__ __launch_bounds__(kNucThreads) LS_OCCUPANCY8 void k_nuc_sort(
     const uint32_t* keys, uint32_t stride, int32_t len, uint32_t rows, uint32_t parts,
-    const NucRow* info, const uint2* groups, uint32_t ngroups, float* sorted) {
+    const NucRow* info, const uint2* groups, uint32_t slots, float* sorted) {
     __shared__ NucSortLds L;
     __shared__ uint32_t s_v[4];
     const uint32_t part = blockIdx.x / rows, row = blockIdx.x - part * rows;
-    const uint2* gr = groups + (int64_t)row * (ngroups + 1);
-    const uint32_t m = uni(info[row].sorted);
-    const uint32_t* lk = keys + (int64_t)row * stride;
-    for (uint32_t g = part; g < ngroups; g += parts) {
-        uint32_t a = uni(gr[g].x);
-        const uint32_t end = uni(gr[g + 1].x);
-        if (a == end) continue;  // uniform
-        const bool big = end - a > kNucGroupMax;
-        uint32_t floor, cap;
-        group_keys(gr, g, &floor, &cap);
-        while (a < end) {  // once, unless big; every step writes a key
-            uint32_t from = floor, hi = cap, fits = 1;
-            if (big) nuc_window(lk, m, floor, cap, &from, &hi, &fits, s_v, L);
-            const uint32_t n = nuc_select(lk, m, from, hi, s_v, L);
-            // only when the row was rewritten while the call ran, so that the
-            // list and the histogram disagree; the loop ends all the same
-            if (n == 0) return;  // uniform
-            uint32_t* out = reinterpret_cast<uint32_t*>(sorted) + (int64_t)row * len + a;
-            cap = from - 1u;
+    const uint2* gr = groups + (int64_t)row * (slots + 1);
+    const uint32_t ng = uni(info[row].groups);
+    for (uint32_t g = part; g < ng; g += parts) {
+        const uint32_t first = uni(gr[g].x), m = uni(gr[g + 1].x) - first;
+        const uint32_t* lk = keys + (int64_t)row * stride + first;
+        uint32_t* out = reinterpret_cast<uint32_t*>(sorted) + (int64_t)row * len + first;
+        uint32_t cap = UINT_MAX;
+        for (uint32_t a = 0; a < m;) {  // once, unless m is too large; every step writes a key
+            const bool big = m > kNucGroupMax;
+            uint32_t from, hi, fits = 1, n = m;
+            if (big) {
+                nuc_window(lk, m, 0u, cap, &from, &hi, &fits, s_v, L);
+                n = nuc_select(lk, m, from, hi, s_v, L);
+                // only when the row was rewritten while the call ran, so that the
+                // list and the histogram disagree; the loop ends all the same
+                if (n == 0 || a + n > m) return;  // uniform
+                cap = from - 1u;
+            }
+            uint32_t* o = out + a;
             a += n;
             if (fits == 0) {  // one key, more often than fits
-                for (uint32_t i = nuc_thread(); i < n && a <= end; i += kNucThreads)
-                    out[i] = nuc_bits(hi);
+                for (uint32_t i = nuc_thread(); i < n; i += kNucThreads) o[i] = nuc_bits(hi);
                 continue;
             }
+            if (n > kNucGroupMax) return;  // never
             uint32_t key[kNucPer];
             const uint32_t t0 = nuc_thread();
 #pragma unroll
             for (int e = 0; e < kNucPer; ++e) {
                 const uint32_t i = t0 + e * kNucThreads;
-                key[e] = i < n ? L.key[i] : 0u;
+                key[e] = i < n ? (big ? L.key[i] : lk[i]) : 0u;
             }
-            if (n <= kNucGroupMax && a <= end) {  // always; checked all the same
-                nuc_range(key, n, &from, &hi, L);
-                nuc_sort(key, n, from, hi, out, L);
-            }
+            nuc_range(key, n, &from, &hi, L);
+            nuc_sort(key, n, from, hi, o, L);
         }
     }
 }
@@ -965,8 +1014,8 @@ static uint32_t nucleus_window(int64_t rows, int64_t len) {
 }
 
 struct NucLayout {
-    uint32_t segs, window, ngroups, stride;
-    size_t keys, idx, hist, above, maps, rows, groups, end;  // after the sorted keys
+    uint32_t segs, window, slots, stride;
+    size_t keys, idx, hist, above, maps, rows, groups, cursors, end;  // after the sorted keys
 };
 static NucLayout nucleus_layout(int64_t rows, int64_t len) {
     NucLayout l{};
@@ -980,7 +1029,7 @@ static NucLayout nucleus_layout(int64_t rows, int64_t len) {
     // rows that start off 16-byte boundaries: up to 3 positions before them
     l.segs = (uint32_t)((len + 3 + tile - 1) / tile);
     l.window = nucleus_window(rows, len);
-    l.ngroups = (uint32_t)((len + l.window - 1) / l.window);
+    l.slots = (uint32_t)((len + l.window - 1) / l.window);  // the most groups a row can have
     l.stride = (uint32_t)((len + 3) / 4 * 4);
     const size_t tiles = (size_t)rows * l.segs;
     l.idx = l.keys + align256((size_t)rows * l.stride * 4);
@@ -989,7 +1038,8 @@ static NucLayout nucleus_layout(int64_t rows, int64_t len) {
     l.maps = l.above + align256(tiles * sizeof(double));
     l.rows = l.maps + (size_t)rows * kNucCells * sizeof(uint32_t);
     l.groups = l.rows + (size_t)rows * sizeof(NucRow);
-    l.end = l.groups + (size_t)rows * (l.ngroups + 1) * sizeof(uint2);
+    l.cursors = l.groups + (size_t)rows * (l.slots + 1) * sizeof(uint2);
+    l.end = l.cursors + (size_t)rows * l.slots * sizeof(uint32_t);
     return l;
 }
 
@@ -1001,6 +1051,8 @@ static void nucleus_bins(const uint32_t* x, int64_t rows, int64_t len, float p, 
     uint32_t* maps = reinterpret_cast<uint32_t*>(s + l.maps);
     NucRow* info = reinterpret_cast<NucRow*>(s + l.rows);
     uint2* groups = reinterpret_cast<uint2*>(s + l.groups);
+    uint32_t* cursors = reinterpret_cast<uint32_t*>(s + l.cursors);
+    uint16_t* bin_groups = reinterpret_cast<uint16_t*>(maps);  // in the maps' place
     uint32_t* keys = reinterpret_cast<uint32_t*>(s + l.keys);
     uint32_t* idx = reinterpret_cast<uint32_t*>(s + l.idx);
     float* sorted = reinterpret_cast<float*>(s);
@@ -1014,14 +1066,20 @@ static void nucleus_bins(const uint32_t* x, int64_t rows, int64_t len, float p, 
                        kNucGroupMax - l.window < 4096u ? kNucGroupMax - l.window : 4096u);
     hipLaunchKernelGGL(k_nuc_pick, dim3((unsigned)rows), dim3(kNucThreads), 0, stream,
                        (const uint16_t*)hist, segs, (const uint32_t*)maps, p, n, heads, info,
-                       (const double*)above, l.window, l.ngroups, groups);
+                       (const double*)above, l.window, l.slots, groups, cursors, bin_groups);
     hipLaunchKernelGGL(k_nuc_gather<J>, dim3(tiles), dim3(kNucThreads), 0, stream, x, n,
-                       (uint32_t)rows, segs, info, keys, idx, l.stride);
+                       (uint32_t)rows, segs, (const NucRow*)info, (const uint16_t*)hist,
+                       (const uint16_t*)bin_groups, (const uint2*)groups, cursors, l.slots, keys,
+                       idx, l.stride);
+    // as many workgroups a row as groups are usual, or as fit the chip at once
+    // (two a CU), should that be more; those without a group cost 9 ns each
     const uint32_t want = (heads * 4096u * 5 / 4 + l.window - 1) / l.window;
-    const uint32_t parts = want < l.ngroups ? want : l.ngroups;
+    const uint32_t fit = (uint32_t)(512 / rows);
+    const uint32_t most = want > fit ? want : fit;
+    const uint32_t parts = most < l.slots ? most : l.slots;
     hipLaunchKernelGGL(k_nuc_sort, dim3((unsigned)rows * parts), dim3(kNucThreads), 0, stream,
                        (const uint32_t*)keys, l.stride, n, (uint32_t)rows, parts,
-                       (const NucRow*)info, (const uint2*)groups, l.ngroups, sorted);
+                       (const NucRow*)info, (const uint2*)groups, l.slots, sorted);
 }
 
 // The sorted rows (stride len) at the start of scratch (16-byte aligned; 16
@@ -1049,6 +1107,8 @@ hipError_t launch_nucleus_sort(const float* probs, float p, uint32_t heads, int6
     src->keys = reinterpret_cast<const uint32_t*>(s + l.keys);
     src->idx = reinterpret_cast<const uint32_t*>(s + l.idx);
     src->rows = reinterpret_cast<const NucRow*>(s + l.rows);
+    src->groups = reinterpret_cast<const uint2*>(s + l.groups);
+    src->slots = l.slots;
     src->stride = l.stride;
     return hipGetLastError();
 }

@@ -22,21 +22,23 @@ constexpr int kNucBins = 4096;
 struct NucRow {
     uint32_t lo, hi, shift;
     uint32_t key_min;  // keys from here up are gathered and sorted
-    uint32_t sorted;   // how many they are
-    uint32_t cursor;   // list slots taken so far (k_nuc_gather)
+    uint32_t groups;   // groups they form
     uint32_t direct;   // the cells are the bins
-    uint32_t pad;
+    uint32_t pad[2];
 };
 
 // Where the draw finds the source index of a sorted element: the row's list
-// (rows[r].sorted keys and their source indices, in no particular order; 16-byte
-// aligned, `stride` words from row to row), or, with keys null, the row x.
+// (keys and their source indices; `stride` words from row to row), where group g
+// of rows[r].groups has the same places as in the sorted row, from groups[r
+// (slots + 1) + g].x to the next one's, in no particular order; or, with keys
+// null, the row x.
 struct NucSource {
     const uint32_t* x;
     const uint32_t* keys;
     const uint32_t* idx;
     const NucRow* rows;
-    uint32_t stride;
+    const uint2* groups;
+    uint32_t stride, slots;
 };
 
 }  // namespace ls

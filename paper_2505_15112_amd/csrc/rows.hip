@@ -659,23 +659,42 @@ __device__ int64_t topp_head_find(const float* xr, int64_t len, const uint64_t* 
 
 // Source index of the element at position j of a row's sorted elements: of the
 // elements of that value the one with as many before it, by index, as the
-// sorted row has equal ones before j.  The whole workgroup (kThreads); s_t:
-// 1027 words of LDS.
+// sorted row has equal ones before j.  Equal keys are in one group, so only that
+// part of the list is searched.  The whole workgroup (kThreads); s_t: 1027 words
+// of LDS.
 template <int kThreads>
 __device__ __forceinline__ int32_t topp_token(const NucSource& src, uint32_t row, int64_t len,
                                               const float* sorted, uint32_t j, uint32_t* s_t) {
     const uint32_t t = threadIdx.x;
     const uint32_t* xr = src.x + (int64_t)row * len;
-    const uint32_t* kr = src.keys + (int64_t)row * src.stride;
-    const uint32_t* ir = src.idx + (int64_t)row * src.stride;
-    const uint32_t n = src.keys ? src.rows[row].sorted : (uint32_t)len;
     const uint32_t key = nuc_key(Bits<float>::to(sorted[j]));
     uint32_t* s_c = s_t + 1024;  // matches, equal before j, equal in all
     if (t < 3) s_c[t] = 0;
+    if (t < 2) s_t[t] = 0;
+    __syncthreads();
+    // the group of place j: its first place and number of keys (none, should the
+    // row have been rewritten while the call ran)
+    uint32_t first = 0, n = (uint32_t)len;
+    if (src.keys) {
+        const uint2* gr = src.groups + (int64_t)row * (src.slots + 1);
+        const uint32_t ng = src.rows[row].groups;
+        for (uint32_t g = t; g < ng; g += kThreads) {
+            const uint32_t a = gr[g].x, b = gr[g + 1].x;
+            if (a <= j && j < b) {  // one thread
+                s_t[0] = a;
+                s_t[1] = b - a;
+            }
+        }
+        __syncthreads();
+        first = s_t[0];
+        n = s_t[1];
+    }
+    const uint32_t* kr = src.keys + (int64_t)row * src.stride + first;
+    const uint32_t* ir = src.idx + (int64_t)row * src.stride + first;
     __syncthreads();
     // equal elements next to j in the sorted row, up to kThreads each side
     const bool eb = t < j && nuc_key(Bits<float>::to(sorted[j - 1 - t])) == key;
-    const bool ea = t + j + 1 < n && nuc_key(Bits<float>::to(sorted[j + 1 + t])) == key;
+    const bool ea = t + j + 1 < first + n && nuc_key(Bits<float>::to(sorted[j + 1 + t])) == key;
     const uint32_t cb = (uint32_t)__builtin_popcountll(__ballot(eb));
     const uint32_t ca = (uint32_t)__builtin_popcountll(__ballot(ea));
     if (lane_id() == 0 && (cb || ca)) {
@@ -689,11 +708,12 @@ __device__ __forceinline__ int32_t topp_token(const NucSource& src, uint32_t row
         if (src.keys) {
             constexpr int kLoads = 12;  // 16-byte loads in flight
             for (uint32_t b = 0; b < n && !done(); b += kLoads * 4 * kThreads) {
-                u32x4 v[kLoads];
+                u32x4_a4 v[kLoads];  // up to 3 words past the group's last
 #pragma unroll
                 for (int q = 0; q < kLoads; ++q) {
                     const uint32_t i = b + (q * kThreads + t) * 4;
-                    v[q] = i < n ? reinterpret_cast<const u32x4*>(kr)[i / 4] : u32x4{0u, 0u, 0u, 0u};
+                    v[q] = i < n ? reinterpret_cast<const u32x4_a4*>(kr)[i / 4]
+                                 : u32x4_a4{0u, 0u, 0u, 0u};
                 }
 #pragma unroll
                 for (int q = 0; q < kLoads; ++q)

@@ -377,6 +377,8 @@ def _crowded_rows(kind, rows, length, seed):
         return torch.full_like(z, 1.0 / length)
     if kind == "flat":
         return torch.softmax(1e-3 * z, 1)
+    if kind == "soft":
+        return torch.softmax(2 * z, 1)
     if kind == "bf16":
         return torch.softmax(2 * z, 1).bfloat16().float()
     x = torch.softmax(1e-6 * z, 1) * 0.5  # scales
@@ -443,7 +445,24 @@ def _best_us(f, batches=8, calls=3):
     return best
 
 
-TIMED = [((128, 8192), k) for k in ("spike.001", "mask.1", "mask.001", "mask.000001")] + \
+@pytest.mark.parametrize("length", [40_000, 262_145, 1 << 20])
+@pytest.mark.parametrize("kind", ["soft", "flat", "bf16", "scales"])
+def test_topp_sample_many_groups(ops, length, kind):
+    """Long rows sorted to their end: many groups a row, each with its own part
+    of the row's list, and the token looked up in the draw's group."""
+    import torch
+    announce("topp many groups", length, kind)
+    rows = 3
+    x = _crowded_rows(kind, rows, length, seed=length)
+    theta = torch.tensor([0.0, 0.5, 0.999], device="cuda")
+    for p in (0.5, 0.99, 2.0):
+        _check_as_sorted(ops, x, theta, p, f"{kind} {length}")
+
+
+TIMED = [((1, 1 << 20), k) for k in ("soft", "flat")] + \
+        [((4, 200_003), k) for k in ("soft", "flat", "bf16")] + \
+        [((128, 131_072), "flat")] + \
+        [((128, 8192), k) for k in ("spike.001", "mask.1", "mask.001", "mask.000001")] + \
         [((64, 12_288), k) for k in ("spike.001", "mask.1", "mask.001", "mask.000001", "equal")]
 
 
@@ -452,7 +471,7 @@ TIMED = [((128, 8192), k) for k in ("spike.001", "mask.1", "mask.001", "mask.000
 def test_topp_sample_time_bounded(ops, shape, kind):
     """The partial sort never costs much more than the sort of whole rows that
     it stands in for, whatever the values: the sampler takes at most 1.3 times the
-    row sort and a cutoff on its result, or 3 times its own time on softmax
+    row sort and two cutoffs on its result (its own cutoff and the draw), or 3 times its own time on softmax
     rows of the same shape if that is longer (unbounded group sorts took 10 to 50
     times as long)."""
     import torch
@@ -471,8 +490,8 @@ def test_topp_sample_time_bounded(ops, shape, kind):
             return ops.topp_sample_f32(v, theta, p, with_cutoff=True, ws=ws, scratch_buf=scr)
         srt = ops.radix_sort_rows_f32(x, descending=True)[0]
         whole = _best_us(lambda: ops.radix_sort_rows_f32(x, descending=True, ws=wss)) + \
-            _best_us(lambda: ops.topp_cutoff_f32(srt, p, ws=wsc))
+            2 * _best_us(lambda: ops.topp_cutoff_f32(srt, p, ws=wsc))
         t, usual = _best_us(lambda: sample(x)), _best_us(lambda: sample(z))
-        print(f"[time] {shape} {kind} p={p}: {t:.1f} us, row sort and cutoff {whole:.1f}, "
+        print(f"[time] {shape} {kind} p={p}: {t:.1f} us, row sort and cutoffs {whole:.1f}, "
               f"softmax rows {usual:.1f}", flush=True)
         assert t <= max(1.3 * whole, 3 * usual), (shape, kind, p, t, whole, usual)
