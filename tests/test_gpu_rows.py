@@ -2,8 +2,8 @@
 
 Row scans: int32 bit-exact, fp32 within the float bound plus bit-exact runs
 on {-1, 0, 1}.  Shapes cover the one-wave-per-row schedule (len <= 1024), the
-one-workgroup-per-row schedule (1024 < len <= 4096), the segmented look-back
-schedule (len > 4096), ragged and unaligned lengths.
+one-workgroup-per-row schedule (1024 < len <= 65536), the segmented look-back
+schedule (longer rows and small batches), ragged and unaligned lengths.
 Top-p: the cutoff equals the oracle's, or lies inside the tolerance band
 around p; dyadic rows (exact sums) must match exactly.
 """
@@ -76,6 +76,62 @@ def test_rows_tile_choice(ops, shape, excl):
     ye = to_host(ops.scan_rows_f32(to_dev(xe), exclusive=excl))
     assert_equal_first_diff(ye.astype(np.float64), oracle.scan_rows_f32(xe, exclusive=excl)[0],
                             f"rows f32 exact {shape}")
+
+
+def _wave_incl(a):
+    """The wavefront's inclusive scan over the last axis (64), in fp32: steps of 1,
+    2, 4 and 8 inside rows of 16 lanes, then the rows' ends."""
+    r = a.reshape(a.shape[:-1] + (4, 16))
+    for s in (1, 2, 4, 8):
+        o = np.zeros_like(r)
+        o[..., s:] = r[..., :-s]
+        r = r + o
+    r[..., 1, :] += r[..., 0, 15:]
+    r[..., 3, :] += r[..., 2, 15:]
+    r[..., 2:, :] += r[..., 1:2, 15:]
+    return r.reshape(a.shape)
+
+
+def _scan_tiles_of_8192(x):
+    """Row scans by tiles of 4 waves x 8 chunks of 64 lanes x 4, all sums in fp32 and
+    chained from chunk to chunk, wave to wave and tile to tile."""
+    rows = x.shape[0]
+    y = np.empty_like(x)
+    before = np.zeros(rows, np.float32)
+    for b in range(0, x.shape[1], 8192):
+        v = x[:, b:b + 8192].reshape(rows, 4, 8, 64, 4).copy()
+        for e in range(1, 4):
+            v[..., e] = v[..., e - 1] + v[..., e]
+        inc = _wave_incl(v[..., 3])
+        lane = np.zeros_like(inc)
+        lane[..., 1:] = inc[..., :-1]
+        run = np.zeros((rows, 4), np.float32)
+        for j in range(8):
+            v[:, :, j] = (run[..., None] + lane[:, :, j])[..., None] + v[:, :, j]
+            run = run + inc[:, :, j, 63]
+        waves = np.zeros(rows, np.float32)
+        for w in range(4):
+            v[:, w] = (before + waves)[:, None, None, None] + v[:, w]
+            waves = waves + run[:, w]
+        y[:, b:b + 8192] = v.reshape(rows, 8192)
+        before = before + waves
+    return y
+
+
+@pytest.mark.parametrize("seed", [1, 2])
+def test_rows_f32_whole_row_error(ops, seed):
+    """Rows of 65536 scanned whole by one workgroup are no further from 64-bit
+    sums than the same rows cut into tiles of 8192, although a wave adds up 16
+    chunks instead of 8.  (Whole rows wait for nothing: the sums are the same in
+    every run.)"""
+    announce("rows f32 error", seed)
+    x = (np.random.default_rng(seed).random((256, 65_536), dtype=np.float32) * 2 - 1)
+    ref = np.cumsum(x.astype(np.float64), axis=1)
+    tiles = np.linalg.norm(_scan_tiles_of_8192(x) - ref)
+    whole = np.linalg.norm(to_host(ops.scan_rows_f32(to_dev(x))) - ref)
+    print(f"[error] whole rows {whole / np.linalg.norm(ref):.3e}, tiles "
+          f"{tiles / np.linalg.norm(ref):.3e}", flush=True)
+    assert whole <= tiles
 
 
 def test_rows_inplace_and_empty(ops):
