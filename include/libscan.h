@@ -260,8 +260,8 @@ int split_by_flags_u32(const uint32_t* keys, const int32_t* idx_in, const uint8_
  * perm_out, keys_tmp, perm_tmp may overlap.  n <= INT32_MAX.  Workspace:
  * LIBSCAN_OP_RADIX_SORT with n and bits = bits_per_pass; the size reported for
  * 8 bits includes room for the count table of smaller tiles, which sorts of
- * 16385 to 2^22 - 1 keys use if it is there (the largest size reported for any
- * n' <= n serves n as well or better). */
+ * 16385 to 2^22 - 1 keys use if it is there (the size reported for n holds
+ * that of every smaller sort too). */
 int radix_sort_u32(const uint32_t* keys, uint32_t* keys_out, int32_t* perm_out, uint32_t* keys_tmp,
                    int32_t* perm_tmp, int64_t n, int bits_per_pass, void* ws, size_t ws_bytes,
                    void* stream);

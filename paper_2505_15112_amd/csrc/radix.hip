@@ -938,15 +938,31 @@ size_t radix_rows_ws_bytes(int64_t rows, int64_t len) {
 //         2^22:  52 / 54 / 58     2^23: 73 / 76 / 88
 // Rows follow their total: 4 x 200003 71 / 66 / 68, 30 x 32000 70 / 56 / 52,
 // 64 x 65536 96 / 91 / 105, 32 x 131072 93 / 94 / 109.
+constexpr int64_t kR8Small4 = int64_t(3) << 19;        // up to here 4 chunks
+constexpr int64_t kR8Small8 = (int64_t(1) << 22) - 1;  // up to here 8
 static int r8_chunks(int64_t rows, int64_t len) {
     const int64_t n = rows * len;
-    return n >= int64_t(1) << 22 ? 16 : (n > int64_t(3) << 19 ? 8 : 4);
+    return n > kR8Small8 ? 16 : (n > kR8Small4 ? 8 : 4);
 }
+// What a sort of any number of keys up to len (one row) or of any number of
+// such rows up to `rows` takes, not only of this size: smaller tiles have more
+// counts, and a workspace sized for the largest sort has room for them.
 size_t radix_rows_ws_want(int64_t rows, int64_t len) {
-    const size_t a = radix_rows_ws_bytes(rows, len);
-    if (rows == 0 || len <= kR8RowMax) return a;
-    const size_t b = radix8_ws_bytes(rows, len, r8_chunks(rows, len));
-    return a > b ? a : b;
+    size_t want = radix_rows_ws_bytes(rows, len);
+    if (rows == 0 || len <= kR8RowMax) return want;
+    if (rows > 1) {
+        const size_t one = radix_rows_ws_want(1, len);
+        want = one > want ? one : want;
+    }
+    for (int ch : {4, 8}) {
+        const int64_t most = ch == 4 ? kR8Small4 : kR8Small8;
+        const int64_t l = rows == 1 && len > most ? most : len;
+        const int64_t r = rows < most / l ? rows : most / l;
+        if (r == 0) continue;
+        const size_t b = radix8_ws_bytes(r, l, ch);
+        want = b > want ? b : want;
+    }
+    return want;
 }
 
 template <class K, int CH>

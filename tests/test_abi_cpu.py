@@ -251,6 +251,26 @@ def test_sort_rows_validation(lib):
     assert out.value >= 256 + 64 * 256 * 4 * ((1 << 17) // 8192)
 
 
+def test_sort_workspace_serves_smaller_sorts(lib):
+    """A workspace of the size reported for a sort holds what is reported for
+    every smaller one (small sorts use more, smaller tiles than large ones), over
+    the numbers of keys and, at each row length, over the numbers of rows."""
+    def size(op, n, rows=0, length=0):
+        out = ctypes.c_size_t(0)
+        assert lib.libscan_workspace_bytes(op, n, rows, length, 8, ctypes.byref(out)) == _lib.OK
+        return out.value
+
+    edges = [1 << 14, 3 << 19, 1 << 22, 1 << 23]
+    ns = sorted({max(1, e + d) for e in edges for d in (-8193, -1, 0, 1, 8193)} |
+                set(range(1000, 1 << 24, 99_991)))
+    sizes = [size(_lib.OP_RADIX_SORT, n) for n in ns]
+    assert sizes == sorted(sizes)
+    for length in (1000, 16_384, 16_385, 32_000, 65_536, 131_072, 200_003, 1 << 20, (3 << 19) + 1,
+                   (1 << 22) - 1, 1 << 22, (1 << 22) + 1):
+        sizes = [size(_lib.OP_SORT_ROWS, 0, rows, length) for rows in range(0, 300)]
+        assert sizes == sorted(sizes), length
+
+
 def test_weighted_sample_validation(lib):
     fn = lib.weighted_sample_f32
     TH, OUT = P(0x2000000), P(0x3000000)
