@@ -463,10 +463,13 @@ __global__ __launch_bounds__(kNucThreads) void k_nuc_pick(const uint16_t* hist, 
         double, moved(inc, std::integral_constant<int, 0x138>{}, std::integral_constant<int, 0xf>{}));
     __syncthreads();
     for (int q = 0; q < w; ++q) before += s_d[q];
-    // Should rounding in 32 bits (at most 64 additions deep: 4e-6 of the sum,
-    // all terms up to the crossing having one sign) lose a little, the running
-    // sum has still reached p where the bound reaches p (1 + 1e-5).
-    const double goal = (double)p + 1e-5 * (p < 0.f ? -(double)p : (double)p);
+    // The draw adds in 32 bits, each addition off by at most 2^-24 of a sum whose
+    // terms up to the crossing have one sign: fewer than 48 additions deep inside a
+    // tile and over the head tiles, one more for every step of 8192 behind them.
+    // Whatever these lose, its running sum has reached p where the bound is past
+    // p by as much (and as much again: 64 instead of 48, the steps of the whole row).
+    const double lost = (64 + len / 8192) * 0x1p-24;  // 1.1e-5 at 2^20 elements
+    const double goal = (double)p + lost * (p < 0.f ? -(double)p : (double)p);
     if (!s_nan) {
         double s = before;
         uint32_t n = UINT_MAX;
