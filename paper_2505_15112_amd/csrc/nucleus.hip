@@ -1002,11 +1002,12 @@ __global__ __launch_bounds__(kNucThreads) void k_nuc_sort_row(const uint32_t* x,
 
 static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
-// Tiles of 32768 positions when they occupy the chip, of 8192 otherwise (rows
-// of up to 40960 take the large ones always: a tile's counts have to fit the 4
-// bytes per element of scratch beside the list and the result).
+// Tiles of 32768 positions when they occupy the chip, of 8192 otherwise (us a call
+// at tiles of 32768 / 8192: 1 x 20000 44.6 / 36.9, 4 x 32000 47.1 / 37.4, 64 x 32000
+// 52.8 / 40.7, 150 x 40000 70.0 / 67.5); rows beyond 2^18 have too many small ones
+// for the tables (kNucMaxSegs).
 static uint32_t nucleus_tile(int64_t rows, int64_t len) {
-    return rows * len >= int64_t(256) * 32768 || len > (1 << 18) || len <= 40960 ? 32768u : 8192u;
+    return rows * len >= int64_t(256) * 32768 || len > (1 << 18) ? 32768u : 8192u;
 }
 // Elements per group: large groups read the list fewer times (four a row at
 // p = 0.9 over softmax rows, so that the two workgroups of every CU sort the
