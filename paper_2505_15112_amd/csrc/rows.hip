@@ -1005,6 +1005,16 @@ static void topp_long(bool vec, const float* probs, const int32_t* idx, const fl
                        len, segs, p, reinterpret_cast<WsHeader*>(ws), sums, arrivals);
 }
 
+// Draws on rows that no other path takes: of one tile of 4096, or of more than 2^20
+// elements, in tiles of 32768.
+template <ToppMode MODE>
+static void topp_draw(bool vec, const float* probs, const int32_t* idx, const float* theta,
+                      int32_t* cutoff, int32_t* token, int64_t rows, int64_t len, float p,
+                      void* ws, hipStream_t stream) {
+    auto go = len <= kRowTile ? topp_long<RGeomS, MODE> : topp_long<RGeomL, MODE>;
+    go(vec, probs, idx, theta, cutoff, token, rows, len, p, ws, stream);
+}
+
 // Rows of 2 to kEarlyMaxSegs tiles of 4096 take the early-exit cutoff kernels.
 static bool topp_early(int64_t len) {
     return len > kEarlyTile && (len + kEarlyTile - 1) / kEarlyTile <= kEarlyMaxSegs;
@@ -1013,8 +1023,11 @@ static size_t topp_early_ws_bytes(int64_t rows, int64_t len) {
     return kWsHeader + (size_t)rows * topp_heads(len) * 2 * sizeof(uint64_t);
 }
 
-static void topp_cutoff_early(bool vec, const float* probs, int32_t* cutoff, int64_t rows,
-                              int64_t len, float p, void* ws, hipStream_t stream) {
+// The cutoff, or (SAMPLE) the draw on sorted rows, by the early-exit kernels.
+template <bool SAMPLE>
+static void topp_early_rows(bool vec, const float* probs, const NucSource& src, const float* theta,
+                            int32_t* cutoff, int32_t* token, int64_t rows, int64_t len, float p,
+                            void* ws, hipStream_t stream) {
     using TV = RowTile<float, RGeomS, true>;
     using TU = RowTile<float, RGeomS, false>;
     static_assert(TV::kElems == kEarlyTile && TU::kElems == kEarlyTile, "early-exit tile");
@@ -1023,46 +1036,10 @@ static void topp_cutoff_early(bool vec, const float* probs, int32_t* cutoff, int
     auto kh = vec ? k_topp_head<TV, true> : k_topp_head<TU, false>;
     hipLaunchKernelGGL(kh, dim3((unsigned)(rows * heads)), dim3(vec ? TV::kThreads : TU::kThreads),
                        0, stream, probs, len, (uint32_t)rows, heads, words);
-    auto kf = vec ? k_topp_finish<true, false> : k_topp_finish<false, false>;
+    auto kf = vec ? k_topp_finish<true, SAMPLE> : k_topp_finish<false, SAMPLE>;
     hipLaunchKernelGGL(kf, dim3((unsigned)rows),
-                       dim3(vec ? kFinishThreads<true> : kFinishThreads<false>), 0,
-                       stream, probs, cutoff,
-                       len, heads, p, words, NucSource{}, nullptr, nullptr);
-}
-
-// The top-p draw on sorted rows by the same two kernels (rows as topp_early).
-static void topp_sample_early(bool vec, const float* sorted, const NucSource& src,
-                              const float* theta, int32_t* cutoff, int32_t* token, int64_t rows,
-                              int64_t len, float p, void* ws, hipStream_t stream) {
-    using TV = RowTile<float, RGeomS, true>;
-    using TU = RowTile<float, RGeomS, false>;
-    const uint32_t heads = topp_heads(len);
-    uint64_t* words = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(ws) + kWsHeader);
-    auto kh = vec ? k_topp_head<TV, true> : k_topp_head<TU, false>;
-    hipLaunchKernelGGL(kh, dim3((unsigned)(rows * heads)), dim3(vec ? TV::kThreads : TU::kThreads),
-                       0, stream, sorted, len, (uint32_t)rows, heads, words);
-    auto kf = vec ? k_topp_finish<true, true> : k_topp_finish<false, true>;
-    hipLaunchKernelGGL(kf, dim3((unsigned)rows),
-                       dim3(vec ? kFinishThreads<true> : kFinishThreads<false>), 0,
-                       stream, sorted, cutoff,
-                       len, heads, p, words, src, theta, token);
-}
-
-template <ToppMode MODE>
-static void topp_any(bool vec, const float* probs, const int32_t* idx, const float* theta,
-                     int32_t* cutoff, int32_t* token, int64_t rows, int64_t len, float p,
-                     void* ws, hipStream_t stream) {
-    if (MODE == ToppMode::Cutoff && topp_early(len)) {
-        topp_cutoff_early(vec, probs, cutoff, rows, len, p, ws, stream);
-        return;
-    }
-    const int64_t t = row_tile(len);
-    if (t == 32768)
-        topp_long<RGeomL, MODE>(vec, probs, idx, theta, cutoff, token, rows, len, p, ws, stream);
-    else if (t == 8192)
-        topp_long<RGeomM, MODE>(vec, probs, idx, theta, cutoff, token, rows, len, p, ws, stream);
-    else
-        topp_long<RGeomS, MODE>(vec, probs, idx, theta, cutoff, token, rows, len, p, ws, stream);
+                       dim3(vec ? kFinishThreads<true> : kFinishThreads<false>), 0, stream, probs,
+                       cutoff, len, heads, p, words, src, theta, token);
 }
 
 template <class T, bool TOPP>
@@ -1092,9 +1069,14 @@ static hipError_t rows_typed(bool exclusive, const T* x, T* y, int64_t rows, int
         hipLaunchKernelGGL(k, grid, block, 0, stream, x, y, rows, len, p, cutoff);
         return hipGetLastError();
     }
-    if constexpr (TOPP)
-        topp_any<ToppMode::Cutoff>(vec, x, nullptr, nullptr, cutoff, nullptr, rows, len, p, ws,
+    if constexpr (TOPP) {
+        if (topp_early(len))
+            topp_early_rows<false>(vec, x, NucSource{}, nullptr, cutoff, nullptr, rows, len, p, ws,
                                    stream);
+        else
+            topp_long<RGeomL, ToppMode::Cutoff>(vec, x, nullptr, nullptr, cutoff, nullptr, rows,
+                                                len, p, ws, stream);
+    }
     return hipGetLastError();
 }
 
@@ -1151,8 +1133,8 @@ hipError_t launch_weighted_sample(const float* w, const float* theta, int32_t* o
         else
             weighted_two<RGeomS>(vec, w, theta, out, rows, len, ws, stream);
     } else {
-        topp_any<ToppMode::Weighted>(vec, w, nullptr, theta, nullptr, out, rows, len, 0.f, ws,
-                                     stream);
+        topp_draw<ToppMode::Weighted>(vec, w, nullptr, theta, nullptr, out, rows, len, 0.f, ws,
+                                      stream);
     }
     return hipGetLastError();
 }
@@ -1173,12 +1155,7 @@ hipError_t launch_topp_draw_sorted(const float* sorted, const int32_t* idx, cons
         return hipGetLastError();
     }
     const bool vec = (len % 4 == 0) && aligned16(sorted);
-    if (len <= kRowTile)
-        topp_long<RGeomS, ToppMode::Sample>(vec, sorted, idx, theta, cutoff, token, rows, len, p,
-                                            ws, stream);
-    else
-        topp_long<RGeomL, ToppMode::Sample>(vec, sorted, idx, theta, cutoff, token, rows, len, p,
-                                            ws, stream);
+    topp_draw<ToppMode::Sample>(vec, sorted, idx, theta, cutoff, token, rows, len, p, ws, stream);
     return hipGetLastError();
 }
 
@@ -1211,8 +1188,8 @@ hipError_t launch_topp_sample(const float* probs, const float* theta, float p, i
         const hipError_t e = launch_nucleus_sort(
             probs, p, heads, rows, len, scratch, topp_sample_scratch_bytes(rows, len), &src, stream);
         if (e != hipSuccess) return e;
-        topp_sample_early(len % 4 == 0, reinterpret_cast<const float*>(scratch), src, theta, cutoff,
-                          token, rows, len, p, ws, stream);
+        topp_early_rows<true>(len % 4 == 0, reinterpret_cast<const float*>(scratch), src, theta,
+                              cutoff, token, rows, len, p, ws, stream);
         return hipGetLastError();
     }
     const size_t mb = align256((size_t)rows * (size_t)len * 4);
