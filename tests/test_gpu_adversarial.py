@@ -97,11 +97,12 @@ def test_scans_mid_sizes(ops, adversarial, n):
 
 
 @pytest.mark.skipif(not FULL, reason="full-size cases disabled")
-def test_lds_tiles(ops, adversarial):
-    """The register + LDS tiles (n >= 2^27), ragged last tile, with carries."""
+@pytest.mark.parametrize("n", [102400 * 205 + 80000, (1 << 27) + 12345, 114688 * 2341 + 100000])
+def test_lds_tiles(ops, adversarial, n):
+    """The register + LDS tiles (102400, 81920 and, from 2^28 elements on, 114688
+    elements), ragged last tile, with carries."""
     import torch
-    announce("adversarial lds tiles")
-    n = (1 << 27) + 12345
+    announce("adversarial lds tiles", n)
     x = W.scan_i32_full_range(n, seed=61)
     carry = torch.tensor([7], dtype=torch.int32, device="cuda")
     y, _ = ops.scan_exclusive_i32_carry(to_dev(x), carry_in=carry, total_out=carry)

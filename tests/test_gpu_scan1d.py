@@ -189,49 +189,51 @@ def test_large_tiles_ragged(ops, kind, excl, shift):
         assert int(to_host(total)[0]) == rtot
 
 
-# Register + LDS tiles (n >= 2^27, 16-byte aligned 32-bit data): 114688-element
-# integer tiles and 102400-element float tiles; a ragged last tile is scanned
-# in passes of 65536.  Sizes: ragged last tiles of one pass (2^27 for integers,
-# a last tile of one element) and of two (2^27 for floats, 100000 elements
-# past a multiple of the integer tile), and an exact multiple of each tile
-# (the last full tile writes the total).
-LDS_I32_TILE, LDS_F32_TILE = 114688, 102400
-LDS_SIZES = [1 << 27, LDS_I32_TILE * 1170 + 100000, LDS_I32_TILE * 1171,
-             LDS_I32_TILE * 1171 + 1, LDS_F32_TILE * 1311, LDS_F32_TILE * 1311 + 1]
+# Register + LDS tiles (16-byte aligned 32-bit data): 81920 elements (16 + 4 chunks
+# a wave) and 102400 (16 + 9) below 2^28 elements, by how they fill the CUs, and
+# from 2^28 on 114688 (integers, 19 + 9) or 102400 (floats).  A ragged last tile
+# is scanned in passes of 65536.  For each tile an exact multiple (the last full
+# tile writes the total), a last tile of one element, and one of two passes;
+# 2^28: a last tile of one pass for both types.
+LDS_SIZES = [81920 * 205 + d for d in (0, 1, 70000)] + \
+            [102400 * 205 + d for d in (0, 1, 80000)] + [1 << 28] + \
+            [114688 * 2341 + d for d in (0, 1, 100000)] + \
+            [102400 * 2622 + d for d in (0, 1, 100000)]
 
 
 @pytest.mark.skipif(not FULL, reason="full-size cases disabled")
 @pytest.mark.parametrize("n", LDS_SIZES)
-@pytest.mark.parametrize("excl", [False, True])
-def test_lds_tiles_i32(ops, n, excl):
-    """int32 through the large-array kernel, with carry_in and total_out."""
+def test_lds_tiles_i32(ops, n):
+    """int32 through the register + LDS tiles, with carry_in and total_out."""
     import torch
-    announce("lds tiles i32", n, excl)
-    x = W.scan_i32_full_range(n, seed=31)
-    carry = torch.tensor([-123456789], dtype=torch.int32, device="cuda")
-    fn = ops.scan_exclusive_i32_carry if excl else ops.scan_inclusive_i32_carry
-    y, _ = fn(to_dev(x), carry_in=carry, total_out=carry)
-    ref = (oracle.scan_i32(x, exclusive=excl).astype(np.int64) - 123456789).astype(np.int32)
-    assert_equal_first_diff(to_host(y), ref, f"lds i32 n={n}")
-    tot = (int(oracle.scan_i32(x)[-1]) - 123456789 + 2**31) % 2**32 - 2**31
-    assert int(to_host(carry)[0]) == tot
+    announce("lds tiles i32", n)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randint(-2**31, 2**31, (n,), dtype=torch.int32, device="cuda", generator=g)
+    incl = torch.cumsum(x, 0, dtype=torch.int32) - 123456789  # wraps
+    for fn, want in ((ops.scan_inclusive_i32_carry, incl), (ops.scan_exclusive_i32_carry, incl - x)):
+        carry = torch.tensor([-123456789], dtype=torch.int32, device="cuda")
+        y, _ = fn(x, carry_in=carry, total_out=carry)
+        assert torch.equal(y, want), n
+        assert int(carry[0]) == int(incl[-1]), n
 
 
 @pytest.mark.skipif(not FULL, reason="full-size cases disabled")
 @pytest.mark.parametrize("n", LDS_SIZES)
-@pytest.mark.parametrize("excl", [False, True])
-def test_lds_tiles_f32(ops, n, excl):
-    """fp32 through the large-array kernel: bit-exact on {-1, 0, 1} inputs
+def test_lds_tiles_f32(ops, n):
+    """fp32 through the register + LDS tiles: bit-exact on {-1, 0, 1} inputs
     with an exact carry_in, and the total."""
     import torch
-    announce("lds tiles f32", n, excl)
-    x = W.exact_pm1(n, seed=32)
-    cf = torch.tensor([0.5], dtype=torch.float32, device="cuda")
-    fn = ops.scan_exclusive_f32_carry if excl else ops.scan_inclusive_f32_carry
-    y, _ = fn(to_dev(x), carry_in=cf, total_out=cf)
-    ref, _ = oracle.scan_f32(x, exclusive=excl)
-    assert_equal_first_diff(to_host(y).astype(np.float64), ref + 0.5, f"lds f32 n={n}")
-    assert float(to_host(cf)[0]) == float(np.sum(x.astype(np.float64))) + 0.5
+    announce("lds tiles f32", n)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    xi = torch.randint(-1, 2, (n,), dtype=torch.int32, device="cuda", generator=g)
+    incl = torch.cumsum(xi, 0, dtype=torch.int32)
+    assert int(incl.abs().max()) < 1 << 22  # a random walk: sums and halves are exact
+    x = xi.float()
+    for fn, want in ((ops.scan_inclusive_f32_carry, incl), (ops.scan_exclusive_f32_carry, incl - xi)):
+        cf = torch.tensor([0.5], dtype=torch.float32, device="cuda")
+        y, _ = fn(x, carry_in=cf, total_out=cf)
+        assert torch.equal(y, want.float() + 0.5), n
+        assert float(cf[0]) == float(incl[-1]) + 0.5, n
 
 
 # The matrix-core tile scan (row scans as A * U_32 on MFMA, ScanU): whole
