@@ -657,6 +657,67 @@ __device__ int64_t topp_head_find(const float* xr, int64_t len, const uint64_t* 
     return -1;
 }
 
+// The index of the element of rank `need` (from 0, by index) among those of the row
+// with these bits (0 if there are fewer).  The whole workgroup; s_t: 1024 words of
+// LDS.  Reads the row up to there in order, 16 bytes a load.
+template <int kThreads>
+__device__ __forceinline__ int32_t topp_nth_equal(const uint32_t* xr, uint32_t len, uint32_t bits,
+                                                  uint32_t need, uint32_t* s_t) {
+    constexpr uint32_t kLoads = 12, kChunk = kLoads * 4 * kThreads, kWaves = kThreads / kWave;
+    constexpr uint32_t kMaxChunks = ((1u << 20) + kChunk - 1) / kChunk;
+    static_assert(kMaxChunks + kLoads * kWaves + 1 <= 1024, "a word per chunk, then per load and wave");
+    const uint32_t t = threadIdx.x, w = t / kWave;
+    __syncthreads();
+    for (uint32_t i = t; i < 1024; i += kThreads) s_t[i] = 0;
+    __syncthreads();
+    for (uint32_t k = 0, b = 0; b < len; ++k, b += kChunk) {  // rows of up to 2^20
+        uint64_t eq = 0;  // bit 4 q + e
+#pragma unroll
+        for (uint32_t q = 0; q < kLoads; ++q) {
+            const uint32_t i = b + (q * kThreads + t) * 4;
+            u32x4_a4 v = {~bits, ~bits, ~bits, ~bits};
+            if (i + 4 <= len) {
+                v = *reinterpret_cast<const u32x4_a4*>(xr + i);
+            } else {
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e)
+                    if (i + e < len) v[e] = xr[i + e];
+            }
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e) eq |= (uint64_t)(v[e] == bits ? 1u : 0u) << (4 * q + e);
+        }
+        const uint32_t in_wave = wave_sum((uint32_t)__builtin_popcountll(eq));
+        if (lane_id() == 0 && in_wave) atomicAdd(&s_t[k], in_wave);
+        __syncthreads();
+        const uint32_t here = s_t[k];
+        if (need >= here) {  // uniform
+            need -= here;
+            continue;
+        }
+        // per load and wave, in the order of the elements
+        uint32_t* s_w = s_t + kMaxChunks;
+        uint32_t* s_at = s_w + kLoads * kWaves;
+#pragma unroll
+        for (uint32_t q = 0; q < kLoads; ++q) {
+            const uint32_t c = wave_sum((uint32_t)__builtin_popcount((uint32_t)(eq >> (4 * q)) & 15u));
+            if (lane_id() == 0) s_w[q * kWaves + w] = c;
+        }
+        __syncthreads();
+        uint32_t g = 0;
+        for (; g + 1 < kLoads * kWaves && need >= s_w[g]; ++g) need -= s_w[g];
+        const uint32_t q = g / kWaves;
+        uint32_t mine = (uint32_t)(eq >> (4 * q)) & 15u;
+        const uint32_t c = (uint32_t)__builtin_popcount(mine), inc = wave_incl_scan(c);
+        if (w == g % kWaves && inc - c <= need && need < inc) {  // one thread
+            for (uint32_t left = need - (inc - c); left != 0; --left) mine &= mine - 1;
+            *s_at = b + (q * kThreads + t) * 4 + (uint32_t)__builtin_ctz(mine);
+        }
+        __syncthreads();
+        return (int32_t)*s_at;
+    }
+    return 0;
+}
+
 // Source index of the element at position j of a row's sorted elements: of the
 // elements of that value the one with as many before it, by index, as the
 // sorted row has equal ones before j.  Equal keys are in one group, so only that
@@ -746,43 +807,18 @@ __device__ __forceinline__ int32_t topp_token(const NucSource& src, uint32_t row
         __syncthreads();
         return (int32_t)(equal > 1 ? s_c[1] : s_t[0]);
     }
-    // many: how many equal elements precede j (a search for the first of them
-    // in the sorted row), then the index of that rank (below 2^20), 10 bits at
-    // a time
-    uint32_t lo = 0, hi = j;
-    while (lo < hi) {  // uniform
-        const uint32_t mid = (lo + hi) / 2;
-        if (nuc_key(Bits<float>::to(sorted[mid])) > key) lo = mid + 1; else hi = mid;
+    // many: how many equal elements precede j (the first of them is searched in the
+    // sorted row, kThreads places a round), then the one of that rank in the row
+    // itself, which holds them in the order of their indices
+    uint32_t lo = first, hi = j;
+    while (lo < hi) {  // uniform; [first, lo) is larger, hi is not
+        const uint32_t at = lo + (uint32_t)((uint64_t)(hi - lo) * t / kThreads);
+        const uint32_t c = (uint32_t)__syncthreads_count(nuc_key(Bits<float>::to(sorted[at])) > key);
+        const uint32_t span = hi - lo;
+        if (c < (uint32_t)kThreads) hi = lo + (uint32_t)((uint64_t)span * c / kThreads);
+        if (c > 0) lo += (uint32_t)((uint64_t)span * (c - 1) / kThreads) + 1;
     }
-    uint32_t need = j - lo, prefix = 0;
-    for (int sh = 10; sh >= 0; sh -= 10) {
-        __syncthreads();
-        for (uint32_t i = t; i < 1024; i += kThreads) s_t[i] = 0;
-        __syncthreads();
-        each(
-            [&](uint32_t i) {
-                const uint32_t s = source(i);
-                if (sh == 10 || (s >> 10) == prefix) atomicAdd(&s_t[(s >> sh) & 1023u], 1u);
-            },
-            [] { return false; });
-        __syncthreads();
-        if (t < kWave) {  // lane t: counts 16 t .. 16 t + 15
-            uint32_t c = 0;
-            for (int i = 0; i < 16; ++i) c += s_t[16 * t + i];
-            const uint32_t inc = wave_incl_scan(c);
-            uint32_t left = need - (inc - c);
-            if (inc - c <= need && need < inc) {  // one lane
-                uint32_t i = 16 * t;
-                while (left >= s_t[i]) left -= s_t[i++];
-                s_c[0] = i;
-                s_c[1] = left;
-            }
-        }
-        __syncthreads();
-        prefix = (prefix << 10) | s_c[0];
-        need = s_c[1];
-    }
-    return (int32_t)prefix;
+    return topp_nth_equal<kThreads>(xr, (uint32_t)len, nuc_bits(key), j - lo, s_t);
 }
 
 // The cutoff k (len - 1 when no running sum reaches p); SAMPLE: the top-p
