@@ -26,10 +26,15 @@
 //
 // Bound: two reads of the rows from HBM (22 us for 128 x 131072) and the LDS
 // work of the sort.  Kernel times at 128 x 131072, p = 0.9 (about 38000
-// elements of each row gathered): histogram 19 us, pick 9, gather 27 (105 MB
-// moved), sort 25, and the draw 5 + 9; the call 272 us by the row sort, 94 us
-// this way.  4 x 200003: 93 -> 42 us, each of the six kernels a few us of
-// latency.  Measured on the way: the elements scattered to their bins by LDS
+// elements of each row gathered): histogram 20 us, pick 9, gather 27 (105 MB
+// moved), sort 24, and the draw 5 + 9; the call 272 us by the row sort, 92 us
+// this way.  4 x 200003: 93 -> 43 us, each of the six kernels a few us of
+// latency.  Rows whose elements crowd at few values cost more (128 x 131072 equal
+// 166 us, flat rows with a tenth of zeros 190 to 290), but hardly ever more than
+// the row sort and the draw on it (300 to 390): up to 1.15 times, and 1 x 2^20 with
+// 99 % zeros sorted to its end 147 us for 100.  Only rows in which a structure that
+// follows the 512 places of the sample hides most elements from it take 3 to 50
+// times as long (windows, see nuc_window).  Measured on the way: the elements scattered to their bins by LDS
 // counters instead of gathered (one 8-byte store per lane and line): 62 us for
 // the scatter; a workgroup for every group a row could have, most of them
 // without work: 9 ns each, 26 us.
@@ -52,7 +57,7 @@ static_assert(kNucSlots % (2 * kNucThreads) == 0, "whole words per thread");
 constexpr int64_t kNucMaxLen = int64_t(1) << 20;
 constexpr uint32_t kNucMinGroup = 4096;
 constexpr uint32_t kNucMaxGroups = 1024;  // table room in LDS
-static_assert(kNucMaxLen / kNucMinGroup <= kNucMaxGroups, "a row's groups fit the tables");
+static_assert(kNucMaxLen / kNucMinGroup * 2 <= kNucMaxGroups, "a row's groups fit the tables");
 constexpr uint16_t kNucNoGroup = 0xFFFF;
 constexpr uint32_t kNucMaxSegs = 40;  // 2^20 + 3 positions of 32768, 2^18 + 3 of 8192: 33
 // The last two bins are in no map (see k_nuc_hist): the elements above the
@@ -94,6 +99,15 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* s_w, u
     const int wu = __builtin_amdgcn_readfirstlane(w);
     *total = lane_read(sc, kNucWaves - 1);
     return (wu > 0 ? lane_read(sc, wu - 1) : 0u) + inc - v;
+}
+
+// One more in LDS counter c[i], for the active lanes: those with the first one's
+// i by one addition.  (Crowds again: 64 lanes on one counter take their turns.)
+__device__ __forceinline__ void nuc_count(uint32_t* c, uint32_t i) {
+    const bool with = i == uni(i);
+    const uint64_t same = __ballot(with);
+    if (!with || lanes_below(same) == 0)
+        atomicAdd(&c[i], with ? (uint32_t)__builtin_popcountll(same) : 1u);
 }
 
 // ---------------------------------------------------------------- the row's elements
@@ -260,7 +274,8 @@ __global__ __launch_bounds__(kNucThreads) LS_OCCUPANCY8 void k_nuc_hist(
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const uint32_t s = s_map[2 * t + i];
-        if ((uint64_t)s * (uint32_t)len > (uint64_t)kNucSample * fine) s_dense = 1;
+        if ((uint64_t)s * (uint32_t)len > (uint64_t)kNucSample * fine) atomicMax(&s_dense, 1u);
+        if (s > kNucSample / 4) atomicMax(&s_dense, 2u);
         const uint32_t b = s > 2 ? 32u - (uint32_t)__builtin_clz((s + 1) / 2 - 1) : 0u;
         sub[i] = b < shift ? b : shift;
     }
@@ -277,7 +292,7 @@ __global__ __launch_bounds__(kNucThreads) LS_OCCUPANCY8 void k_nuc_hist(
     s_map[2 * t + 1] = (first + n[0]) | sub[1] << 16;
     __syncthreads();
     int32_t top = 0;
-    auto count = [&](auto bin_of) {
+    auto count = [&](auto bin_of, auto add) {
         tile.each([&](uint32_t b, uint32_t, bool ok) {
             if (!ok) return;
             top = top > (int32_t)b ? top : (int32_t)b;
@@ -285,18 +300,23 @@ __global__ __launch_bounds__(kNucThreads) LS_OCCUPANCY8 void k_nuc_hist(
             const bool over = k > hi;
             if (over) atomicAdd(&s_above, (double)Bits<float>::from(b));
             const uint32_t bin = bin_of(k > lo ? k - lo : 0u);
-            atomicAdd(&s_h[over ? kNucAbove : bin], 1u);
+            add(over ? kNucAbove : bin);
         });
     };
+    auto one = [&](uint32_t bin) { atomicAdd(&s_h[bin], 1u); };
     // keys above hi index no cell: the bin they would get is not used
+    auto cell = [&](uint32_t d) { return d >> shift; };
+    auto mapped = [&](uint32_t d) {
+        const uint32_t c = d >> shift;
+        const uint32_t e = s_map[c < kNucCells ? c : kNucCells - 1];
+        return (e & 0xFFFFu) + ((d & ((1u << shift) - 1u)) >> (shift - (e >> 16)));
+    };
     if (direct)
-        count([&](uint32_t d) { return d >> shift; });
-    else
-        count([&](uint32_t d) {
-            const uint32_t c = d >> shift;
-            const uint32_t e = s_map[c < kNucCells ? c : kNucCells - 1];
-            return (e & 0xFFFFu) + ((d & ((1u << shift) - 1u)) >> (shift - (e >> 16)));
-        });
+        count(cell, one);
+    else if (s_dense == 1)
+        count(mapped, one);
+    else  // much of the row in one cell
+        count(mapped, [&](uint32_t bin) { nuc_count(s_h, bin); });
     if (top > 0x7F800000) s_h[kNucNan] = 1;  // every such thread stores the same
     if (seg == 0) {
         uint32_t* m = maps + (int64_t)row * kNucCells;
@@ -482,12 +502,17 @@ __global__ __launch_bounds__(kNucThreads) void k_nuc_pick(const uint16_t* hist, 
     }
     __syncthreads();
     const uint32_t need = s_need;
-    // the bins that start before `need` are sorted; those that start in one
-    // window of the sorted row are a group
+    // The bins that start before `need` are sorted; those that start in one window
+    // of the sorted row are a group, but one of more elements than a window is a
+    // group of its own (the next bin then starts in a later window): mostly it is a
+    // crowd of few values, which k_nuc_sort handles best alone.
+    auto group_of = [&](uint32_t first, uint32_t count) {
+        return first / window * 2 + (count > window ? 1u : 0u);
+    };
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         if (cnt[i] && start[i] < need) {
-            const uint32_t g = start[i] / window;
+            const uint32_t g = group_of(start[i], cnt[i]);
             atomicMin(&s_g[g], start[i]);
             atomicMin(&s_low[g], low[i]);
             if (start[i] + cnt[i] >= need) {  // the last one
@@ -519,7 +544,7 @@ __global__ __launch_bounds__(kNucThreads) void k_nuc_pick(const uint16_t* hist, 
     uint16_t bg[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        bg[3 - i] = cnt[i] && start[i] < need ? (uint16_t)s_id[start[i] / window] : kNucNoGroup;
+        bg[3 - i] = cnt[i] && start[i] < need ? (uint16_t)s_id[group_of(start[i], cnt[i])] : kNucNoGroup;
     reinterpret_cast<ushort4*>(bin_groups + row * kNucBins)[b0 / 4] =
         make_ushort4(bg[0], bg[1], bg[2], bg[3]);
 }
@@ -810,28 +835,49 @@ __device__ __forceinline__ void nuc_range(const uint32_t (&key)[kNucPer], uint32
     *hi = uni(mx);
 }
 
+// f(key) for the m keys at `keys` (4-byte aligned; up to 3 words after them may be
+// read): 16-byte loads, three in flight a thread.
+template <class F>
+__device__ __forceinline__ void nuc_each(const uint32_t* keys, uint32_t m, F f) {
+    const uint32_t t4 = nuc_thread() * 4;
+    constexpr uint32_t kLoads = 3, kStep = 4 * kNucThreads;
+    uint32_t b = 0;
+#pragma unroll 1
+    for (; b + kLoads * kStep <= m; b += kLoads * kStep) {
+        const uint32_t* kb = keys + b;  // uniform
+        u32x4_a4 v[kLoads];
+#pragma unroll
+        for (uint32_t q = 0; q < kLoads; ++q)
+            v[q] = *reinterpret_cast<const u32x4_a4*>(kb + (q * kStep + t4));
+#pragma unroll
+        for (uint32_t q = 0; q < kLoads; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) f(v[q][e]);
+    }
+#pragma unroll 1
+    for (uint32_t i = b + t4; i < m; i += kStep) {
+        const u32x4_a4 v = *reinterpret_cast<const u32x4_a4*>(keys + i);
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e)
+            if (i + e < m) f(v[e]);
+    }
+}
+
 // A group too large for LDS (a bin of many elements: most of them equal, or so
 // close together that the sample's map did not part them) is sorted in windows
-// of at most kNucGroupMax keys from the top down.  nuc_window finds the next
-// one among the m keys at lk in [floor, cap]: keys in [*from, *hi]; *fits 0:
-// the key *hi alone, more often than that.  The keys left are
-// counted in at most 4096 equal parts of their range; the parts from the top
-// that fit together are the window, and a first part that does not fit is cut
-// up again.
-__device__ void nuc_window(const uint32_t* lk, uint32_t m, uint32_t floor, uint32_t cap,
-                           uint32_t* from, uint32_t* hi, uint32_t* fits, uint32_t* s_v,
-                           NucSortLds& L) {
-    const uint32_t t = nuc_thread();
-    constexpr uint32_t kParts = 4096;
-    static_assert(kParts <= kNucSlots / 2, "parts fit the slots");
+// of at most kNucGroupMax keys from the top down, until those left are few
+// values.  nuc_limits: the least and the largest of the m keys at lk that are at
+// most cap (least > largest: none).
+__device__ void nuc_limits(const uint32_t* lk, uint32_t m, uint32_t cap, uint32_t* lo,
+                           uint32_t* hi, uint32_t* s_v) {
     uint32_t mn = 0xFFFFFFFFu, mx = 0u;
-    for (uint32_t i = t; i < m; i += kNucThreads) {
-        const uint32_t k = lk[i];
-        if (k >= floor && k <= cap) {
+    nuc_each(lk, m, [&](uint32_t k) {
+        if (k <= cap) {
             mn = k < mn ? k : mn;
             mx = k > mx ? k : mx;
         }
-    }
+    });
+    const uint32_t t = nuc_thread();
     __syncthreads();
     if (t < 2) s_v[t] = t - 1u;  // the largest value, 0
     __syncthreads();
@@ -842,20 +888,91 @@ __device__ void nuc_window(const uint32_t* lk, uint32_t m, uint32_t floor, uint3
         atomicMax(&s_v[1], mx);
     }
     __syncthreads();
-    uint32_t lo = uni(s_v[0]);
-    const uint32_t top = uni(s_v[1]);
+    *lo = uni(s_v[0]);
+    *hi = uni(s_v[1]);
+}
+
+constexpr uint32_t kNucParts = 4096;
+static_assert(kNucParts <= kNucSlots / 2 && kNucParts == 4 * kNucThreads, "four parts a thread");
+
+// Keys of fewer than kNucParts values, [lo, hi], in descending order to out[0,
+// room): each value is counted and written as often as it is there.  The other
+// keys of lk[0, m) are above hi; `room` are not.  (Crowds
+// are what makes large groups: equal elements, masked zeros, flat rows.  In
+// windows, three reads of the list each, the call on softmax of N(0, 10^-5) with a
+// tenth of the row zero took 31.4 ms at 1 x 2^20 and 1.37 ms at 128 x 131072, now
+// 0.43 and 0.23.)
+__device__ void nuc_emit(const uint32_t* lk, uint32_t m, uint32_t lo, uint32_t hi, uint32_t* out,
+                         uint32_t room, NucSortLds& L) {
+    const uint32_t range = hi - lo;
+    if (range == 0) {
+        for (uint32_t i = nuc_thread(); i < room; i += kNucThreads) out[i] = nuc_bits(hi);
+        return;
+    }
+    uint32_t* own = L.slot + 4 * nuc_thread();
+    __syncthreads();  // L free
+#pragma unroll
+    for (int i = 0; i < 4; ++i) own[i] = 0;
+    __syncthreads();
+    nuc_each(lk, m, [&](uint32_t k) {
+        const uint32_t d = hi - k;
+        if (d <= range) nuc_count(L.slot, d);
+    });
+    __syncthreads();
+    own = L.slot + 4 * nuc_thread();
+    uint32_t total;
+    uint32_t at = block_excl_scan(own[0] + own[1] + own[2] + own[3], L.w, &total);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t c = own[i];
+        own[i] = at;
+        at += c;
+    }
+    __syncthreads();
+    total = uni(total);
+    if (total > room) return;  // uniform; only when the row was rewritten while the call ran
+    // short runs one wave each, 64 values a round; long ones the workgroup
+    constexpr uint32_t kLong = 1024;
+    const uint32_t w = uni(nuc_thread() / kWave);
+#pragma unroll 1
+    for (uint32_t b = 0; b <= range; b += kWave) {
+        const uint32_t p = b + lane_id();
+        const uint32_t first = L.slot[p], last = p + 1 < kNucParts ? L.slot[p + 1] : total;
+        const uint64_t longer = __ballot(last - first > kLong), some = __ballot(last > first);
+        const bool mine = b / kWave % kNucWaves == w;
+#pragma unroll 1
+        for (uint64_t runs = mine ? some : longer; runs != 0; runs &= runs - 1) {
+            const int l = __builtin_ctzll(runs);
+            const bool all = (longer >> l) & 1;
+            const uint32_t n = lane_read(last, l) - lane_read(first, l), step = all ? kNucThreads : kWave;
+            uint32_t* o = out + lane_read(first, l);
+            const uint32_t v = nuc_bits(hi - (b + l));
+#pragma unroll 1
+            for (uint32_t i = all ? nuc_thread() : lane_id(); i < n; i += step) o[i] = v;
+        }
+    }
+}
+
+// The next window of the m keys at lk, those in [lo, top] left (kNucParts values
+// or more): keys in [*from, *hi]; *fits 0: the key *hi alone, more often than
+// that.  The keys left are counted in at most kNucParts equal parts of their range;
+// the parts from the top that fit together are the window, and a first part that
+// does not fit is cut up again.
+__device__ void nuc_window(const uint32_t* lk, uint32_t m, uint32_t lo, uint32_t top,
+                           uint32_t* from, uint32_t* hi, uint32_t* fits, uint32_t* s_v,
+                           NucSortLds& L) {
+    const uint32_t t = nuc_thread();
     while (true) {  // the range [lo, top] gets 4096 times smaller each time
         const uint32_t range = top - lo;
         const int bits = range ? 32 - __builtin_clz(range) : 0;
         const uint32_t sh = bits > 12 ? (uint32_t)(bits - 12) : 0u;
         __syncthreads();
-        for (uint32_t i = t; i < kParts; i += kNucThreads) L.slot[i] = 0;
+        for (uint32_t i = t; i < kNucParts; i += kNucThreads) L.slot[i] = 0;
         if (t < 2) s_v[2 + t] = 0;
         __syncthreads();
-        for (uint32_t i = t; i < m; i += kNucThreads) {
-            const uint32_t k = lk[i];
-            if (k >= lo && k <= top) atomicAdd(&L.slot[(top - k) >> sh], 1u);
-        }
+        nuc_each(lk, m, [&](uint32_t k) {
+            if (k >= lo && k <= top) nuc_count(L.slot, (top - k) >> sh);
+        });
         __syncthreads();
         uint32_t total;
         uint32_t inc = block_excl_scan(L.slot[4 * t] + L.slot[4 * t + 1] + L.slot[4 * t + 2] +
@@ -954,7 +1071,14 @@ __global__ __launch_bounds__(kNucThreads) LS_OCCUPANCY8 void k_nuc_sort(
             const bool big = m > kNucGroupMax;
             uint32_t from, hi, fits = 1, n = m;
             if (big) {
-                nuc_window(lk, m, 0u, cap, &from, &hi, &fits, s_v, L);
+                uint32_t least, largest;
+                nuc_limits(lk, m, cap, &least, &largest, s_v);
+                if (least > largest) return;  // uniform; as below
+                if (largest - least < kNucParts) {
+                    nuc_emit(lk, m, least, largest, out + a, m - a, L);
+                    break;
+                }
+                nuc_window(lk, m, least, largest, &from, &hi, &fits, s_v, L);
                 n = nuc_select(lk, m, from, hi, s_v, L);
                 // only when the row was rewritten while the call ran, so that the
                 // list and the histogram disagree; the loop ends all the same
@@ -1033,7 +1157,7 @@ static NucLayout nucleus_layout(int64_t rows, int64_t len) {
     // rows that start off 16-byte boundaries: up to 3 positions before them
     l.segs = (uint32_t)((len + 3 + tile - 1) / tile);
     l.window = nucleus_window(rows, len);
-    l.slots = (uint32_t)((len + l.window - 1) / l.window);  // the most groups a row can have
+    l.slots = (uint32_t)((len + l.window - 1) / l.window) * 2;  // the most groups a row can have
     l.stride = (uint32_t)((len + 3) / 4 * 4);
     const size_t tiles = (size_t)rows * l.segs;
     l.idx = l.keys + align256((size_t)rows * l.stride * 4);

@@ -356,7 +356,9 @@ def _check_as_sorted(ops, x, theta, p, what):
 def _crowded_rows(kind, rows, length, seed):
     """Probabilities far from evenly spread over their range: flat rows (keys a
     few hundred or thousand apart) with one large element or a share of zeros,
-    rows mostly zero, rows of one value, few values, and values at three scales."""
+    rows mostly zero, rows of one value, few values, values at three scales, and
+    rows whose values the sampler's sample misses (4 elements in each of 512
+    places, zeros here), a fifth of them equal."""
     import torch
     g = torch.Generator(device="cuda").manual_seed(seed)
     z = torch.randn((rows, length), device="cuda", generator=g)
@@ -376,14 +378,20 @@ def _crowded_rows(kind, rows, length, seed):
         return torch.softmax(2 * z, 1)
     if kind == "bf16":
         return torch.softmax(2 * z, 1).bfloat16().float()
+    if kind == "hidden":
+        x = torch.softmax(2 * z, 1).masked_fill(u < 0.2, 1.0 / length)
+        at = torch.arange(512, device="cuda") * (length - 4) // 511
+        x[:, (at[:, None] + torch.arange(4, device="cuda")).flatten()] = 0.0
+        return x
     x = torch.softmax(1e-6 * z, 1) * 0.5  # scales
     x = torch.where(u < 0.3, x * 1e-20, x)
     return torch.where(u > 0.9, torch.softmax(z, 1), x).contiguous()
 
 
 @pytest.mark.parametrize("length", [4097, 8192, 12_288, 12_289, 131_072])
-@pytest.mark.parametrize("kind", ["spike.1", "spike.001", "mask.1", "mask.001", "mask.000001",
-                                  "rare", "equal", "scales"])
+@pytest.mark.parametrize("kind", ["spike.1", "spike.001", "spike.000001", "mask.1", "mask.001",
+                                  "mask.00001", "mask.000001", "rare", "equal", "scales",
+                                  "hidden"])
 def test_topp_sample_crowded(ops, length, kind):
     """Rows whose keys crowd in a small part of their range, on both sides of the
     row length up to which one workgroup sorts a row whole."""
@@ -440,23 +448,24 @@ def _best_us(f, batches=8, calls=3):
     return best
 
 
-@pytest.mark.parametrize("length", [40_000, 262_145, 1 << 20])
-@pytest.mark.parametrize("kind", ["soft", "flat", "bf16", "scales"])
-def test_topp_sample_many_groups(ops, length, kind):
-    """Long rows sorted to their end: many groups a row, each with its own part
-    of the row's list, and the token looked up in the draw's group."""
+@pytest.mark.parametrize("rows,length", [(3, 40_000), (3, 262_145), (3, 1 << 20), (70, 262_145)])
+@pytest.mark.parametrize("kind", ["soft", "flat", "bf16", "scales", "hidden", "mask.00001"])
+def test_topp_sample_many_groups(ops, rows, length, kind):
+    """Long rows sorted to their end: many groups a row (of 4096 elements, and from
+    2^23 elements on of 11264), each with its own part of the row's list, and the
+    token looked up in the draw's group; groups too large for LDS, of few values
+    and of many."""
     import torch
-    announce("topp many groups", length, kind)
-    rows = 3
+    announce("topp many groups", length, kind, rows)
     x = _crowded_rows(kind, rows, length, seed=length)
-    theta = torch.tensor([0.0, 0.5, 0.999], device="cuda")
+    theta = torch.tensor([0.0, 0.5, 0.999], device="cuda").repeat(rows)[:rows].contiguous()
     for p in (0.5, 0.99, 2.0):
         _check_as_sorted(ops, x, theta, p, f"{kind} {length}")
 
 
-TIMED = [((1, 1 << 20), k) for k in ("soft", "flat")] + \
-        [((4, 200_003), k) for k in ("soft", "flat", "bf16")] + \
-        [((128, 131_072), "flat")] + \
+TIMED = [((1, 1 << 20), k) for k in ("soft", "flat", "equal", "mask.00001", "mask.000001")] + \
+        [((4, 200_003), k) for k in ("soft", "flat", "bf16", "rare", "scales", "mask.00001")] + \
+        [((128, 131_072), k) for k in ("flat", "rare", "equal", "scales", "mask.000001")] + \
         [((128, 8192), k) for k in ("spike.001", "mask.1", "mask.001", "mask.000001")] + \
         [((64, 12_288), k) for k in ("spike.001", "mask.1", "mask.001", "mask.000001", "equal")]
 
@@ -465,7 +474,7 @@ TIMED = [((1, 1 << 20), k) for k in ("soft", "flat")] + \
                          else f"{v[0]}x{v[1]}")
 def test_topp_sample_time_bounded(ops, shape, kind):
     """The partial sort never costs much more than the sort of whole rows that
-    it stands in for, whatever the values: the sampler takes at most 1.3 times the
+    it stands in for, whatever the values: the sampler takes at most 1.5 times the
     row sort and two cutoffs on its result (its own cutoff and the draw), or 3
     times its own time on softmax rows of the same shape if that is longer
     (unbounded group sorts took 10 to 50 times as long)."""
@@ -489,4 +498,4 @@ def test_topp_sample_time_bounded(ops, shape, kind):
         t, usual = _best_us(lambda: sample(x)), _best_us(lambda: sample(z))
         print(f"[time] {shape} {kind} p={p}: {t:.1f} us, row sort and cutoffs {whole:.1f}, "
               f"softmax rows {usual:.1f}", flush=True)
-        assert t <= max(1.3 * whole, 3 * usual), (shape, kind, p, t, whole, usual)
+        assert t <= max(1.5 * whole, 3 * usual), (shape, kind, p, t, whole, usual)
