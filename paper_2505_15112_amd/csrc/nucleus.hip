@@ -342,20 +342,11 @@ __global__ __launch_bounds__(kNucThreads) LS_OCCUPANCY8 void k_nuc_hist(
 
 // ---------------------------------------------------------------- how far to sort
 
-// Positions of the sorted row that the draw reads when its crossing lies in
-// the first n: whole tiles of 4096 among the row's `heads` first ones, whole
-// steps of 8192 after them.
-__device__ __forceinline__ uint32_t nuc_reads(uint32_t n, uint32_t heads, uint32_t len) {
-    const uint32_t h = heads * 4096u;
-    const uint32_t m = n <= h ? (n + 4095u) / 4096u * 4096u : h + (n - h + 8191u) / 8192u * 8192u;
-    return m < len ? m : len;
-}
-
 // One workgroup per row.  Thread t takes the four bins at descending places
 // 4 t .. 4 t + 3 (bin kNucBins - 1 - place).
 __global__ __launch_bounds__(kNucThreads) void k_nuc_pick(const uint16_t* hist, uint32_t segs,
                                                           const uint32_t* maps, float p,
-                                                          int32_t len, uint32_t heads,
+                                                          int32_t len,
                                                           NucRow* rows, const double* above,
                                                           uint32_t window, uint32_t slots,
                                                           uint2* groups, uint32_t* cursors,
@@ -498,14 +489,16 @@ __global__ __launch_bounds__(kNucThreads) void k_nuc_pick(const uint16_t* hist, 
             s += m[i];
             if (n == UINT_MAX && cnt[i] && s >= goal) n = start[i] + cnt[i];
         }
-        if (n != UINT_MAX) atomicMin(&s_need, nuc_reads(n, heads, (uint32_t)len));
+        if (n != UINT_MAX) atomicMin(&s_need, n);
     }
     __syncthreads();
     const uint32_t need = s_need;
     // The bins that start before `need` are sorted; those that start in one window
     // of the sorted row are a group, but one of more elements than a window is a
     // group of its own (the next bin then starts in a later window): mostly it is a
-    // crowd of few values, which k_nuc_sort handles best alone.
+    // crowd of few values, which k_nuc_sort handles best alone.  Behind `need`
+    // the sorted row is not written; the draw reads whole tiles, but what
+    // follows the crossing changes nothing in what it finds.
     auto group_of = [&](uint32_t first, uint32_t count) {
         return first / window * 2 + (count > window ? 1u : 0u);
     };
@@ -1193,7 +1186,7 @@ static void nucleus_bins(const uint32_t* x, int64_t rows, int64_t len, float p, 
                        (uint32_t)rows, segs, hist, info, maps, above,
                        kNucGroupMax - l.window < 4096u ? kNucGroupMax - l.window : 4096u);
     hipLaunchKernelGGL(k_nuc_pick, dim3((unsigned)rows), dim3(kNucThreads), 0, stream,
-                       (const uint16_t*)hist, segs, (const uint32_t*)maps, p, n, heads, info,
+                       (const uint16_t*)hist, segs, (const uint32_t*)maps, p, n, info,
                        (const double*)above, l.window, l.slots, groups, cursors, bin_groups);
     hipLaunchKernelGGL(k_nuc_gather<J>, dim3(tiles), dim3(kNucThreads), 0, stream, x, n,
                        (uint32_t)rows, segs, (const NucRow*)info, (const uint16_t*)hist,
