@@ -90,6 +90,29 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
 }
 
+// A value that is the same in every lane, in a scalar register.
+__device__ __forceinline__ uint32_t uni(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+
+// Minimum over the wave with DPP (lanes outside the row / disabled read the
+// largest value), in a scalar register.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp_umin(uint32_t v) {
+    const uint32_t o =
+        (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, CTRL, ROW_MASK, 0xf, false);
+    return o < v ? o : v;
+}
+__device__ __forceinline__ uint32_t wave_reduce_min(uint32_t v) {
+    v = dpp_umin<0x111, 0xf>(v);
+    v = dpp_umin<0x112, 0xf>(v);
+    v = dpp_umin<0x114, 0xf>(v);
+    v = dpp_umin<0x118, 0xf>(v);
+    v = dpp_umin<0x142, 0xa>(v);
+    v = dpp_umin<0x143, 0xc>(v);
+    return lane_read(v, kWave - 1);
+}
+
 // Lanes holding the same 8-bit digit as this lane, when every lane of the
 // wave holds a key: the AND over the digit bits of that bit's ballot,
 // complemented where this lane's bit is 0.  Per bit: e = all ones if the bit

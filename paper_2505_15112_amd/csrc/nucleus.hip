@@ -64,29 +64,6 @@ constexpr uint32_t kNucMaxSegs = 40;  // 2^20 + 3 positions of 32768, 2^18 + 3 o
 // sampled range, and the flag of a row that holds a NaN.
 constexpr int kNucAbove = kNucBins - 2, kNucNan = kNucBins - 1;
 
-// A value that is the same in every lane, in a scalar register.
-__device__ __forceinline__ uint32_t uni(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
-}
-
-// Minimum over the wave with DPP (lanes outside the row / disabled read the
-// largest value), in a scalar register.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ uint32_t dpp_umin(uint32_t v) {
-    const uint32_t o =
-        (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, CTRL, ROW_MASK, 0xf, false);
-    return o < v ? o : v;
-}
-__device__ __forceinline__ uint32_t wave_reduce_min(uint32_t v) {
-    v = dpp_umin<0x111, 0xf>(v);
-    v = dpp_umin<0x112, 0xf>(v);
-    v = dpp_umin<0x114, 0xf>(v);
-    v = dpp_umin<0x118, 0xf>(v);
-    v = dpp_umin<0x142, 0xa>(v);
-    v = dpp_umin<0x143, 0xc>(v);
-    return lane_read(v, kWave - 1);
-}
-
 // Exclusive scan over the workgroup; s_w: one word per wave.  One barrier
 // inside; s_w may be rewritten after the next one.
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* s_w, uint32_t* total) {

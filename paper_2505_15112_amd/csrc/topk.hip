@@ -21,7 +21,7 @@
 // selection over its row).  That route's first round is two kernels: the
 // tiles store their counts, then one workgroup per row adds them.  With
 // k <= 256 the candidates come from one read instead: each tile keeps its
-// keys at or above its own k-th key's top 16 bits (k_topk_tilesel).
+// keys from a bound up that is not above its own k-th key (k_topk_tilesel).
 //
 // No workgroup waits for another during the histogram rounds: each tile
 // writes its 256 digit counts to its own slots, and (on the longer route)
@@ -516,13 +516,13 @@ __global__ __launch_bounds__(TileT::kThreads) LS_OCCUPANCY8 void k_topk_gather(
 }
 
 // The route for small k (rows of up to 2^17 elements, k <= kTopkTileK): one
-// read of each row.  Every tile keeps as candidates its keys whose top 16
-// bits are at least those of the tile's own k-th largest key.  That is a
-// superset of the tile's share of the row's top k: a key below it has k keys
-// of its own tile above it.  Two digit rounds over the largest keys of the
-// tile's 512 groups (or, failing that, over the whole tile, held in registers)
-// find a prefix that is no larger (LDS histograms as in k_topk_count0);
-// the tile writes its candidates to its own kTopkTileSlots slots (keys and
+// read of each row.  Every tile keeps as candidates its keys from a bound up that
+// is no larger than the tile's own k-th largest key.  That is a superset of the
+// tile's share of the row's top k: a key below it has k keys of its own tile
+// above it.  Two digit rounds over the largest keys of the tile's 512 groups find
+// the bound's top 16 bits (LDS histograms as in k_topk_count0); where that keeps
+// more than kTopkTileSlots, up to four rounds over the tile's keys, held in
+// registers, raise it to the k-th largest key.  The tile writes its candidates to its own kTopkTileSlots slots (keys and
 // complemented indices, the two halves of their composites) and their number
 // to tcount (more than the slots: none written, and the row is finished the
 // long way).
@@ -558,23 +558,26 @@ __device__ __forceinline__ void tile_bucket(const uint32_t* s_h, uint32_t need, 
     }
 }
 
+// Bits below the part number when keys up to `range` apart get at most 256 parts.
+__device__ __forceinline__ uint32_t topk_part(uint32_t range) {
+    return range > 255u ? 24u - (uint32_t)__builtin_clz(range) : 0u;
+}
+
 template <class TileT, bool VEC>
 __global__ __launch_bounds__(TileT::kThreads) LS_OCCUPANCY8 void k_topk_tilesel(
     const uint32_t* x, int64_t len, uint32_t segs, uint32_t k, bool largest, uint64_t* cand,
     uint32_t* tcount) {
     static_assert(TileT::kThreads >= kTopkDigits, "one thread per digit");
-    // round 1 counts only the keys of one round-0 bucket: fewer copies, so
-    // that the LDS of 8 workgroups fits a CU (with at most 64 VGPRs, 8 waves
-    // per SIMD: every tile of a 128 x 131072 call resident at once)
-    constexpr int kCopies1 = 2;
-    constexpr int kHist = kTopkCopies * kTopkCopyStride, kHist1 = kCopies1 * kTopkCopyStride;
+    // the LDS of 8 workgroups fits a CU (with at most 64 VGPRs, 8 waves per SIMD:
+    // every tile of a 128 x 131072 call resident at once); the groups' round has
+    // few atomics: two copies, quicker added up
+    constexpr int kCopies0 = 2;
+    constexpr int kHist = kTopkCopies * kTopkCopyStride;
     __shared__ uint32_t s_h[kHist];
-    __shared__ uint32_t s_h1[kHist1];
     __shared__ uint32_t s_part[kTopkDigits / kWave];
-    __shared__ uint32_t s_wtot[TileT::WAVES];
+    __shared__ uint32_t s_wtot[TileT::WAVES], s_least[TileT::WAVES];
     __shared__ uint32_t s_sel;
     for (int i = threadIdx.x; i < kHist; i += TileT::kThreads) s_h[i] = 0;
-    for (int i = threadIdx.x; i < kHist1; i += TileT::kThreads) s_h1[i] = 0;
     const int64_t row = blockIdx.x / segs;
     const uint32_t seg = blockIdx.x - (uint32_t)row * segs;
     const int64_t base = (int64_t)seg * TileT::kElems;
@@ -606,35 +609,24 @@ __global__ __launch_bounds__(TileT::kThreads) LS_OCCUPANCY8 void k_topk_tilesel(
             asm volatile("" : "+v"(v[j][e]));  // the unmasked key is dead here
         }
     }
-    __syncthreads();  // histograms cleared
     const uint32_t need = k < (uint32_t)valid ? k : (uint32_t)valid;
     // First the tile's 512 groups (a thread's keys, or two halves of them) stand
     // in for the keys: the need-th largest of their largest keys is no more
     // than the tile's need-th largest key, since need groups hold a key at
-    // least that large.  Two LDS atomics a thread instead of one a key: the
-    // tile kernel of 128 x 131072 at k = 64 takes 16.6 instead of 19.6 us (the
-    // call 26.2 -> 23.8).  On
-    // keys in no order about need (1 + need / 1024) are kept; should the large
-    // keys lie together (or a ragged tile have too few groups) so that more than
-    // the tile's slots are, every key is counted.
+    // least that large.  Two LDS atomics a thread instead of one a key, in one
+    // round over 256 parts of their range: the call on 128 x 131072 at k = 64 takes
+    // 23.5 us, 23.8 with a round each for the top two bytes, 26.2 with every key
+    // counted in two such rounds.  On keys in no order about need (1 + need / 1024)
+    // are kept; should the large keys lie together (or a ragged tile have too few
+    // groups) so that more than the tile's slots are, the bound is raised by
+    // rounds over the kept keys, until they are few enough or one value.  Sorted
+    // or nearly constant rows, every key counted / this way, us: 128 x 131072 sorted,
+    // k = 256, 51.3 / 30.4; 300 x 8192 constant 41.1 / 36.5, sorted at k = 64 14.0 /
+    // 16.4 (260 keys are kept in place of 64, which the finisher then sorts).
     constexpr int kParts = 512 / TileT::kThreads;
     static_assert(kParts >= 1 && TileT::J % kParts == 0, "512 groups of whole chunks");
-    Mask take = 0;
-    uint32_t lpos = 0, total = 0;  // this lane's first slot in the tile
-    for (bool all = false;; all = true) {  // at most twice, uniform
-        uint32_t tid = threadIdx.x;
-        asm volatile("" : "+v"(tid));  // as the keys below
-        const uint32_t w = tid / kWave;
-        if (all) {
-            for (uint32_t i = tid; i < kHist; i += TileT::kThreads) s_h[i] = 0;
-            for (uint32_t i = tid; i < kHist1; i += TileT::kThreads) s_h1[i] = 0;
-            __syncthreads();  // histograms cleared
-        }
-#pragma unroll
-        for (int j = 0; j < TileT::J; ++j)
-#pragma unroll
-            for (int e = 0; e < TileT::V; ++e)  // nothing derived from the keys outlives a round
-                asm volatile("" : "+v"(v[j][e]));
+    uint32_t least, high;  // the bound and the largest key, uniform
+    {
         uint32_t top[kParts];  // the largest key of each of the thread's groups
 #pragma unroll
         for (int q = 0; q < kParts; ++q) {
@@ -644,44 +636,55 @@ __global__ __launch_bounds__(TileT::kThreads) LS_OCCUPANCY8 void k_topk_tilesel(
 #pragma unroll
                 for (int e = 0; e < TileT::V; ++e) top[q] = v[j][e] > top[q] ? v[j][e] : top[q];
         }
-        // round 0: the top byte of every counted key
-        if (all) {
-            uint32_t* h = s_h + (tid & (kTopkCopies - 1)) * kTopkCopyStride;
+        // their range (without the groups that hold padding alone) is cut into
+        // at most 256 parts
+        uint32_t mn = 0xFFFFFFFFu, mx = 0;
 #pragma unroll
-            for (int j = 0; j < TileT::J; ++j)
-#pragma unroll
-                for (int e = 0; e < TileT::V; ++e) atomicAdd(&h[v[j][e] >> 24], 1u);
-            __syncthreads();
-            tile_bucket<kTopkCopies>(s_h, need, s_part, &s_sel);
-        } else {  // few atomics: two copies, quicker added up
-            uint32_t* h = s_h + (tid & (kCopies1 - 1)) * kTopkCopyStride;
-#pragma unroll
-            for (int q = 0; q < kParts; ++q) atomicAdd(&h[top[q] >> 24], 1u);
-            __syncthreads();
-            tile_bucket<kCopies1>(s_h, need, s_part, &s_sel);
+        for (int q = 0; q < kParts; ++q) {
+            mn = top[q] - 1u < mn ? top[q] - 1u : mn;
+            mx = top[q] > mx ? top[q] : mx;
         }
-        __syncthreads();  // s_sel written
-        const uint32_t sel = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_sel);
-        const uint32_t d = sel & 255u, need1 = sel >> 8;
-        // round 1: the second byte of those in bucket d
-        uint32_t* h1 = s_h1 + (tid & (kCopies1 - 1)) * kTopkCopyStride;
-        if (all) {
-#pragma unroll
-            for (int j = 0; j < TileT::J; ++j)
-#pragma unroll
-                for (int e = 0; e < TileT::V; ++e)
-                    if ((v[j][e] >> 24) == d) atomicAdd(&h1[(v[j][e] >> 16) & 255u], 1u);
-        } else {
-#pragma unroll
-            for (int q = 0; q < kParts; ++q)
-                if ((top[q] >> 24) == d) atomicAdd(&h1[(top[q] >> 16) & 255u], 1u);
+        mn = wave_reduce_min(mn);
+        mx = ~wave_reduce_min(~mx);
+        if (lane_id() == 0) {
+            s_least[threadIdx.x / kWave] = mn;
+            s_wtot[threadIdx.x / kWave] = mx;
         }
+        if (threadIdx.x == 0) s_sel = 0;
+        __syncthreads();  // and the histogram cleared
+        least = s_least[0];
+        high = s_wtot[0];
+#pragma unroll
+        for (int q = 1; q < TileT::WAVES; ++q) {
+            least = s_least[q] < least ? s_least[q] : least;
+            high = s_wtot[q] > high ? s_wtot[q] : high;
+        }
+        least = uni(least) + 1u;  // all padding: 0
+        high = uni(high);
+        const uint32_t sh = topk_part(high - least);
+        uint32_t* h = s_h + (threadIdx.x & (kCopies0 - 1)) * kTopkCopyStride;
+#pragma unroll
+        for (int q = 0; q < kParts; ++q)
+            if (top[q] >= least) atomicAdd(&h[(top[q] - least) >> sh], 1u);
         __syncthreads();
-        tile_bucket<kCopies1>(s_h1, need1, s_part, &s_sel);
-        __syncthreads();
-        const uint32_t p16 =
-            (d << 8) | ((uint32_t)__builtin_amdgcn_readfirstlane((int)s_sel) & 255u);
-        const uint32_t least = p16 << 16;
+        tile_bucket<kCopies0>(s_h, need, s_part, &s_sel);
+        __syncthreads();  // s_sel written (0: fewer groups than need)
+        const uint32_t sel = uni(s_sel);
+        least = sel ? least + ((sel & 255u) << sh) : 0u;
+    }
+    Mask take = 0;
+    uint32_t lpos = 0, total = 0;  // this lane's first slot in the tile
+    // the need-th largest key is the rest-th largest of those in [least, high]
+    uint32_t rest = need;
+    for (bool again = false;; again = true) {  // at most five times, uniform
+        uint32_t tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));  // as the keys below
+        const uint32_t w = tid / kWave;
+#pragma unroll
+        for (int j = 0; j < TileT::J; ++j)
+#pragma unroll
+            for (int e = 0; e < TileT::V; ++e)  // nothing derived from the keys outlives a round
+                asm volatile("" : "+v"(v[j][e]));
         take = 0;
 #pragma unroll
         for (int j = 0; j < TileT::J; ++j) {
@@ -713,8 +716,43 @@ __global__ __launch_bounds__(TileT::kThreads) LS_OCCUPANCY8 void k_topk_tilesel(
             lpos += (uint32_t)q < w ? s_wtot[q] : 0u;
             total += s_wtot[q];
         }
-        if (all || total <= kTopkTileSlots) break;
-        __syncthreads();  // s_wtot and the histograms are rewritten
+        if (total <= kTopkTileSlots) break;
+        // Too many: [least, high] is cut into at most 256 parts, and the part that
+        // holds the need-th largest key has the next bound (padding counts as key
+        // 0: not above any).  One value alone cannot be cut.
+        for (uint32_t i = tid; i < kHist; i += TileT::kThreads) s_h[i] = 0;
+        if (again) {  // the largest key in the part
+            uint32_t mx = 0;
+#pragma unroll
+            for (int j = 0; j < TileT::J; ++j)
+#pragma unroll
+                for (int e = 0; e < TileT::V; ++e)
+                    mx = v[j][e] <= high && v[j][e] > mx ? v[j][e] : mx;
+            mx = ~wave_reduce_min(~mx);
+            if ((tid & (kWave - 1)) == 0) s_least[w] = mx;
+            __syncthreads();
+            high = s_least[0];
+#pragma unroll
+            for (int q = 1; q < TileT::WAVES; ++q) high = s_least[q] > high ? s_least[q] : high;
+            high = uni(high);
+        }
+        if (high == least) break;
+        const uint32_t range = high - least, sh = topk_part(range);
+        __syncthreads();  // histogram cleared
+        uint32_t* h = s_h + (tid & (kTopkCopies - 1)) * kTopkCopyStride;
+#pragma unroll
+        for (int j = 0; j < TileT::J; ++j)
+#pragma unroll
+            for (int e = 0; e < TileT::V; ++e)
+                if (v[j][e] - least <= range) atomicAdd(&h[(v[j][e] - least) >> sh], 1u);
+        __syncthreads();
+        tile_bucket<kTopkCopies>(s_h, rest, s_part, &s_sel);
+        __syncthreads();  // s_sel written
+        const uint32_t sel = uni(s_sel);
+        rest = sel >> 8;
+        least += (sel & 255u) << sh;
+        const uint32_t part = (1u << sh) - 1u;
+        high = part < high - least ? least + part : high;
     }
     if (threadIdx.x == 0) tcount[blockIdx.x] = total;
     if (total > kTopkTileSlots) return;  // uniform: the row goes the long way

@@ -107,22 +107,23 @@ def test_topk_misaligned_small_k(ops):
 
 
 @pytest.mark.parametrize("n_t", [1024, 1025])
+@pytest.mark.parametrize("values", [1, 64])
 @pytest.mark.parametrize("largest", [True, False])
-def test_topk_tile_slot_edges(ops, n_t, largest):
-    """On the small-k route every 8192-element tile keeps its keys whose top 16
-    key bits are at least its own k-th key's, in 1024 slots; a tile with more
-    sends its row the long way.  Here one tile of the middle row holds n_t
-    values sharing their top 16 bits (2 + i * 2^-20), with ties among them,
-    above (below, for the smallest k) the rest of the row, which is normal
-    data of small magnitude."""
-    announce("topk tile slots", n_t, largest)
+def test_topk_tile_slot_edges(ops, n_t, values, largest):
+    """On the small-k route every 8192-element tile keeps its keys from a bound up
+    that is raised as far as its own k-th key while they are more than 1024 slots
+    hold; a tile with more all the same sends its row the long way.  Here one tile
+    of the middle row holds n_t values sharing their top 16 bits (2 + i * 2^-20),
+    one value or 64 with ties among them, above (below, for the smallest k) the
+    rest of the row, which is normal data of small magnitude."""
+    announce("topk tile slots", n_t, values, largest)
     rows, length, k = 3, 131_072, 100
     rng = np.random.default_rng(n_t)
     x = (W.values_f32(rows * length, seed=n_t).reshape(rows, length) * 0.1).astype(np.float32)
     pos = 5 * 8192 + rng.choice(8192, n_t, replace=False)
-    big = (2.0 + rng.integers(0, 64, n_t) * 2.0**-20).astype(np.float32)
+    big = (2.0 + rng.integers(0, values, n_t) * 2.0**-20).astype(np.float32)
     x[1, pos] = big if largest else -big
-    _check(ops, x, k, largest, f"tile slots n_t={n_t} largest={largest}")
+    _check(ops, x, k, largest, f"tile slots n_t={n_t} values={values} largest={largest}")
 
 
 @pytest.mark.parametrize("k", [64, 4096])
@@ -194,17 +195,32 @@ def test_topk_long_way_close_values(ops, k):
 
 
 @pytest.mark.parametrize("length", [4096, 8192, 16_384, 20_000, 24_576 + 300, 131_072])
-@pytest.mark.parametrize("order", ["descending", "ascending", "blocks"])
+@pytest.mark.parametrize("order", ["descending", "ascending", "blocks", "close", "two", "nan"])
 def test_topk_tile_groups(ops, length, order):
     """The small-k route first lets the largest keys of a tile's 512 groups stand
     in for its keys: rows whose large keys lie together (sorted, or in blocks)
-    keep too many that way and are counted whole; k on both sides of that, whole
-    and ragged last tiles, tiles with fewer groups than k."""
+    keep too many that way and the bound is raised by rounds over the keys; k on
+    both sides of that, whole and ragged last tiles, tiles with fewer groups than
+    k; keys that need several rounds (a run of close values and one far above
+    them), that no round parts (two values), and the largest and smallest keys."""
     announce("topk tile groups", length, order)
     x = W.values_f32(3 * length, seed=length).reshape(3, length)
     if order == "blocks":  # 300 large keys in a run across a tile edge
         at = min(8192, length) - 150
         x[:, at:at + 300] += 100.0
+    elif order == "close":  # 2000 values 2^-22 apart, in a run; one of 10^30
+        rng = np.random.default_rng(length)
+        x = (x * 0.1).astype(np.float32)
+        x[:, 1000:3000] = 2.0 + rng.integers(0, 1 << 14, (3, 2000)) * 2.0**-22
+        x[:, 17] = 1e30
+        x[:, 18] = -1e30
+    elif order == "two":
+        x = (x > 0).astype(np.float32)
+    elif order == "nan":  # NaN of both signs: the largest and the smallest codes
+        x = np.sort(x, axis=1)
+        x[:, -700:] = np.nan
+        x[:, :700] = -np.float32(np.nan)
+        x[:, ::11] = np.float32(np.inf)
     else:
         x = np.sort(x, axis=1)
         x = x[:, ::-1] if order == "descending" else x
