@@ -29,15 +29,17 @@
 // elements of each row gathered): histogram 20 us, pick 9, gather 27 (105 MB
 // moved), sort 24, and the draw 5 + 9; the call 272 us by the row sort, 92 us
 // this way.  4 x 200003: 93 -> 43 us, each of the six kernels a few us of
-// latency.  Rows whose elements crowd at few values cost more (128 x 131072 equal
-// 166 us, flat rows with a tenth of zeros 190 to 290), but hardly ever more than
-// the row sort and the draw on it (300 to 390): up to 1.15 times, and 1 x 2^20 with
-// 99 % zeros sorted to its end 147 us for 100.  Only rows in which a structure that
+// latency.  Rows whose elements crowd at few values cost more, but no more than
+// the row sort, within a few per cent, up to 2^18 elements: 128 x 131072 equal 367 -> 161 us, flat with a tenth
+// of zeros 345 -> 222, 4 x 200003 147 -> 154.  At 2^20 one workgroup counts such a
+// crowd: 1 x 2^20 equal 275 -> 364, flat with zeros 244 -> 557, 16 of them 610 -> 776;
+// rows of 2^20 sorted to their end take up to 1.15 times the row sort, ordinary ones
+// at p = 0.9 87 -> 57 (1) and 296 -> 175 (16).  Only rows in which a structure that
 // follows the 512 places of the sample hides most elements from it take 3 to 50
-// times as long (windows, see nuc_window).  Measured on the way: the elements scattered to their bins by LDS
-// counters instead of gathered (one 8-byte store per lane and line): 62 us for
-// the scatter; a workgroup for every group a row could have, most of them
-// without work: 9 ns each, 26 us.
+// times as long (windows, see nuc_window).  Measured on the way: the elements
+// scattered to their bins by LDS counters instead of gathered (one 8-byte store
+// per lane and line): 62 us for the scatter; a workgroup for every group a row
+// could have, most of them without work: 9 ns each, 26 us.
 #include <limits.h>
 
 #include <type_traits>
