@@ -463,6 +463,27 @@ def test_topp_sample_many_groups(ops, rows, length, kind):
         _check_as_sorted(ops, x, theta, p, f"{kind} {length}")
 
 
+@pytest.mark.parametrize("length", [4097, 12_289, 131_072, 1 << 20])
+def test_topp_sample_scratch_contents(ops, length):
+    """What the scratch holds before the call (the sorted row is written as far as
+    the crossing only) changes nothing: infinities, NaN, large values of both signs."""
+    import torch
+    from paper_2505_15112_amd import _lib
+    announce("topp scratch contents", length)
+    rows = 3
+    x = torch.cat([_crowded_rows(k, 1, length, seed=3) for k in ("soft", "rare", "flat")])
+    theta = torch.tensor([0.999, 0.5, 0.999], device="cuda")
+    scr = ops.scratch(_lib.OP_TOPP_SAMPLE, x.device, rows, length)
+    for p in (0.05, 0.9):
+        got = []
+        for bits in (0, 0x7F800000, 0x7FC00000, 0x7F7FFFFF, 0x7F7FFFFF - 2**31, -1):
+            scr.view(torch.int32).fill_(bits)
+            got.append(ops.topp_sample_f32(x, theta, p, with_cutoff=True, scratch_buf=scr))
+        for tok, cut in got[1:]:
+            assert torch.equal(tok, got[0][0]) and torch.equal(cut, got[0][1]), (length, p)
+        _check_as_sorted(ops, x, theta, p, f"scratch {length}")
+
+
 TIMED = [((1, 1 << 20), k) for k in ("soft", "flat", "equal", "mask.00001", "mask.000001")] + \
         [((4, 200_003), k) for k in ("soft", "flat", "bf16", "rare", "scales", "mask.00001")] + \
         [((128, 131_072), k) for k in ("flat", "rare", "equal", "scales", "mask.000001")] + \
@@ -474,8 +495,8 @@ TIMED = [((1, 1 << 20), k) for k in ("soft", "flat", "equal", "mask.00001", "mas
                          else f"{v[0]}x{v[1]}")
 def test_topp_sample_time_bounded(ops, shape, kind):
     """The partial sort never costs much more than the sort of whole rows that
-    it stands in for, whatever the values: the sampler takes at most 1.5 times (rows
-    of 2^20, whose crowds one workgroup counts: 2.5 times) the row sort and two
+    it stands in for, whatever the values: the sampler takes at most twice (rows of
+    2^20, whose crowds one workgroup counts: 3 times) the row sort and two
     cutoffs on its result (its own cutoff and the draw), or 3 times its own time
     on softmax rows of the same shape if that is longer
     (unbounded group sorts took 10 to 50 times as long)."""
@@ -499,4 +520,4 @@ def test_topp_sample_time_bounded(ops, shape, kind):
         t, usual = _best_us(lambda: sample(x)), _best_us(lambda: sample(z))
         print(f"[time] {shape} {kind} p={p}: {t:.1f} us, row sort and cutoffs {whole:.1f}, "
               f"softmax rows {usual:.1f}", flush=True)
-        assert t <= max((2.5 if length == 1 << 20 else 1.5) * whole, 3 * usual), (shape, kind, p, t, whole, usual)
+        assert t <= max((3 if length == 1 << 20 else 2) * whole, 3 * usual), (shape, kind, p, t, whole, usual)

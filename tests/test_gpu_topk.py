@@ -92,8 +92,7 @@ def test_topk_misaligned(ops):
 
 
 def test_topk_misaligned_small_k(ops):
-    """The small-k route on misaligned rows (element-wise loads, twice the
-    waves per tile)."""
+    """The small-k route on misaligned rows (twice the waves per tile)."""
     announce("topk misaligned small k")
     flat = _rows(1, 3 * 70_000 + 1, seed=12, kind="normal").reshape(-1)
     d = to_dev(flat)[1:].reshape(3, 70_000)
