@@ -662,8 +662,8 @@ def main():
             ws_clean(ws_smp, "samplers")
             # top-k of the same rows.  Algorithmic: one read of each row and the k
             # values and indices written per row.  For k <= 256 the implementation
-            # reads each row once (every tile keeps its keys at or above its own
-            # k-th key's top 16 bits); for larger k it reads the rows twice (one
+            # reads each row once (every tile keeps its keys from a bound up that is
+            # not above its own k-th key); for larger k it reads the rows twice (one
             # digit-count round, then the gather of the keys at or above the
             # k-th's top byte).  Either way the candidates are then selected and
             # ordered per row in LDS: reported beside it, without the
