@@ -11,8 +11,8 @@
 //    tile's elements are counted per bin;
 //  * k_nuc_pick, one workgroup per row: the bins in descending order, the
 //    first at which a lower bound of the running sum (each element counted as
-//    its bin's least key) passes p, hence how many elements the draw reads, and
-//    where each tile's share of them goes;
+//    its bin's least key) passes p, hence how many elements the draw needs, and
+//    the groups that they form;
 //  * k_nuc_gather: those elements, keys and source indices, to the row's list,
 //    group by group (some thousand elements: the bins that start in one window of
 //    the sorted row);
@@ -20,9 +20,9 @@
 //    order.
 // Workgroups are numbered tile by tile (or group by group) of all rows, so that
 // with a multiple of 8 rows everything of one row runs on one XCD and finds the
-// row's list in its L2.  Rows of up to kNucGroupMax elements are one group, sorted whole by
-// k_nuc_sort_row alone.  The draw (rows.hip) then runs on the sorted keys with
-// the same additions as on a whole sorted row, so its results are the same.
+// row's list in its L2.  Rows of up to kNucGroupMax elements are one group, sorted
+// whole by k_nuc_sort_row alone.  The draw (rows.hip) then runs on the sorted keys
+// with the same additions as on a whole sorted row, so its results are the same.
 //
 // Bound: two reads of the rows from HBM (22 us for 128 x 131072) and the LDS
 // work of the sort.  Kernel times at 128 x 131072, p = 0.9 (about 38000
@@ -30,16 +30,17 @@
 // moved), sort 24, and the draw 5 + 9; the call 272 us by the row sort, 92 us
 // this way.  4 x 200003: 93 -> 43 us, each of the six kernels a few us of
 // latency.  Rows whose elements crowd at few values cost more, but no more than
-// the row sort, within a few per cent, up to 2^18 elements: 128 x 131072 equal 367 -> 161 us, flat with a tenth
-// of zeros 345 -> 222, 4 x 200003 147 -> 154.  At 2^20 one workgroup counts such a
-// crowd: 1 x 2^20 equal 275 -> 364, flat with zeros 244 -> 557, 16 of them 610 -> 776;
-// rows of 2^20 sorted to their end take up to 1.15 times the row sort, ordinary ones
-// at p = 0.9 87 -> 57 (1) and 296 -> 175 (16).  Only rows in which a structure that
-// follows the 512 places of the sample hides most elements from it take 3 to 50
-// times as long (windows, see nuc_window).  Measured on the way: the elements
-// scattered to their bins by LDS counters instead of gathered (one 8-byte store
-// per lane and line): 62 us for the scatter; a workgroup for every group a row
-// could have, most of them without work: 9 ns each, 26 us.
+// the row sort, within a few per cent, up to 2^18 elements: 128 x 131072 equal
+// 367 -> 161 us, flat with a tenth of zeros 345 -> 222, 4 x 200003 147 -> 154.  At
+// 2^20 one workgroup counts such a crowd: 1 x 2^20 equal 275 -> 364, flat with zeros
+// 244 -> 557, 16 of them 610 -> 776; rows of 2^20 sorted to their end take up to 1.15
+// times the row sort, ordinary ones at p = 0.9 87 -> 57 (1) and 296 -> 175 (16).
+// Only rows in which a structure that follows the 512 places of the sample hides
+// most elements from it take 3 to 50 times as long (windows, see nuc_window).
+// Measured on the way: the elements scattered to their bins by LDS counters
+// instead of gathered (one 8-byte store per lane and line): 62 us for the
+// scatter; a workgroup for every group a row could have, most of them without
+// work: 9 ns each, 26 us.
 #include <limits.h>
 
 #include <type_traits>
@@ -869,11 +870,10 @@ static_assert(kNucParts <= kNucSlots / 2 && kNucParts == 4 * kNucThreads, "four 
 
 // Keys of fewer than kNucParts values, [lo, hi], in descending order to out[0,
 // room): each value is counted and written as often as it is there.  The other
-// keys of lk[0, m) are above hi; `room` are not.  (Crowds
-// are what makes large groups: equal elements, masked zeros, flat rows.  In
-// windows, three reads of the list each, the call on softmax of N(0, 10^-5) with a
-// tenth of the row zero took 31.4 ms at 1 x 2^20 and 1.37 ms at 128 x 131072, now
-// 0.43 and 0.23.)
+// keys of lk[0, m) are above hi; `room` are not.  (Crowds are what makes large
+// groups: equal elements, masked zeros, flat rows.  In windows, three reads of the
+// list each, the call on softmax of N(0, 10^-5) with a tenth of the row zero took
+// 31.4 ms at 1 x 2^20 and 1.37 ms at 128 x 131072; so 0.43 to 0.6 and 0.23.)
 __device__ void nuc_emit(const uint32_t* lk, uint32_t m, uint32_t lo, uint32_t hi, uint32_t* out,
                          uint32_t room, NucSortLds& L) {
     const uint32_t range = hi - lo;

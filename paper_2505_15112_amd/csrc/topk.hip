@@ -522,10 +522,10 @@ __global__ __launch_bounds__(TileT::kThreads) LS_OCCUPANCY8 void k_topk_gather(
 // above it.  Two digit rounds over the largest keys of the tile's 512 groups find
 // the bound's top 16 bits (LDS histograms as in k_topk_count0); where that keeps
 // more than kTopkTileSlots, up to four rounds over the tile's keys, held in
-// registers, raise it to the k-th largest key.  The tile writes its candidates to its own kTopkTileSlots slots (keys and
-// complemented indices, the two halves of their composites) and their number
-// to tcount (more than the slots: none written, and the row is finished the
-// long way).
+// registers, raise it to the k-th largest key.  The tile writes its candidates to
+// its own kTopkTileSlots slots (keys and complemented indices, the two halves of
+// their composites) and their number to tcount (more than the slots: none
+// written, and the row is finished the long way).
 constexpr uint32_t kTopkTileK = 256;
 constexpr uint32_t kTopkTileSlots = 1024;
 static_assert(kTopkTileSlots * kTopkGatherSegs <= kTopkCand, "a row's candidates fit the LDS sort");
